@@ -11,10 +11,9 @@
 // open-addressing table of row ids keyed by the string (a slot keeps the
 // first row that claimed it; a later row with the same string finds it by
 // comparing the words) and records its slot; the occupied slots are
-// compacted to one representative row per distinct string; a bitonic sort
-// orders the representatives by string (tiles of 2048 in LDS with their
-// words, only the stages whose partner lies in another tile in global
-// memory); the position of each becomes the code of its slot and its bytes
+// compacted to one representative row per distinct string; the
+// representatives are sorted by string (tiles of 1024 in LDS, then merges of
+// 16 runs); the position of each becomes the code of its slot and its bytes
 // the dictionary row; finally every row reads its code through its slot.
 // Lookup searches a sample of every S-th dictionary string held in LDS, then
 // the one run of S strings in memory.  Strings compare as sequences of
@@ -27,6 +26,25 @@ namespace tdp {
 namespace {
 
 constexpr int kDictMaxWords = 8;  // 32 bytes
+
+// The W words of one string as they lie in memory: loads of up to 16 bytes
+// when the string starts that aligned.
+template <int W>
+__device__ __forceinline__ void load_raw(const uint32_t* s, bool aligned, uint32_t w[W]) {
+    constexpr int V = W % 4 == 0 ? 4 : W % 2 == 0 ? 2 : 1;
+    typedef uint32_t vec __attribute__((ext_vector_type(V)));
+    if (V > 1 && aligned) {
+#pragma unroll
+        for (int k = 0; k < W; k += V) {
+            const vec q = *(const vec*)(s + k);
+#pragma unroll
+            for (int e = 0; e < V; ++e) w[k + e] = ((const uint32_t*)&q)[e];
+        }
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < W; ++k) w[k] = s[k];
+}
 
 // The W words of one string as big-endian values (zero past W): 16-byte
 // loads when the string starts 16-byte aligned and W is a multiple of 4 (a
@@ -59,12 +77,23 @@ __device__ __forceinline__ int cmp_words(const uint32_t a[kDictMaxWords], const 
     return 0;
 }
 
-__device__ __forceinline__ uint32_t hash_words(const uint32_t w[kDictMaxWords], int W) {
+template <int W>
+__device__ __forceinline__ uint32_t hash_raw(const uint32_t w[W]) {
     uint32_t h = 0x9E3779B9u;
 #pragma unroll
-    for (int k = 0; k < kDictMaxWords; ++k)
-        if (k < W) h = hash32(h ^ w[k]) + (uint32_t)k;
-    return h;
+    for (int k = 0; k < W; ++k) {
+        h = (h ^ w[k]) * 0x85EBCA6Bu;
+        h ^= h >> 15;
+    }
+    return hash32(h);
+}
+
+template <int W>
+__device__ __forceinline__ bool same_raw(const uint32_t a[W], const uint32_t b[W]) {
+    uint32_t d = 0;
+#pragma unroll
+    for (int k = 0; k < W; ++k) d |= a[k] ^ b[k];
+    return d == 0;
 }
 
 __global__ void dict_fill_kernel(int32_t* p, int64_t n, int32_t v, int64_t* d_count, int32_t* status) {
@@ -76,171 +105,315 @@ __global__ void dict_fill_kernel(int32_t* p, int64_t n, int32_t v, int64_t* d_co
     }
 }
 
-// Each row finds or claims the slot of its string; row_slot[i] = the slot.
-__global__ void dict_insert_kernel(const uint32_t* __restrict__ strs, int64_t n, int W, int32_t* table, uint32_t mask,
-                                   int32_t* row_slot, int32_t* status) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        uint32_t w[kDictMaxWords];
-        load_words(strs + i * W, W, w);
-        uint32_t s = hash_words(w, W) & mask;
-        int32_t slot = -1;
-        for (uint32_t probes = 0; probes <= mask; ++probes) {
-            // a claimed slot never changes, so a plain (cached) read that sees
-            // a row is final; one that sees the slot empty may be stale, and
-            // the compare-and-swap then returns the slot's current value
-            int32_t cur = table[s];
-            if (cur < 0) {
-                cur = atomicCAS(&table[s], -1, (int32_t)i);
-                if (cur < 0) {
-                    slot = (int32_t)s;
-                    break;
+// Each row of [first, n) finds or claims the slot of its string;
+// row_slot[i] = the slot.  SEEN: `seen` holds copies of the strings whose
+// slots were claimed by an earlier launch, [slot][W], so a row whose string
+// is among them reads one line of a small array instead of a slot and then a
+// row of the column at a random place (the column's lines, 128 bytes for each
+// row's 16, were the bound of the one-launch form: 235 us for 10M rows of
+// 100K distinct 16-byte strings).  A copy that begins with a zero word is no
+// copy: the slot was free then, or holds the empty string.
+// A thread takes kRows rows at a time, 256 apart, and walks their probe
+// sequences together: a wave lasts as long as its longest sequence, so one
+// row after the other would add up the longest of each.
+template <int W, bool SEEN>
+__global__ __launch_bounds__(256) void dict_insert_kernel(const uint32_t* __restrict__ strs, int64_t first, int64_t n,
+                                                          int32_t* table, uint32_t mask,
+                                                          const uint32_t* __restrict__ seen, int32_t* row_slot,
+                                                          int32_t* status) {
+    constexpr int kRows = SEEN ? (W <= 4 ? 4 : 2) : 1;
+    const int64_t step = 256 * kRows;
+    const bool aligned = ((uintptr_t)strs & 15) == 0;
+    for (int64_t i0 = first + (int64_t)blockIdx.x * step; i0 < n; i0 += (int64_t)gridDim.x * step) {
+        uint32_t w[kRows][W], s[kRows];
+        bool found[kRows];
+#pragma unroll
+        for (int e = 0; e < kRows; ++e) {
+            const int64_t i = i0 + e * 256 + threadIdx.x;
+            load_raw<W>(strs + (i < n ? i : n - 1) * W, aligned, w[e]);
+        }
+#pragma unroll
+        for (int e = 0; e < kRows; ++e) {
+            s[e] = hash_raw<W>(w[e]) & mask;
+            found[e] = false;
+        }
+        uint32_t probes = 0;  // of the rows that probed longest
+        if (SEEN) {
+            bool walk[kRows], any = true;
+#pragma unroll
+            for (int e = 0; e < kRows; ++e) walk[e] = true;
+            for (; any && probes <= mask; ++probes) {
+                uint32_t o[kRows][W];
+#pragma unroll
+                for (int e = 0; e < kRows; ++e)
+                    if (walk[e]) load_raw<W>(seen + (int64_t)s[e] * W, true, o[e]);
+                any = false;
+#pragma unroll
+                for (int e = 0; e < kRows; ++e) {
+                    if (!walk[e]) continue;
+                    found[e] = o[e][0] != 0 && same_raw<W>(w[e], o[e]);
+                    walk[e] = o[e][0] != 0 && !found[e];
+                    if (walk[e]) s[e] = (s[e] + 1) & mask;
+                    any |= walk[e];
                 }
             }
-            uint32_t o[kDictMaxWords];
-            load_words(strs + (int64_t)cur * W, W, o);
-            if (cmp_words(w, o, W) == 0) {
-                slot = (int32_t)s;
-                break;
-            }
-            s = (s + 1) & mask;
         }
-        if (slot < 0) raise_flag(status, TDP_FLAG_TABLE_FULL);
-        row_slot[i] = slot;
+#pragma unroll
+        for (int e = 0; e < kRows; ++e) {
+            const int64_t i = i0 + e * 256 + threadIdx.x;
+            if (i >= n) continue;
+            int32_t slot = found[e] ? (int32_t)s[e] : -1;
+            for (uint32_t p = 0; slot < 0 && p <= mask; ++p) {
+                // a claimed slot never changes, so a plain (cached) read that
+                // sees a row is final; one that sees the slot empty may be
+                // stale, and the compare-and-swap then returns the slot's
+                // current value
+                int32_t cur = table[s[e]];
+                if (cur < 0) cur = atomicCAS(&table[s[e]], -1, (int32_t)i);
+                bool mine = cur < 0;
+                if (!mine) {
+                    uint32_t o[W];
+                    load_raw<W>(strs + (int64_t)cur * W, aligned, o);
+                    mine = same_raw<W>(w[e], o);
+                }
+                if (mine) slot = (int32_t)s[e];
+                else s[e] = (s[e] + 1) & mask;
+            }
+            if (slot < 0) raise_flag(status, TDP_FLAG_TABLE_FULL);
+            row_slot[i] = slot;
+        }
+    }
+}
+
+// Copies of the claimed slots' strings (zeros for free slots).
+__global__ void dict_seen_kernel(const uint32_t* __restrict__ strs, int W, const int32_t* table, int64_t n_slots,
+                                 uint32_t* seen) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n_slots * W; e += stride) {
+        const int32_t r = table[e / W];
+        seen[e] = r >= 0 ? strs[(int64_t)r * W + e % W] : 0u;
     }
 }
 
 // One representative row per occupied slot, in any order; more than `cap`
-// distinct strings raise the flag.
-// (A wave reserves its occupied slots' positions with one atomic add.)
-__global__ void dict_compact_kernel(const int32_t* table, int64_t n_slots, int32_t* reps, int64_t cap,
-                                    int64_t* d_count, int32_t* status) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t s0 = (int64_t)blockIdx.x * blockDim.x; s0 < n_slots; s0 += stride) {
-        const int64_t s = s0 + threadIdx.x;
-        const int32_t r = s < n_slots ? table[s] : -1;
-        const uint64_t m = ballot(r >= 0);
-        if (m == 0) continue;
-        unsigned long long first = 0;
-        if (lane_id() == 0) first = atomicAdd((unsigned long long*)d_count, (unsigned long long)__popcll(m));
-        first = __shfl(first, 0, kWave);
-        if (r < 0) continue;
-        const int64_t k = (int64_t)first + lanes_below(m);
-        if (k < cap) reps[k] = r;
-        else raise_flag(status, TDP_FLAG_TABLE_FULL);
-    }
-}
+// distinct strings raise the flag.  A workgroup reserves the positions of its
+// 4096 slots with one atomic add: an add per wave serialised on the one
+// counter (51 us for 2^18 slots; 5 us now).
+constexpr int kCompactThreads = 1024;
 
-// Representatives beyond the count (or beyond the capacity, when more
-// distinct strings arrived than it holds) become the sentinel -1, sorted last.
-__global__ void dict_pad_kernel(int32_t* reps, int64_t sort_n, const int64_t* d_count, int64_t cap) {
-    const int64_t d = *d_count < cap ? *d_count : cap;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < sort_n; i += stride)
-        if (i >= d) reps[i] = -1;
-}
-
-// One compare-exchange stage (k, j) of the bitonic sort of representative
-// rows by their strings (ascending; the sentinel -1 is largest).
-__global__ void dict_bitonic_kernel(const uint32_t* __restrict__ strs, int W, int32_t* reps, int64_t sort_n,
-                                    int64_t k, int64_t j) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < sort_n; i += stride) {
-        const int64_t l = i ^ j;
-        if (l <= i) continue;
-        const int32_t a = reps[i], b = reps[l];
-        int c;
-        if (a < 0 || b < 0) {
-            c = (a < 0) == (b < 0) ? 0 : (a < 0 ? 1 : -1);
-        } else {
-            uint32_t wa[kDictMaxWords], wb[kDictMaxWords];
-            load_words(strs + (int64_t)a * W, W, wa);
-            load_words(strs + (int64_t)b * W, W, wb);
-            c = cmp_words(wa, wb, W);
-        }
-        const bool up = (i & k) == 0;
-        if ((up && c > 0) || (!up && c < 0)) {
-            reps[i] = b;
-            reps[l] = a;
-        }
-    }
-}
-
-// The stages of the same bitonic network whose partners lie within one tile
-// of representatives, in LDS (words as [W][tile], so lanes read consecutive
-// addresses).  k == 0: every stage of every merge size up to the tile (the
-// tiles come out sorted, alternately ascending and descending as the network
-// needs); else the stages j < tile of merge size k.  A tile is 2048
-// representatives, 1024 for 32-byte strings, so that it fits 64 KiB of LDS.
-constexpr int kSortThreads = 1024;
-constexpr int kSortLdsBytes = 64 * 1024;
-
-int64_t sort_tile(int64_t sort_n, int W) {
-    int64_t tile = 2048;
-    while (tile * (W + 1) * (int64_t)sizeof(uint32_t) > kSortLdsBytes) tile >>= 1;
-    return std::min(sort_n, tile);
-}
-
-__device__ __forceinline__ int cmp_lds(const uint32_t* sw, const int32_t* si, int tile, int W, int a, int b) {
-    const int32_t ia = si[a], ib = si[b];
-    if (ia < 0 || ib < 0) return (ia < 0) == (ib < 0) ? 0 : (ia < 0 ? 1 : -1);
-    for (int k = 0; k < W; ++k) {
-        const uint32_t x = sw[k * tile + a], y = sw[k * tile + b];
-        if (x != y) return x < y ? -1 : 1;
-    }
-    return 0;
-}
-
-__global__ __launch_bounds__(kSortThreads) void dict_sort_local_kernel(const uint32_t* __restrict__ strs, int W,
-                                                                       int32_t* reps, int tile, int64_t k) {
-    extern __shared__ uint32_t s_sort[];
-    uint32_t* sw = s_sort;                       // [W][tile]
-    int32_t* si = (int32_t*)(s_sort + W * tile);  // [tile]
-    const int64_t base = (int64_t)blockIdx.x * tile;
-    for (int e = threadIdx.x; e < tile; e += blockDim.x) {
-        const int32_t r = reps[base + e];
-        si[e] = r;
-        for (int q = 0; q < W; ++q) sw[q * tile + e] = r >= 0 ? __builtin_bswap32(strs[(int64_t)r * W + q]) : 0u;
-    }
-    __syncthreads();
-    auto stage = [&](int64_t kk, int j) {
-        for (int t = threadIdx.x; t < tile / 2; t += blockDim.x) {
-            const int i = ((t & ~(j - 1)) << 1) | (t & (j - 1));
-            const int l = i | j;
-            const bool up = ((base + i) & kk) == 0;
-            const int c = cmp_lds(sw, si, tile, W, i, l);
-            if ((up && c > 0) || (!up && c < 0)) {
-                const int32_t x = si[i];
-                si[i] = si[l];
-                si[l] = x;
-                for (int q = 0; q < W; ++q) {
-                    const uint32_t y = sw[q * tile + i];
-                    sw[q * tile + i] = sw[q * tile + l];
-                    sw[q * tile + l] = y;
-                }
+__global__ __launch_bounds__(kCompactThreads) void dict_compact_kernel(const int32_t* table, int64_t n_slots,
+                                                                       int32_t* reps, int64_t cap, int64_t* d_count,
+                                                                       int32_t* status) {
+    __shared__ uint32_t s_wave[kCompactThreads / kWave];
+    __shared__ unsigned long long s_first;
+    const int wave = threadIdx.x / kWave;
+    const int64_t step = (int64_t)kCompactThreads * 4;
+    for (int64_t s0 = (int64_t)blockIdx.x * step; s0 < n_slots; s0 += (int64_t)gridDim.x * step) {
+        const int64_t s = s0 + threadIdx.x * 4;  // n_slots is a multiple of 4
+        int4 r = make_int4(-1, -1, -1, -1);
+        if (s < n_slots) r = *(const int4*)&table[s];
+        uint32_t below, total;
+        wave_count_scan<3>((uint32_t)((r.x >= 0) + (r.y >= 0) + (r.z >= 0) + (r.w >= 0)), below, total);
+        if (lane_id() == 0) s_wave[wave] = total;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            uint32_t sum = 0;
+            for (int w = 0; w < kCompactThreads / kWave; ++w) {
+                const uint32_t c = s_wave[w];
+                s_wave[w] = sum;
+                sum += c;
             }
+            s_first = sum ? atomicAdd((unsigned long long*)d_count, (unsigned long long)sum) : 0;
         }
         __syncthreads();
-    };
-    if (k == 0) {
-        for (int kk = 2; kk <= tile; kk <<= 1)
-            for (int j = kk >> 1; j > 0; j >>= 1) stage(kk, j);
-    } else {
-        for (int j = tile >> 1; j > 0; j >>= 1) stage(k, j);
+        int64_t k = (int64_t)s_first + s_wave[wave] + below;
+        const int32_t v[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (v[e] < 0) continue;
+            if (k < cap) reps[k] = v[e];
+            else raise_flag(status, TDP_FLAG_TABLE_FULL);
+            ++k;
+        }
+        __syncthreads();
     }
-    for (int e = threadIdx.x; e < tile; e += blockDim.x) reps[base + e] = si[e];
 }
 
-// Position r of the sorted representatives: the code of its slot and the
-// dictionary's row r.
-__global__ void dict_rank_kernel(const uint32_t* __restrict__ strs, int W, const int32_t* reps, const int64_t* d_count,
-                                 int64_t cap, const int32_t* row_slot, int32_t* slot_code, uint32_t* dict) {
+// The representatives are sorted by tiles of kTile in LDS, then by merges of
+// kMergeWay sorted runs at a time in which every representative finds its
+// place by binary searches of the other runs of its group: one launch per
+// factor of kMergeWay (two for 100K strings, where a bitonic network over the
+// same tiles took 28 launches and 212 us).  A launch works on the first
+// *d_count representatives (at most cap) and does little past them.
+constexpr int kTile = 1024;
+constexpr int kSortThreads = kTile / 2;
+constexpr int kMergeWay = 16;
+constexpr int kMergeWaves = 4;  // waves that share the searches of 64 representatives
+
+// Word pair p of a string, most significant word first.
+__device__ __forceinline__ uint64_t load_pair(const uint32_t* s, int W, int p) {
+    const uint64_t hi = (uint64_t)__builtin_bswap32(s[2 * p]) << 32;
+    return 2 * p + 1 < W ? hi | __builtin_bswap32(s[2 * p + 1]) : hi;
+}
+
+// Representatives in order: their rows, and their strings as word pairs (pair
+// p of representative i at pair[p * n + i]).
+struct DictRun {
+    int32_t* rep;
+    uint64_t* pair;
+    int64_t n;
+};
+
+// A bitonic network over one tile.  Only the first pair and the tile position
+// move; a tie reads the other pairs where they were loaded.  Strides of at
+// most a wave's 128 elements need no workgroup barrier.
+template <int P>
+__global__ __launch_bounds__(kSortThreads) void dict_tile_sort_kernel(const uint32_t* __restrict__ strs, int W,
+                                                                      const int32_t* reps, const int64_t* d_count,
+                                                                      int64_t cap, DictRun out) {
+    constexpr uint16_t kNone = 0xFFFF;  // no string: sorts last
+    __shared__ uint64_t s_key[kTile];
+    __shared__ uint64_t s_rest[P > 1 ? P - 1 : 1][kTile];
+    __shared__ uint16_t s_at[kTile];
     const int64_t d = *d_count < cap ? *d_count : cap;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < d; r += stride) {
-        const int32_t row = reps[r];
-        slot_code[row_slot[row]] = (int32_t)r;
-        for (int k = 0; k < W; ++k) dict[r * W + k] = strs[(int64_t)row * W + k];
+    const int64_t base = (int64_t)blockIdx.x * kTile;
+    if (base >= d) return;
+    const int m = (int)(d - base < kTile ? d - base : kTile);
+#pragma unroll
+    for (int e = threadIdx.x; e < kTile; e += kSortThreads) {
+        const uint32_t* q = strs + (int64_t)reps[base + (e < m ? e : 0)] * W;
+        s_at[e] = e < m ? (uint16_t)e : kNone;
+        s_key[e] = e < m ? load_pair(q, W, 0) : ~0ull;
+#pragma unroll
+        for (int p = 1; p < P; ++p) s_rest[p - 1][e] = load_pair(q, W, p);
+    }
+    __syncthreads();
+    int span = 2;  // the tile's power of two
+    while (span < m) span <<= 1;
+    for (int kk = 2; kk <= span; kk <<= 1) {
+        for (int j = kk >> 1; j > 0; j >>= 1) {
+            const int t = threadIdx.x;
+            const int i = ((t & ~(j - 1)) << 1) | (t & (j - 1));
+            const int l = i | j;
+            if (i < span) {
+                const uint64_t x = s_key[i], y = s_key[l];
+                const uint16_t ax = s_at[i], ay = s_at[l];
+                bool gt = x > y;
+                if (x == y) {
+                    gt = ax == kNone && ay != kNone;
+                    if (P > 1 && ax != kNone && ay != kNone) {
+                        bool open = true;
+#pragma unroll
+                        for (int p = 0; p < P - 1; ++p) {
+                            const uint64_t a = s_rest[p][ax], b = s_rest[p][ay];
+                            if (open && a != b) {
+                                gt = a > b;
+                                open = false;
+                            }
+                        }
+                    }
+                }
+                // strings are distinct, so "not greater" is "smaller" except between two missing ones
+                if (gt == ((i & kk) == 0)) {
+                    s_key[i] = y;
+                    s_key[l] = x;
+                    s_at[i] = ay;
+                    s_at[l] = ax;
+                }
+            }
+            if (j > kWave) __syncthreads();
+            else wave_lds_sync();
+        }
+        __syncthreads();
+    }
+    for (int e = threadIdx.x; e < m; e += kSortThreads) {
+        const int at = s_at[e];
+        out.rep[base + e] = reps[base + at];
+        out.pair[base + e] = s_key[e];
+#pragma unroll
+        for (int p = 1; p < P; ++p) out.pair[p * out.n + base + e] = s_rest[p - 1][at];
+    }
+}
+
+// One merge of up to kMergeWay sorted runs of `run` representatives: the place
+// of each in the merged run is its place in its own run plus the number of
+// smaller strings in each other run of the group.  A workgroup takes 64
+// neighbours of one run, whose searches touch the same few lines, and its
+// waves share the runs, four searches in flight per lane.  LAST (one group in
+// all): the place is the string's code and its row of the dictionary.
+template <int P, bool LAST>
+__global__ __launch_bounds__(kMergeWaves * kWave) void dict_merge_kernel(DictRun in, DictRun out, int64_t run,
+                                                                         const int64_t* d_count, int64_t cap, int W,
+                                                                         const int32_t* row_slot, int32_t* slot_code,
+                                                                         uint32_t* dict) {
+    constexpr int kPer = kMergeWay / kMergeWaves;
+    __shared__ int32_t s_part[kMergeWaves][kWave];
+    const int64_t d = *d_count < cap ? *d_count : cap;
+    const int64_t i = (int64_t)blockIdx.x * kWave + lane_id();
+    if ((int64_t)blockIdx.x * kWave >= d) return;
+    const bool have = i < d;
+    const int wave = threadIdx.x / kWave;
+    uint64_t key[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) key[p] = in.pair[p * in.n + (have ? i : d - 1)];
+    const int64_t own = (int64_t)blockIdx.x * kWave / run;  // run is a multiple of 64
+    const int64_t g0 = own / kMergeWay * kMergeWay;         // first run of the group
+    int64_t first[kPer];
+    int32_t lo[kPer], len[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int64_t r = g0 + wave * kPer + k;
+        first[k] = r * run;
+        const int64_t left = d - first[k];
+        len[k] = r == own || left <= 0 ? 0 : (int32_t)(left < run ? left : run);
+        if (len[k] == 0) first[k] = 0;
+        lo[k] = 0;
+    }
+    // lo counts strings known to be smaller; the last step can find the whole run smaller
+    for (int64_t step = run / 2; step >= 0; step = step > 1 ? step >> 1 : step - 1) {
+        const int32_t s = step > 0 ? (int32_t)step : 1;
+        uint64_t x[kPer];
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) x[k] = in.pair[first[k] + (lo[k] + s <= len[k] ? lo[k] + s - 1 : 0)];
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            if (lo[k] + s > len[k]) continue;
+            bool less = x[k] < key[0];
+            if (P > 1 && x[k] == key[0]) {
+                bool open = true;
+#pragma unroll
+                for (int p = 1; p < P; ++p) {
+                    const uint64_t y = in.pair[p * in.n + first[k] + lo[k] + s - 1];
+                    if (open && y != key[p]) {
+                        less = y < key[p];
+                        open = false;
+                    }
+                }
+            }
+            if (less) lo[k] += s;
+        }
+    }
+    int32_t sum = 0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) sum += lo[k];
+    s_part[wave][lane_id()] = sum;
+    __syncthreads();
+    if (wave > 0 || !have) return;
+    int64_t rank = g0 * run + i - own * run;
+#pragma unroll
+    for (int w = 0; w < kMergeWaves; ++w) rank += s_part[w][lane_id()];
+    const int32_t row = in.rep[i];
+    if (LAST) {
+        slot_code[row_slot[row]] = (int32_t)rank;
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            dict[rank * W + 2 * p] = __builtin_bswap32((uint32_t)(key[p] >> 32));
+            if (2 * p + 1 < W) dict[rank * W + 2 * p + 1] = __builtin_bswap32((uint32_t)key[p]);
+        }
+    } else {
+        out.rep[rank] = row;
+#pragma unroll
+        for (int p = 0; p < P; ++p) out.pair[p * out.n + rank] = key[p];
     }
 }
 
@@ -331,32 +504,79 @@ __global__ void dict_decode_kernel(const int32_t* codes, int64_t n, const uint32
     }
 }
 
+// When the bound promises at least kSeenRepeat rows per string, the first
+// sixteenth of the rows claims most slots and the rest read the copies of
+// their strings; the first 64th goes alone, so that few rows at a time find a
+// slot empty (each such row is a device-scope compare-and-swap, about 11 G/s:
+// 46 us for a sixteenth of 10M rows in one launch, 2 x 20 us in two).  These
+// builds get four slots per string: a wave waits for its longest probe
+// sequence (10M rows, 100K strings: 298 us for the whole encoding with four
+// slots, 318 with two, 585 at 76% load, 330 with eight).
+constexpr int64_t kSeenMinRows = 1 << 17;
+constexpr int64_t kSeenRepeat = 8;
+
 struct DictWs {
     int32_t* table;
     int32_t* slot_code;
     int32_t* row_slot;
     int32_t* reps;
-    int64_t n_slots, sort_n;
+    uint32_t* seen;  // string copies by slot, for builds whose rows repeat their strings (null otherwise)
+    DictRun run[2];  // the sorted runs before and after a merge
+    int64_t n_slots;
 };
 
-DictWs dict_layout(void* ws, int64_t n, int64_t max_distinct, size_t* bytes) {
+DictWs dict_layout(void* ws, int64_t n, int64_t max_distinct, int W, size_t* bytes) {
     DictWs w;
     int64_t slots = 256;
-    while (slots < 2 * max_distinct) slots <<= 1;
-    int64_t sn = 1;
-    while (sn < max_distinct) sn <<= 1;
+    const bool repeats = n >= kSeenMinRows && n >= kSeenRepeat * max_distinct;
+    while (slots < (repeats ? 4 : 2) * max_distinct) slots <<= 1;
     WsAlloc wa(ws);
     w.table = wa.take<int32_t>(slots);
     w.slot_code = wa.take<int32_t>(slots);
     w.row_slot = wa.take<int32_t>(std::max<int64_t>(n, 1));
-    w.reps = wa.take<int32_t>(sn);
+    w.reps = wa.take<int32_t>(max_distinct);
+    for (DictRun& r : w.run) {
+        r.n = max_distinct;
+        r.rep = wa.take<int32_t>(max_distinct);
+        r.pair = wa.take<uint64_t>(max_distinct * ((W + 1) / 2));
+    }
+    w.seen = repeats ? wa.take<uint32_t>(slots * W) : nullptr;
     w.n_slots = slots;
-    w.sort_n = sn;
     if (bytes) *bytes = wa.bytes();
     return w;
 }
 
 int dict_grid(int64_t n) { return (int)std::min<int64_t>(std::max<int64_t>(ceil_div(n, 256), 1), 8192); }
+
+template <int W>
+void dict_insert(const uint32_t* strs, int64_t n, const DictWs& w, int32_t* status, hipStream_t stream) {
+    const uint32_t mask = (uint32_t)(w.n_slots - 1);
+    const int64_t first = w.seen ? n / 16 : n, few = w.seen ? n / 64 : 0;
+    if (few)
+        dict_insert_kernel<W, false><<<dict_grid(few), 256, 0, stream>>>(strs, 0, few, w.table, mask, nullptr,
+                                                                         w.row_slot, status);
+    dict_insert_kernel<W, false><<<dict_grid(first - few), 256, 0, stream>>>(strs, few, first, w.table, mask, nullptr,
+                                                                             w.row_slot, status);
+    if (!w.seen) return;
+    dict_seen_kernel<<<dict_grid(w.n_slots * W), 256, 0, stream>>>(strs, W, w.table, w.n_slots, w.seen);
+    dict_insert_kernel<W, true><<<dict_grid(ceil_div(n - first, 4)), 256, 0, stream>>>(strs, first, n, w.table, mask, w.seen,
+                                                                          w.row_slot, status);
+}
+
+template <int P>
+void dict_sort(const uint32_t* strs, int W, const DictWs& w, int64_t cap, const int64_t* d_count, uint32_t* dict,
+               hipStream_t stream) {
+    dict_tile_sort_kernel<P><<<(unsigned)ceil_div(cap, kTile), kSortThreads, 0, stream>>>(strs, W, w.reps, d_count, cap,
+                                                                                         w.run[0]);
+    const unsigned grid = (unsigned)ceil_div(cap, kWave);
+    int at = 0;
+    int64_t run = kTile;
+    for (; run * kMergeWay < cap; run *= kMergeWay, at ^= 1)
+        dict_merge_kernel<P, false><<<grid, kMergeWaves * kWave, 0, stream>>>(w.run[at], w.run[at ^ 1], run, d_count, cap,
+                                                                              W, nullptr, nullptr, nullptr);
+    dict_merge_kernel<P, true><<<grid, kMergeWaves * kWave, 0, stream>>>(w.run[at], w.run[at ^ 1], run, d_count, cap, W,
+                                                                         w.row_slot, w.slot_code, dict);
+}
 
 int dict_check_width(int32_t L, const char* fn) {
     if (L < 4 || L > 4 * kDictMaxWords || (L & 3)) return fail(TDP_EINVAL, "%s: width %d is not a multiple of 4 in 4..32", fn, L);
@@ -378,7 +598,8 @@ int64_t dict_bound(int64_t n, int64_t max_distinct) {
 
 extern "C" size_t tdp_dict_build_workspace_size(int64_t n, int64_t max_distinct) {
     size_t b;
-    dict_layout(nullptr, std::max<int64_t>(n, 0), dict_bound(std::max<int64_t>(n, 0), std::max<int64_t>(max_distinct, 0)), &b);
+    dict_layout(nullptr, std::max<int64_t>(n, 0), dict_bound(std::max<int64_t>(n, 0), std::max<int64_t>(max_distinct, 0)),
+                kDictMaxWords, &b);  // the widest strings
     return b;
 }
 
@@ -392,28 +613,32 @@ extern "C" int tdp_dict_build(const uint8_t* strs, int64_t n, int32_t L, int64_t
     if ((uintptr_t)strs & 3 || (uintptr_t)dict & 3) return fail(TDP_EINVAL, "tdp_dict_build: strings and dictionary must be 4-byte aligned");
     const int64_t md = dict_bound(n, max_distinct);
     size_t need;
-    dict_layout(nullptr, n, md, &need);
+    dict_layout(nullptr, n, md, kDictMaxWords, &need);
     if (!ws || ws_bytes < need) return fail_need(TDP_EWORKSPACE, (int64_t)need, "tdp_dict_build: workspace %zu < %zu", ws_bytes, need);
     if ((uintptr_t)ws & 255) return fail(TDP_EINVAL, "tdp_dict_build: workspace not 256-byte aligned");
-    DictWs w = dict_layout(ws, n, md, nullptr);
     const int W = L / 4;
+    DictWs w = dict_layout(ws, n, md, W, nullptr);
     const uint32_t* s32 = (const uint32_t*)strs;
     dict_fill_kernel<<<dict_grid(w.n_slots), 256, 0, stream>>>(w.table, w.n_slots, -1, d_n_dict, d_status);
     if (n > 0) {
-        dict_insert_kernel<<<dict_grid(n), 256, 0, stream>>>(s32, n, W, w.table, (uint32_t)(w.n_slots - 1), w.row_slot, d_status);
-        dict_compact_kernel<<<dict_grid(w.n_slots), 256, 0, stream>>>(w.table, w.n_slots, w.reps, md, d_n_dict, d_status);
-        dict_pad_kernel<<<dict_grid(w.sort_n), 256, 0, stream>>>(w.reps, w.sort_n, d_n_dict, md);
-        // bitonic network: the stages within a tile in LDS, the others one launch each
-        const int64_t tile = sort_tile(w.sort_n, W);
-        const unsigned tiles = (unsigned)(w.sort_n / tile);
-        const size_t lds = (size_t)tile * (W + 1) * sizeof(uint32_t);
-        dict_sort_local_kernel<<<tiles, kSortThreads, lds, stream>>>(s32, W, w.reps, (int)tile, 0);
-        for (int64_t k = 2 * tile; k <= w.sort_n; k <<= 1) {
-            for (int64_t j = k >> 1; j >= tile; j >>= 1)
-                dict_bitonic_kernel<<<dict_grid(w.sort_n), 256, 0, stream>>>(s32, W, w.reps, w.sort_n, k, j);
-            dict_sort_local_kernel<<<tiles, kSortThreads, lds, stream>>>(s32, W, w.reps, (int)tile, k);
+        switch (W) {
+            case 1: dict_insert<1>(s32, n, w, d_status, stream); break;
+            case 2: dict_insert<2>(s32, n, w, d_status, stream); break;
+            case 3: dict_insert<3>(s32, n, w, d_status, stream); break;
+            case 4: dict_insert<4>(s32, n, w, d_status, stream); break;
+            case 5: dict_insert<5>(s32, n, w, d_status, stream); break;
+            case 6: dict_insert<6>(s32, n, w, d_status, stream); break;
+            case 7: dict_insert<7>(s32, n, w, d_status, stream); break;
+            default: dict_insert<8>(s32, n, w, d_status, stream); break;
         }
-        dict_rank_kernel<<<dict_grid(md), 256, 0, stream>>>(s32, W, w.reps, d_n_dict, md, w.row_slot, w.slot_code, (uint32_t*)dict);
+        dict_compact_kernel<<<(unsigned)std::min<int64_t>(ceil_div(w.n_slots, 4 * kCompactThreads), kCUs), kCompactThreads, 0, stream>>>(
+            w.table, w.n_slots, w.reps, md, d_n_dict, d_status);
+        switch ((W + 1) / 2) {
+            case 1: dict_sort<1>(s32, W, w, md, d_n_dict, (uint32_t*)dict, stream); break;
+            case 2: dict_sort<2>(s32, W, w, md, d_n_dict, (uint32_t*)dict, stream); break;
+            case 3: dict_sort<3>(s32, W, w, md, d_n_dict, (uint32_t*)dict, stream); break;
+            default: dict_sort<4>(s32, W, w, md, d_n_dict, (uint32_t*)dict, stream); break;
+        }
         dict_codes_kernel<<<dict_grid(ceil_div(n, 4)), 256, 0, stream>>>(w.row_slot, n, w.slot_code, codes);
     }
     return launch_status("tdp_dict_build");

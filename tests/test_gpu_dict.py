@@ -93,3 +93,41 @@ def test_codes_as_keys_of_filter_join_and_groupby():
     names = dictenc.decode(cd, got["k0"].to(torch.int32).contiguous()).cpu().numpy()
     assert all(bytes(r).rstrip(b"\0") >= b"m" for r in names)
     assert np.array_equal(names, od_c[want["k0"]])
+
+
+def _distinct_words(rng, nd, width, prefix):
+    """nd distinct zero-padded strings (the empty one first) whose first `prefix` bytes are alike."""
+    rows = np.full((nd, width), ord("p"), np.uint8)
+    ids = rng.permutation(nd)
+    for k in range(prefix, width):  # base-25 digits of a distinct number, then nothing
+        rows[:, k] = ord("a") + ids % 25 if 25 ** (k - prefix) < 4 * nd else 0
+        ids = ids // 25
+    rows[0] = 0
+    return rows
+
+
+# tile and merge edges of the sort (tiles of 1024, 16 runs a merge), strings that differ only behind the first
+# 8 bytes, rows that repeat at least 8 times (string copies by slot) and rows that do not
+@pytest.mark.parametrize("nd,n,width,prefix", [(1023, 1023, 4, 0), (1024, 2000, 8, 4), (1025, 9000, 12, 8),
+                                                (16384, 140_001, 16, 9), (16385, 20_000, 20, 8),
+                                                (17_000, 136_000, 24, 12), (33_000, 300_007, 32, 24)])
+@pytest.mark.parametrize("shift", [0, 4])  # a column that starts 4 bytes past a 16-byte boundary
+def test_dictionary_build_sort_and_repeat_edges(nd, n, width, prefix, shift):
+    rng = np.random.default_rng(nd + width)
+    words = _distinct_words(rng, nd, width, prefix)
+    rows = words[rng.permutation(np.arange(n) % nd)]
+    print(f"dictionary n={n} distinct={nd} width={width} prefix={prefix} shift={shift}", flush=True)
+    buf = torch.zeros(n * width + shift, dtype=torch.uint8, device=DEV)
+    col = buf[shift:].view(n, width)
+    col.copy_(t(rows))
+    d, codes = dictenc.encode(col, max_distinct=nd)
+    wd, wc = oracle.dict_build(rows)
+    assert np.array_equal(d.cpu().numpy(), wd)
+    assert np.array_equal(codes.cpu().numpy(), wc)
+
+
+def test_dictionary_over_its_bound_with_repeated_rows_raises_the_flag():
+    words = _distinct_words(np.random.default_rng(9), 40_000, 16, 4)
+    rows = words[np.random.default_rng(10).integers(0, 40_000, 200_000)]
+    with pytest.raises(L.TdpError, match="TABLE_FULL"):
+        dictenc.encode(t(rows), max_distinct=5000)
