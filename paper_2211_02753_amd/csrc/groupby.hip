@@ -31,8 +31,10 @@ enum AggForm { F_ACNT = 0, F_SUM = 1, F_ASUM = 2, F_AKCNT_SUM = 3, F_NONE = 4, F
 
 constexpr int kThreads = 256;
 constexpr int kRegMaxG = 8;
-constexpr int kFinRegThreads = 1024;  // threads of the finalize over register partials
+constexpr int kFinThreads = 1024;     // threads of the finalize over partial rows
+constexpr int kPartMaxG = 256;        // groups it takes
 constexpr int kLdsMaxG = 2048;
+constexpr int kGbMaxThreads = 1024;   // threads of a fused kernel's workgroup with LDS accumulators
 constexpr int kLastBlockMaxG = 4096;
 constexpr int kFinChunk = kThreads * 16;
 
@@ -67,7 +69,8 @@ struct GbDev {
     int64_t k;
     int64_t G;
     unsigned long long* gtab;   // [G][sum, count] (LDS / GLOBAL modes): one 16-byte record per group
-    unsigned long long* part;   // [nblocks][G][2] (REG mode)
+    unsigned long long* part;   // [nblocks][G][2] (REG mode, and LDS mode of the fused kernel)
+    int32_t lds_copies;         // fused kernel, LDS mode: copies of the table (a power of two)
     unsigned int* done;
     int32_t* status;
     int32_t last_block_fin;
@@ -300,9 +303,10 @@ __device__ __forceinline__ void colread(const ColDev& c, int64_t r0, int64_t n, 
 // Emit group g (non-empty) at output position pos.
 __device__ __forceinline__ void emit_group(const GbDev& d, int64_t g, int64_t pos, unsigned long long s,
                                            unsigned long long c) {
-    const int64_t c1 = d.n_keys > 1 ? d.card[1] : 1;
-    d.okey0[pos] = d.lo[0] + g / c1;
-    if (d.okey1) d.okey1[pos] = d.n_keys > 1 ? d.lo[1] + g % c1 : 0;
+    const uint32_t c1 = d.n_keys > 1 ? (uint32_t)d.card[1] : 1u;  // at most 2^27 groups
+    const uint32_t k0 = (uint32_t)g / c1;
+    d.okey0[pos] = d.lo[0] + k0;
+    if (d.okey1) d.okey1[pos] = d.n_keys > 1 ? d.lo[1] + ((uint32_t)g - k0 * c1) : 0;
     d.osum[pos] = (int64_t)s;
     d.ocnt[pos] = (int64_t)c;
     d.oavg[pos] = (double)(int64_t)s / (double)(int64_t)c;
@@ -329,78 +333,28 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t& total,
     return woff + incl - v;
 }
 
-// Emit the groups of a small table from one workgroup, after the
-// aggregation kernel: REG partials ([n_parts][G][sum, count]) or the dense
-// global table.
-template <int ACC>
-__device__ void finalize_last_block(const GbDev& d, int n_parts) {
+// Emit the non-empty groups of a small dense table from one workgroup, after
+// the aggregation kernels, and leave the table zero for the next probe.
+__device__ void finalize_table(const GbDev& d) {
     __shared__ uint32_t s_w[kThreads / kWave];
-    const int lane = lane_id(), wave = threadIdx.x / kWave;
-    if (ACC == ACC_REG) {
-        // every thread sums whole partial rows, so all loads are independent
-        __shared__ unsigned long long s_acc[2][kFinRegThreads / kWave][kRegMaxG];
-        unsigned long long s[kRegMaxG], c[kRegMaxG];
-#pragma unroll
-        for (int g = 0; g < kRegMaxG; ++g) s[g] = c[g] = 0;
-        if (d.n_parts_dev) n_parts = min(n_parts, (int)*d.n_parts_dev);
-        for (int64_t b = threadIdx.x; b < n_parts; b += blockDim.x) {
-            const unsigned long long* row = d.part + b * d.G * 2;
-#pragma unroll
-            for (int g = 0; g < kRegMaxG; ++g) {
-                if (g < d.G) {
-                    s[g] += row[2 * g];
-                    c[g] += row[2 * g + 1];
-                }
-            }
+    int64_t base = 0;
+    for (int64_t g0 = 0; g0 < d.G; g0 += kThreads) {
+        const int64_t g = g0 + threadIdx.x;
+        unsigned long long s = 0, c = 0;
+        if (g < d.G) {
+            s = d.gtab[2 * g];
+            c = d.gtab[2 * g + 1];
         }
-#pragma unroll
-        for (int g = 0; g < kRegMaxG; ++g) {
-            const unsigned long long ws = wave_sum_u64(s[g]);
-            const unsigned long long wc = wave_sum_u64(c[g]);
-            if (lane == 0) {
-                s_acc[0][wave][g] = ws;
-                s_acc[1][wave][g] = wc;
-            }
+        uint32_t total;
+        const uint32_t pre = block_excl_scan(c ? 1u : 0u, total, s_w);
+        if (c) {
+            emit_group(d, g, base + pre, s, c);
+            d.gtab[2 * g] = 0;
+            d.gtab[2 * g + 1] = 0;
         }
-        __syncthreads();
-        // thread g adds group g over the waves, then thread 0 numbers the non-empty groups
-        __shared__ unsigned long long s_tot[2][kRegMaxG];
-        if (threadIdx.x < d.G) {
-            unsigned long long ts = 0, tc = 0;
-            for (int w = 0; w < (int)blockDim.x / kWave; ++w) {
-                ts += s_acc[0][w][threadIdx.x];
-                tc += s_acc[1][w][threadIdx.x];
-            }
-            s_tot[0][threadIdx.x] = ts;
-            s_tot[1][threadIdx.x] = tc;
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            int64_t m = 0;
-            for (int64_t g = 0; g < d.G; ++g)
-                if (s_tot[1][g]) emit_group(d, g, m++, s_tot[0][g], s_tot[1][g]);
-            *d.d_n_groups = m;
-        }
-    } else {
-        int64_t base = 0;
-        for (int64_t g0 = 0; g0 < d.G; g0 += kThreads) {
-            const int64_t g = g0 + threadIdx.x;
-            unsigned long long s = 0, c = 0;
-            if (g < d.G) {
-                s = d.gtab[2 * g];
-                c = d.gtab[2 * g + 1];
-            }
-            uint32_t total;
-            const uint32_t pre = block_excl_scan(c ? 1u : 0u, total, s_w);
-            if (c) {
-                emit_group(d, g, base + pre, s, c);
-                d.gtab[2 * g] = 0;  // leave the workspace ready for the next probe
-                d.gtab[2 * g + 1] = 0;
-            }
-            base += total;
-        }
-        if (threadIdx.x == 0) *d.d_n_groups = base;
+        base += total;
     }
+    if (threadIdx.x == 0) *d.d_n_groups = base;
 }
 
 template <int ACC>
@@ -510,18 +464,39 @@ __device__ __forceinline__ void eval_rows(const GbDev& d, int64_t r0, bool ok[4]
                 if (ok[e]) brows[e] = d.t.rowid[slot[e]];
         }
     }
-    // build-side columns (static) or every column (run-time path)
+    // build-side columns (static) or every column (run-time path); a table
+    // that keeps the column's values has given them with the key
+    auto build4 = [&](int64_t v[4]) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = brows[e];
+    };
+    const bool pay = JM == J_ROWID && d.t.pay != nullptr;
     if constexpr (STATIC) {
-        if constexpr (S::K0S == TDP_SIDE_BUILD) colread<S::K0, TDP_SIDE_BUILD, SEL, FULL>(d.key[0], r0, d.n_cand, rows, brows, ok, k0);
-        if constexpr (S::K1 > 0 && S::K1S == TDP_SIDE_BUILD)
-            colread<S::K1, TDP_SIDE_BUILD, SEL, FULL>(d.key[1], r0, d.n_cand, rows, brows, ok, k1);
-        if constexpr (S::A > 0 && S::AS == TDP_SIDE_BUILD) colread<S::A, TDP_SIDE_BUILD, SEL, FULL>(d.a, r0, d.n_cand, rows, brows, ok, av);
-        if constexpr (S::B > 0 && S::BS == TDP_SIDE_BUILD) colread<S::B, TDP_SIDE_BUILD, SEL, FULL>(d.b, r0, d.n_cand, rows, brows, ok, bv);
+        if constexpr (S::K0S == TDP_SIDE_BUILD) {
+            if (pay) build4(k0);
+            else colread<S::K0, TDP_SIDE_BUILD, SEL, FULL>(d.key[0], r0, d.n_cand, rows, brows, ok, k0);
+        }
+        if constexpr (S::K1 > 0 && S::K1S == TDP_SIDE_BUILD) {
+            if (pay) build4(k1);
+            else colread<S::K1, TDP_SIDE_BUILD, SEL, FULL>(d.key[1], r0, d.n_cand, rows, brows, ok, k1);
+        }
+        if constexpr (S::A > 0 && S::AS == TDP_SIDE_BUILD) {
+            if (pay) build4(av);
+            else colread<S::A, TDP_SIDE_BUILD, SEL, FULL>(d.a, r0, d.n_cand, rows, brows, ok, av);
+        }
+        if constexpr (S::B > 0 && S::BS == TDP_SIDE_BUILD) {
+            if (pay) build4(bv);
+            else colread<S::B, TDP_SIDE_BUILD, SEL, FULL>(d.b, r0, d.n_cand, rows, brows, ok, bv);
+        }
     } else {
-        read4(d.key[0], !SEL, r0, d.n_cand, rows, brows, ok, k0);
-        if (n_keys > 1) read4(d.key[1], !SEL, r0, d.n_cand, rows, brows, ok, k1);
-        if (need_a) read4(d.a, !SEL, r0, d.n_cand, rows, brows, ok, av);
-        if (need_b) read4(d.b, !SEL, r0, d.n_cand, rows, brows, ok, bv);
+        auto col4 = [&](const ColDev& c, int64_t v[4]) {
+            if (pay && c.side == TDP_SIDE_BUILD) build4(v);
+            else read4(c, !SEL, r0, d.n_cand, rows, brows, ok, v);
+        };
+        col4(d.key[0], k0);
+        if (n_keys > 1) col4(d.key[1], k1);
+        if (need_a) col4(d.a, av);
+        if (need_b) col4(d.b, bv);
     }
     // group id
 #pragma unroll
@@ -565,16 +540,22 @@ __device__ __forceinline__ void eval_rows(const GbDev& d, int64_t r0, bool ok[4]
     for (int e = 0; e < 4; ++e) cnt[e] = JM == J_AGG ? bcnt[e] : 1ull;
 }
 
+// With LDS accumulators a workgroup keeps d.lds_copies copies of its table,
+// lane l adding to copy l mod lds_copies, so that fewer lanes of an
+// instruction meet on one address, and writes their sum as one partial row.
+// Merging the tables with device-scope atomics instead (2G per workgroup, all
+// on the same 2G words) bound the 1M-row, 75-group star join: 32 us.
 template <int ACC, int JM, bool SEL, class S>
-__global__ __launch_bounds__(kThreads) void groupby_kernel(GbDev d) {
-    extern __shared__ unsigned long long s_tab[];  // ACC_LDS: [G] sums then [G] counts
+__global__ __launch_bounds__(ACC == ACC_LDS ? kGbMaxThreads : kThreads) void groupby_kernel(GbDev d) {
+    extern __shared__ unsigned long long s_all[];  // ACC_LDS: [copies] of [G] sums then [G] counts
+    unsigned long long* s_tab = s_all + (ACC == ACC_LDS ? (lane_id() & (d.lds_copies - 1)) * 2 * d.G : 0);
     unsigned long long rs[kRegMaxG], rc[kRegMaxG];
     if (ACC == ACC_REG) {
 #pragma unroll
         for (int g = 0; g < kRegMaxG; ++g) rs[g] = rc[g] = 0;
     }
     if (ACC == ACC_LDS) {
-        for (int64_t i = threadIdx.x; i < 2 * d.G; i += kThreads) s_tab[i] = 0;
+        for (int64_t i = threadIdx.x; i < 2 * d.G * d.lds_copies; i += blockDim.x) s_all[i] = 0;
         __syncthreads();
     }
     // four consecutive rows per thread and step (eight measured no faster:
@@ -590,12 +571,24 @@ __global__ __launch_bounds__(kThreads) void groupby_kernel(GbDev d) {
         for (int e = 0; e < 4; ++e)
             if (ok[e]) acc_row<ACC>(d, rs, rc, s_tab, gid[e], val[e], cnt[e]);
     };
-    const int64_t stride = (int64_t)gridDim.x * kThreads * 4;
-    int64_t r0 = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * 4;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x * 4;
+    int64_t r0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
     for (; r0 + 4 <= d.n_cand; r0 += stride) rows4(r0, std::true_type{});
     if (r0 < d.n_cand) rows4(r0, std::false_type{});
 
-    merge_and_finish<ACC>(d, rs, rc, s_tab);
+    if (ACC == ACC_LDS) {
+        __syncthreads();
+        for (int64_t g = threadIdx.x; g < d.G; g += blockDim.x) {
+            ulonglong2 v = make_ulonglong2(0ull, 0ull);
+            for (int c = 0; c < d.lds_copies; ++c) {
+                v.x += s_all[c * 2 * d.G + g];
+                v.y += s_all[c * 2 * d.G + d.G + g];
+            }
+            ((ulonglong2*)d.part)[(int64_t)blockIdx.x * d.G + g] = v;
+        }
+    } else {
+        merge_and_finish<ACC>(d, rs, rc, s_tab);
+    }
 }
 
 // Merge one workgroup's accumulators into its partial row (REG) or the
@@ -638,13 +631,99 @@ __device__ void merge_and_finish(const GbDev& d, const unsigned long long* rs, c
 }
 
 // Emits the groups of a small table (G <= 4096) after the aggregation
-// kernel: one workgroup reads the partials or the dense table.  A separate
-// launch orders it after every aggregation workgroup without a device-wide
-// fence in each of them.
-template <int ACC>
-__global__ __launch_bounds__(ACC == ACC_REG ? kFinRegThreads : kThreads) void finalize_small_kernel(GbDev d,
-                                                                                                    int n_parts) {
-    finalize_last_block<ACC>(d, n_parts);
+// kernel: one workgroup reads the dense table.  A separate launch orders it
+// after every aggregation workgroup without a device-wide fence in each of
+// them.
+__global__ __launch_bounds__(kThreads) void finalize_small_kernel(GbDev d) { finalize_table(d); }
+
+// The workgroups' partial rows ([n_parts][G] of (sum, count)) added and
+// emitted by one workgroup, G <= kPartMaxG.  Thread t adds group t mod gp of
+// every (kFinThreads / gp)-th row, so a wave reads whole rows and every load
+// is independent; then the slices are added in LDS and each group's thread
+// emits it.  Bound by latency: 17.8 us for 1,940 rows of 6 groups when each
+// thread added whole rows and thread 0 emitted the groups, 6 us so.
+__global__ __launch_bounds__(kFinThreads) void finalize_part_kernel(GbDev d, int n_parts) {
+    __shared__ ulonglong2 s_acc[kFinThreads];
+    __shared__ uint32_t s_w[kPartMaxG / kWave];
+    if (d.n_parts_dev) n_parts = min(n_parts, (int)*d.n_parts_dev);
+    const int G = (int)d.G, tid = threadIdx.x;
+    int gp = 8;
+    while (gp < G) gp <<= 1;
+    const int g = tid & (gp - 1), slices = kFinThreads / gp;
+    ulonglong2 acc = make_ulonglong2(0ull, 0ull);
+    if (g < G) {
+        const ulonglong2* col = (const ulonglong2*)d.part + g;
+        int b = tid / gp;
+        for (; b + 7 * slices < n_parts; b += 8 * slices) {
+            ulonglong2 v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = col[(int64_t)(b + k * slices) * G];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                acc.x += v[k].x;
+                acc.y += v[k].y;
+            }
+        }
+        for (; b < n_parts; b += slices) {
+            const ulonglong2 v = col[(int64_t)b * G];
+            acc.x += v.x;
+            acc.y += v.y;
+        }
+    }
+    s_acc[tid] = acc;
+    __syncthreads();
+    for (int h = slices / 2; h > 0; h >>= 1) {
+        if (tid < h * gp) {
+            const ulonglong2 v = s_acc[tid + h * gp];
+            acc.x += v.x;
+            acc.y += v.y;
+            s_acc[tid] = acc;
+        }
+        __syncthreads();
+    }
+    // threads 0 .. gp - 1 hold the groups' totals
+    const bool f = tid < G && acc.y != 0;
+    const uint64_t bal = ballot(f);
+    if (tid < kPartMaxG && lane_id() == 0) s_w[tid / kWave] = (uint32_t)__popcll(bal);
+    __syncthreads();
+    if (tid < kPartMaxG) {
+        uint32_t before = 0, total = 0;
+#pragma unroll
+        for (int w = 0; w < kPartMaxG / kWave; ++w) {
+            if (w < tid / kWave) before += s_w[w];
+            total += s_w[w];
+        }
+        if (f) emit_group(d, tid, before + lanes_below(bal), acc.x, acc.y);
+        if (tid == 0) *d.d_n_groups = total;
+    }
+}
+
+// Partial rows of tables too wide for one workgroup, added into the dense
+// table: a workgroup takes 64 groups, its waves every 16th row.
+__global__ __launch_bounds__(1024) void part_reduce_kernel(GbDev d, int n_parts) {
+    __shared__ ulonglong2 s_acc[16][kWave];
+    const int lane = lane_id(), wave = threadIdx.x / kWave;
+    const int64_t g = (int64_t)blockIdx.x * kWave + lane;
+    ulonglong2 acc = make_ulonglong2(0ull, 0ull);
+    if (g < d.G) {
+        const ulonglong2* col = (const ulonglong2*)d.part + g;
+#pragma unroll 8
+        for (int b = wave; b < n_parts; b += 16) {
+            const ulonglong2 v = col[(int64_t)b * d.G];
+            acc.x += v.x;
+            acc.y += v.y;
+        }
+    }
+    s_acc[wave][lane] = acc;
+    __syncthreads();
+    if (wave > 0 || g >= d.G) return;
+#pragma unroll
+    for (int w = 1; w < 16; ++w) {
+        const ulonglong2 v = s_acc[w][lane];
+        acc.x += v.x;
+        acc.y += v.y;
+    }
+    *(ulonglong2*)&d.gtab[2 * g] = acc;
 }
 
 __global__ void gb_init_kernel(unsigned long long* zero, int64_t n_zero, int32_t* d_status, unsigned int* done) {
@@ -2420,10 +2499,14 @@ struct Plan {
     int bdt = 0;
     int form = F_NONE;
     ColDev a, b;
+    ColDev pay;  // the build-side column whose values the row-id table keeps (null: row ids)
     int expr = TDP_EXPR_NONE;
     int64_t G = 1;
     int acc = ACC_REG;
     int nblocks = 1;
+    int threads = kThreads;  // of the fused kernel's workgroups
+    bool lds_part = false;   // fused kernel with LDS accumulators: one partial row per workgroup
+    int lds_copies = 1;
     bool last_block_fin = true;
     int64_t n_cand = 0;
     int topk = 0;
@@ -2519,6 +2602,16 @@ int make_plan(const tdp_groupby_desc* d, Plan& p) {
         if (need_b) build_ref |= d->b.side == TDP_SIDE_BUILD;
         p.cap = table_cap(distinct_bound(j), j->load_pct);
         if (j->build_unique) {
+            // one reference to a build-side column of at most 32 bits: the
+            // table keeps its value in the place of the row id
+            int refs = 0;
+            auto ref = [&](const tdp_col& c) {
+                if (c.side == TDP_SIDE_BUILD) ++refs, p.pay = coldev(c);
+            };
+            for (int i = 0; i < d->n_keys; ++i) ref(d->key[i]);
+            if (need_a) ref(d->a);
+            if (need_b) ref(d->b);
+            if (refs != 1 || p.pay.dt == TDP_I64) p.pay = ColDev();
             p.jm = build_ref ? J_ROWID : J_KEYS;
             p.kind = build_ref ? TABLE_ROWID : TABLE_KEYS;
         } else {
@@ -2571,11 +2664,6 @@ int make_plan(const tdp_groupby_desc* d, Plan& p) {
     // top-k ranks the dense table, so it needs the LDS or global accumulators
     p.acc = (p.G <= kRegMaxG && !p.topk) ? ACC_REG : (p.G <= kLdsMaxG ? ACC_LDS : ACC_GLOBAL);
     p.nblocks = (int)std::min<int64_t>(std::max<int64_t>(ceil_div(p.n_cand, kThreads * 4), 1), 8 * kCUs);
-    // LDS accumulators merge into the global table with 2G atomics per
-    // workgroup, all on the same G slots: one workgroup per CU (measured on
-    // the 1M-row, 75-group query: probe 55 -> 36 us; 128 workgroups 51 us),
-    // four from 4M candidate rows, where the scan outweighs the merge.
-    if (p.acc == ACC_LDS) p.nblocks = std::min(p.nblocks, p.n_cand >= (4 << 20) ? 4 * kCUs : kCUs);
     p.last_block_fin = p.G <= kLastBlockMaxG && !p.topk;
     // Tables well beyond one XCD's L2 with many probe rows take the staged probe.
     if (d->strategy < TDP_PROBE_AUTO || d->strategy > TDP_PROBE_PARTITIONED)
@@ -2645,6 +2733,14 @@ int make_plan(const tdp_groupby_desc* d, Plan& p) {
         p.pagg_np = (int)ceil_div(p.G, kPaggGroups);
         p.stage_tiles = ceil_div(p.n_cand, kStageTile);
     }
+    p.lds_part = p.acc == ACC_LDS && !p.radix && !p.staged;
+    if (p.lds_part) {
+        // one workgroup per CU (one partial row each): small inputs are spread
+        // over the CUs by workgroups of 256 threads, larger ones take 1024
+        p.threads = p.n_cand >= (int64_t)kCUs * kThreads * 4 ? kGbMaxThreads : kThreads;
+        p.nblocks = (int)std::min<int64_t>(std::max<int64_t>(ceil_div(p.n_cand, p.threads * 4), 1), kCUs);
+        while (p.lds_copies < 8 && p.lds_copies * 2 * p.G <= kLdsMaxG) p.lds_copies *= 2;
+    }
     return TDP_OK;
 }
 
@@ -2668,11 +2764,12 @@ WsLayout layout(const Plan& p, const tdp_groupby_desc* d, void* ws) {
     WsLayout L;
     WsAlloc wa(ws);
     L.done = wa.take<unsigned int>(64);
-    const int64_t n_acc = p.acc == ACC_REG ? 0 : 2 * p.G;
-    L.n_zero = n_acc;
+    const bool parts = p.acc == ACC_REG || p.lds_part;
+    L.n_zero = parts ? 0 : 2 * p.G;
     L.zblock = wa.take<unsigned long long>((size_t)std::max<int64_t>(L.n_zero, 1));
-    if (p.acc == ACC_REG) {
+    if (parts) {
         L.part = wa.take<unsigned long long>((size_t)p.nblocks * p.G * 2);
+        if (p.G > kPartMaxG || p.topk) L.gtab = wa.take<unsigned long long>((size_t)p.G * 2);  // the partial rows' sum
     } else {
         L.gtab = L.zblock;
     }
@@ -2731,6 +2828,8 @@ WsLayout layout(const Plan& p, const tdp_groupby_desc* d, void* ws) {
     }
     if (p.jm != J_NONE && !p.radix) {
         L.t = table_alloc(wa, p.kind, d->join->n_build, p.cap, p.with_sum);
+        L.t.pay = p.pay.p;
+        L.t.pay_dt = p.pay.dt;
         L.bs = build_scratch_alloc(wa, p.kind, d->join->n_build, p.cap, p.with_sum);
     }
     L.bytes = wa.bytes();
@@ -2766,29 +2865,29 @@ int pick_sig(const Plan& p, const tdp_groupby_desc* d) {
 }
 
 template <int ACC, int JM>
-void launch_gb(const GbDev& g, bool sel, int sig, int nblocks, size_t lds, hipStream_t s) {
+void launch_gb(const GbDev& g, bool sel, int sig, int nblocks, int threads, size_t lds, hipStream_t s) {
     if (sel) {
-        groupby_kernel<ACC, JM, true, SigGeneric><<<nblocks, kThreads, lds, s>>>(g);
+        groupby_kernel<ACC, JM, true, SigGeneric><<<nblocks, threads, lds, s>>>(g);
         return;
     }
     switch (sig) {
         case SIG_SCALED:
-            groupby_kernel<ACC, JM, false, SigPredI32KeysI8I8ValI64I64><<<nblocks, kThreads, lds, s>>>(g);
+            groupby_kernel<ACC, JM, false, SigPredI32KeysI8I8ValI64I64><<<nblocks, threads, lds, s>>>(g);
             break;
         case SIG_SMALL:
-            groupby_kernel<ACC, JM, false, SigPredI32BuildKeyI8KeyI8ValI64><<<nblocks, kThreads, lds, s>>>(g);
+            groupby_kernel<ACC, JM, false, SigPredI32BuildKeyI8KeyI8ValI64><<<nblocks, threads, lds, s>>>(g);
             break;
         case SIG_ONEKEY:
-            groupby_kernel<ACC, JM, false, SigKeyI32ValI64><<<nblocks, kThreads, lds, s>>>(g);
+            groupby_kernel<ACC, JM, false, SigKeyI32ValI64><<<nblocks, threads, lds, s>>>(g);
             break;
         case SIG_WHERE:
             if constexpr (JM == J_NONE) {
-                groupby_kernel<ACC, JM, false, SigPredI32KeysI8I8Count><<<nblocks, kThreads, lds, s>>>(g);
+                groupby_kernel<ACC, JM, false, SigPredI32KeysI8I8Count><<<nblocks, threads, lds, s>>>(g);
                 break;
             }
             [[fallthrough]];
         default:
-            groupby_kernel<ACC, JM, false, SigGeneric><<<nblocks, kThreads, lds, s>>>(g);
+            groupby_kernel<ACC, JM, false, SigGeneric><<<nblocks, threads, lds, s>>>(g);
             break;
     }
 }
@@ -2822,12 +2921,12 @@ void launch_pagg(const GbDev& g, const PaggDev& pg, int jm, int sig, hipStream_t
 }
 
 template <int ACC>
-void launch_gb_acc(const GbDev& g, int jm, bool sel, int sig, int nblocks, size_t lds, hipStream_t s) {
+void launch_gb_acc(const GbDev& g, int jm, bool sel, int sig, int nblocks, int threads, size_t lds, hipStream_t s) {
     switch (jm) {
-        case J_NONE: launch_gb<ACC, J_NONE>(g, sel, sig, nblocks, lds, s); break;
-        case J_KEYS: launch_gb<ACC, J_KEYS>(g, sel, sig, nblocks, lds, s); break;
-        case J_ROWID: launch_gb<ACC, J_ROWID>(g, sel, sig, nblocks, lds, s); break;
-        default: launch_gb<ACC, J_AGG>(g, sel, sig, nblocks, lds, s); break;
+        case J_NONE: launch_gb<ACC, J_NONE>(g, sel, sig, nblocks, threads, lds, s); break;
+        case J_KEYS: launch_gb<ACC, J_KEYS>(g, sel, sig, nblocks, threads, lds, s); break;
+        case J_ROWID: launch_gb<ACC, J_ROWID>(g, sel, sig, nblocks, threads, lds, s); break;
+        default: launch_gb<ACC, J_AGG>(g, sel, sig, nblocks, threads, lds, s); break;
     }
 }
 
@@ -2877,6 +2976,7 @@ GbDev make_dev(const Plan& p, const WsLayout& L, const tdp_groupby_desc* d, cons
     g.G = p.G;
     g.gtab = L.gtab;
     g.part = L.part;
+    g.lds_copies = p.lds_copies;
     g.done = L.done;
     g.status = d_status;
     g.last_block_fin = p.last_block_fin || p.n_cand == 0;  // no rows: one workgroup emits zero groups
@@ -2927,7 +3027,7 @@ int run_build(const Plan& p, const WsLayout& L, const tdp_groupby_desc* d, int32
         return launch_status("tdp_groupby_build");
     }
     if (p.jm != J_NONE) {
-        int rc = table_clear_zero(L.t, !L.bs.lds, d_status, L.done, L.zblock, n_zero, stream);
+        int rc = table_clear_zero(L.t, !L.bs.lds && !L.bs.direct, d_status, L.done, L.zblock, n_zero, stream);
         if (rc) return rc;
         return table_build(L.t, L.bs, p.kind, d->join->build_key, d->join->n_build, d->join->build_unique != 0,
                            p.bvals, p.bdt, d_status, stream);
@@ -2940,7 +3040,7 @@ int run_build(const Plan& p, const WsLayout& L, const tdp_groupby_desc* d, int32
 int run_probe(const Plan& p, const WsLayout& L, const tdp_groupby_desc* d, const tdp_groupby_out* o,
               int32_t* d_status, hipStream_t stream) {
     GbDev g = make_dev(p, L, d, o, d_status);
-    const size_t lds = p.acc == ACC_LDS ? (size_t)p.G * 2 * sizeof(unsigned long long) : 0;
+    const size_t lds = p.acc == ACC_LDS ? (size_t)p.G * 2 * sizeof(unsigned long long) * p.lds_copies : 0;
     const bool sel = d->sel != nullptr;
     const int sig = pick_sig(p, d);
     if (p.radix) {
@@ -2987,19 +3087,17 @@ int run_probe(const Plan& p, const WsLayout& L, const tdp_groupby_desc* d, const
     } else {
         stage_mark(TDP_STAGE_FUSED_PROBE, 0, stream);
         switch (p.acc) {
-            case ACC_REG: launch_gb_acc<ACC_REG>(g, p.jm, sel, sig, p.nblocks, lds, stream); break;
-            case ACC_LDS: launch_gb_acc<ACC_LDS>(g, p.jm, sel, sig, p.nblocks, lds, stream); break;
-            default: launch_gb_acc<ACC_GLOBAL>(g, p.jm, sel, sig, p.nblocks, lds, stream); break;
+            case ACC_REG: launch_gb_acc<ACC_REG>(g, p.jm, sel, sig, p.nblocks, kThreads, lds, stream); break;
+            case ACC_LDS: launch_gb_acc<ACC_LDS>(g, p.jm, sel, sig, p.nblocks, p.threads, lds, stream); break;
+            default: launch_gb_acc<ACC_GLOBAL>(g, p.jm, sel, sig, p.nblocks, kThreads, lds, stream); break;
         }
         stage_mark(TDP_STAGE_FUSED_PROBE, 1, stream);
     }
     const int n_parts = p.staged && p.n_cand > 0 ? kProbeGrid : p.nblocks;  // radix: one partial per item workgroup
+    if (p.lds_part && L.gtab) part_reduce_kernel<<<(uint32_t)ceil_div(p.G, kWave), 1024, 0, stream>>>(g, n_parts);
     if (g.last_block_fin) {
-        switch (p.acc) {
-            case ACC_REG: finalize_small_kernel<ACC_REG><<<1, kFinRegThreads, 0, stream>>>(g, n_parts); break;
-            case ACC_LDS: finalize_small_kernel<ACC_LDS><<<1, kThreads, 0, stream>>>(g, n_parts); break;
-            default: finalize_small_kernel<ACC_GLOBAL><<<1, kThreads, 0, stream>>>(g, n_parts); break;
-        }
+        if (L.gtab) finalize_small_kernel<<<1, kThreads, 0, stream>>>(g);
+        else finalize_part_kernel<<<1, kFinThreads, 0, stream>>>(g, n_parts);
     } else if (p.topk && p.n_cand > 0) {
         int64_t n = p.G;
         int64_t nb = ceil_div(n, kTopChunk);

@@ -60,9 +60,106 @@ __global__ __launch_bounds__(256) void table_build_kernel(HashView t, const int3
         }
         if (unique && !fresh) raise_flag(status, TDP_FLAG_DUP_BUILD);
         if (KIND == TABLE_ROWID) {
-            if (fresh) t.rowid[slot] = (int32_t)j;
+            if (fresh) t.rowid[slot] = row_value(t, j);
         } else if (KIND == TABLE_LIST) {
             t.next[j] = atomicExch(&t.head[slot], (int32_t)j);
+        }
+    }
+}
+
+// Direct build (n < kDirectRows): workgroup b builds the probing block b, the
+// slots [b * nslots, (b + 1) * nslots), in LDS from every key that falls there
+// and writes it out whole; workgroup 0 also takes the key kEmpty (slot cap).
+constexpr int kDirectThreads = 1024;
+template <int KIND>
+__global__ __launch_bounds__(kDirectThreads) void direct_build_kernel(HashView t, const int32_t* __restrict__ bkey,
+                                                                      int64_t n, int unique,
+                                                                      const void* __restrict__ bvals, int bdt,
+                                                                      int32_t* status) {
+    constexpr bool ROWID = KIND == TABLE_ROWID, AGG = KIND == TABLE_AGG;
+    __shared__ int32_t tk[kTableBlock];
+    __shared__ int32_t tr[ROWID ? kTableBlock : 1];
+    __shared__ uint32_t tc[AGG ? kTableBlock : 1];
+    __shared__ unsigned long long ts[AGG ? kTableBlock : 1];
+    constexpr int kKeys = 8;  // a thread's keys in flight
+    __shared__ int2 s_list[kKeys * kDirectThreads];
+    __shared__ uint32_t s_n;
+    const uint32_t nslots = t.bmask + 1, first = blockIdx.x * nslots;
+    for (uint32_t j = threadIdx.x; j < nslots; j += kDirectThreads) {
+        tk[j] = kEmpty;
+        if (AGG) tc[j] = 0, ts[j] = 0;
+    }
+    __syncthreads();
+    auto insert = [&](int64_t j, int32_t key, unsigned long long v) {
+        if (key == kEmpty) {
+            if (AGG) {
+                agg_add(t, agg_insert(t, key), 1u, v);
+                return;
+            }
+            bool fresh;
+            const int64_t slot = ht_insert(t, key, fresh);
+            if (unique && !fresh) raise_flag(status, TDP_FLAG_DUP_BUILD);
+            if (ROWID && fresh) t.rowid[slot] = row_value(t, j);
+            return;
+        }
+        uint32_t s = hash32((uint32_t)key) & t.bmask;
+        for (uint32_t probe = 0; probe < nslots; ++probe) {
+            const int32_t prev = atomicCAS(&tk[s], kEmpty, key);
+            if (prev == kEmpty || prev == key) {
+                if (prev == key && unique) raise_flag(status, TDP_FLAG_DUP_BUILD);
+                if (ROWID && prev == kEmpty) tr[s] = (int32_t)j;
+                if (AGG) {
+                    atomicAdd(&tc[s], 1u);
+                    if (t.with_sum) atomicAdd(&ts[s], v);
+                }
+                return;
+            }
+            s = (s + 1) & t.bmask;
+        }
+        raise_flag(status, TDP_FLAG_TABLE_FULL);
+    };
+    // the keys that fall here are first gathered in a list, so that every lane
+    // has one to insert; a row's value is read when the block is written, not
+    // in the insertion, where it would hold the wave for a memory latency
+    for (int64_t j0 = 0; j0 < n; j0 += kKeys * kDirectThreads) {
+        int32_t key[kKeys];
+#pragma unroll
+        for (int e = 0; e < kKeys; ++e) {
+            const int64_t j = j0 + e * kDirectThreads + threadIdx.x;
+            key[e] = bkey[j < n ? j : n - 1];
+        }
+        if (threadIdx.x == 0) s_n = 0;
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < kKeys; ++e) {
+            const int64_t j = j0 + e * kDirectThreads + threadIdx.x;
+            const bool here = j < n && (key[e] == kEmpty ? blockIdx.x == 0
+                                                         : (hash32((uint32_t)key[e]) & t.mask & ~t.bmask) == first);
+            const uint64_t m = ballot(here);
+            if (m == 0) continue;
+            uint32_t at = 0;
+            if (lane_id() == 0) at = atomicAdd(&s_n, (uint32_t)__popcll(m));
+            at = __builtin_amdgcn_readfirstlane(at) + lanes_below(m);
+            if (here) s_list[at] = make_int2(key[e], (int32_t)j);
+        }
+        __syncthreads();
+        for (uint32_t i = threadIdx.x; i < s_n; i += kDirectThreads) {
+            const int2 r = s_list[i];
+            insert(r.y, r.x, AGG && t.with_sum ? (unsigned long long)load_int(bvals, bdt, r.y) : 0ull);
+        }
+        __syncthreads();
+    }
+#pragma unroll 4
+    for (uint32_t j = threadIdx.x; j < nslots; j += kDirectThreads) {
+        if (AGG) {
+            AggRec r;
+            r.key = tk[j];
+            r.cnt = tc[j];
+            r.sum = ts[j];
+            t.rec[first + j] = r;
+        } else {
+            t.keys[first + j] = tk[j];
+            if (ROWID && tk[j] != kEmpty) t.rowid[first + j] = row_value(t, tr[j]);
         }
     }
 }
@@ -221,10 +318,11 @@ __global__ __launch_bounds__(256) void lb_basescan_kernel(uint32_t* tot, uint32_
 
 template <int T>
 __global__ __launch_bounds__(T) void lb_scatter_kernel(const int32_t* __restrict__ bkey, int64_t n, int64_t chunk,
-                                                         uint32_t mask, int gshift, uint32_t nblk, const uint32_t* mat,
+                                                         HashView t, int gshift, uint32_t nblk, const uint32_t* mat,
                                                          const uint32_t* base, int32_t* skeys, int32_t* srows,
                                                          const void* __restrict__ bvals, int bdt, AggIn* srec) {
     extern __shared__ uint32_t cur[];
+    const uint32_t mask = t.mask;
     for (uint32_t b = threadIdx.x; b < nblk; b += T) cur[b] = base[b] + mat[(int64_t)blockIdx.x * nblk + b];
     __syncthreads();
     const int64_t lo = (int64_t)blockIdx.x * chunk, hi = lo + chunk < n ? lo + chunk : n;
@@ -238,7 +336,7 @@ __global__ __launch_bounds__(T) void lb_scatter_kernel(const int32_t* __restrict
             srec[pos] = r;
         } else {
             skeys[pos] = key;
-            if (srows) srows[pos] = (int32_t)i;
+            if (srows) srows[pos] = row_value(t, i);
         }
     });
 }
@@ -651,9 +749,24 @@ int table_clear_zero(const HashView& t, bool all_slots, int32_t* d_status, unsig
 int table_build(const HashView& t, const BuildScratch& bs, TableKind kind, const int32_t* build_key, int64_t n_build,
                 bool unique, const void* b_vals, int b_dt, int32_t* d_status, hipStream_t s) {
     if (n_build <= 0) {
-        if (bs.lds) {  // the LDS build writes every block; with no rows, clear them here
+        if (bs.lds || bs.direct) {  // these builds write every block; with no rows, clear them here
             table_clear_kernel<<<grid_for((int64_t)t.mask + 1, 256 * 4), 256, 0, s>>>(t, 0, (int64_t)t.mask + 1, nullptr,
                                                                                      nullptr, nullptr, nullptr, 0);
+        }
+        return launch_status("hash table build");
+    }
+    if (bs.direct) {
+        const unsigned blocks = (t.mask + 1) / (t.bmask + 1);
+        switch (kind) {
+            case TABLE_ROWID:
+                direct_build_kernel<TABLE_ROWID><<<blocks, kDirectThreads, 0, s>>>(t, build_key, n_build, unique, b_vals, b_dt, d_status);
+                break;
+            case TABLE_AGG:
+                direct_build_kernel<TABLE_AGG><<<blocks, kDirectThreads, 0, s>>>(t, build_key, n_build, unique, b_vals, b_dt, d_status);
+                break;
+            default:
+                direct_build_kernel<TABLE_KEYS><<<blocks, kDirectThreads, 0, s>>>(t, build_key, n_build, unique, b_vals, b_dt, d_status);
+                break;
         }
         return launch_status("hash table build");
     }
@@ -674,10 +787,10 @@ int table_build(const HashView& t, const BuildScratch& bs, TableKind kind, const
                                                                       bs.nblk, bs.mat, bs.base, b_vals, b_dt, bs.srec,
                                                                       d_status);
         else if (bs.threads == 1024)
-            lb_scatter_kernel<1024><<<bs.nw, 1024, lds, s>>>(build_key, n_build, bs.chunk, t.mask, bs.gshift, bs.nblk, bs.mat,
+            lb_scatter_kernel<1024><<<bs.nw, 1024, lds, s>>>(build_key, n_build, bs.chunk, t, bs.gshift, bs.nblk, bs.mat,
                                                              bs.base, bs.skeys, bs.srows, b_vals, b_dt, bs.srec);
         else
-            lb_scatter_kernel<512><<<bs.nw, 512, lds, s>>>(build_key, n_build, bs.chunk, t.mask, bs.gshift, bs.nblk, bs.mat,
+            lb_scatter_kernel<512><<<bs.nw, 512, lds, s>>>(build_key, n_build, bs.chunk, t, bs.gshift, bs.nblk, bs.mat,
                                                            bs.base, bs.skeys, bs.srows, b_vals, b_dt, bs.srec);
         const size_t glds = (size_t)bs.gslots * (kind == TABLE_KEYS ? 4 : kind == TABLE_ROWID ? 8 : 16);
         switch (kind) {

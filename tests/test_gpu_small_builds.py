@@ -1,0 +1,97 @@
+"""Hash tables of small build sides built block by block in LDS, tables that
+keep a build-side column's values, and the partial rows of the fused
+group-by, bit-exact against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2211_02753_amd import _lib as L
+from paper_2211_02753_amd import query as Q
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+
+
+def _same(got, want, n_keys):
+    for k in (["k0", "k1"][:n_keys] + ["sum", "count", "avg"]):
+        assert np.array_equal(got[k].cpu().numpy(), want[k]), k
+
+
+# register rows, one-workgroup totals (up to 256 groups) and the two-kernel totals; one row, one workgroup less a
+# row, every CU with small workgroups, every CU with large ones, and a second step
+@pytest.mark.parametrize("G", [1, 8, 9, 64, 65, 256, 257, 2048])
+@pytest.mark.parametrize("n", [1, 1023, 262_143, 262_145, 1_100_003])
+def test_partial_rows(G, n):
+    rng = np.random.default_rng(G * 31 + n)
+    k = rng.integers(0, G, n).astype(np.int32)
+    v = rng.integers(-2**62, 2**62, n)  # sums wrap
+    print("partial rows", G, n, flush=True)
+    got = Q.GroupbyQuery(n, [Q.Key(dev(k), 0, G)], expr=L.EXPR_COL, a=Q.Operand(dev(v)))
+    want = oracle.query(n, keys=[(k, 0)], expr=oracle.EXPR_COL, a=(v, 0))
+    _same(got(), want, 1)
+    _same(got(), want, 1)  # a second call on the same workspace
+    top = Q.GroupbyQuery(n, [Q.Key(dev(k), 0, G)], expr=L.EXPR_COL, a=Q.Operand(dev(v)), topk=5)()
+    order = np.lexsort((want["k0"], -want["sum"].astype(object)))[:5]
+    assert np.array_equal(top["k0"].cpu().numpy(), want["k0"][order])
+    assert np.array_equal(top["sum"].cpu().numpy(), want["sum"][order])
+
+
+# one row, one probing block, several, the last direct build and the first bucketed one
+@pytest.mark.parametrize("nb", [1, 2047, 2049, 10_000, 65_535, 65_536])
+@pytest.mark.parametrize("mode", ["keys", "i8", "i32", "value", "i64", "two", "agg", "aggcount"])
+def test_small_build_sides(nb, mode):
+    rng = np.random.default_rng(nb + len(mode))
+    n = 50_001
+    pool = rng.permutation(np.concatenate([[-2**31, 2**31 - 1, 0], rng.integers(-2**31, 2**31, 2 * nb + 10)]))
+    pool = np.unique(pool)
+    pool = rng.permutation(pool)
+    uniq = pool[:nb].astype(np.int32)
+    if -2**31 not in uniq:
+        uniq[0] = -2**31
+    bk = uniq if not mode.startswith("agg") else uniq[rng.integers(0, max(1, nb // 3), nb)]
+    pk = np.where(rng.random(n) < 0.8, uniq[rng.integers(0, nb, n)], pool[rng.integers(0, len(pool), n)]).astype(np.int32)
+    g = rng.integers(0, 30, n).astype(np.int32)
+    v = rng.integers(-2**40, 2**40, n)
+    b8, b32 = rng.integers(0, 25, nb).astype(np.int8), rng.integers(0, 25, nb).astype(np.int32)
+    bv = rng.integers(-2**31, 2**31, nb).astype(np.int32)  # every 32-bit value
+    b64 = rng.integers(-2**40, 2**40, nb)
+    col, none = oracle.EXPR_COL, oracle.EXPR_NONE
+    P, B = 0, 1
+    keys, expr, a = {"keys": ([(g, P, 30)], col, (v, P)), "i8": ([(b8, B, 25), (g, P, 30)], col, (v, P)),
+                     "i32": ([(g, P, 30), (b32, B, 25)], none, None), "value": ([(g, P, 30)], col, (bv, B)),
+                     "i64": ([(g, P, 30)], col, (b64, B)), "two": ([(b8, B, 25), (b32, B, 25)], col, (v, P)),
+                     "agg": ([(g, P, 30)], col, (b64, B)), "aggcount": ([(g, P, 30)], none, None)}[mode]
+    unique = not mode.startswith("agg")
+    print("small build", nb, mode, flush=True)
+    d = {id(x): dev(x) for x in (g, v, b8, b32, bv, b64)}
+    for load in (0, 90):
+        got = Q.GroupbyQuery(n, [Q.Key(d[id(c)], 0, card, L.BUILD if s else L.PROBE) for c, s, card in keys],
+                             expr=L.EXPR_COL if expr == col else L.EXPR_NONE,
+                             a=None if a is None else Q.Operand(d[id(a[0])], L.BUILD if a[1] else L.PROBE),
+                             join=(dev(bk), dev(pk), unique, load))()
+        want = oracle.query(n, keys=[(c, s) for c, s, _ in keys], expr=expr, a=a, join=(pk, bk))
+        _same(got, want, len(keys))
+
+
+def test_small_build_flags():
+    n = 1000
+    pk = dev(np.arange(n, dtype=np.int32))
+    g = dev(np.zeros(n, np.int32))
+    dup = np.arange(5000, dtype=np.int32)
+    dup[4999] = 17
+    with pytest.raises(L.TdpError, match="DUP_BUILD"):
+        Q.GroupbyQuery(n, [Q.Key(g, 0, 1)], join=(dev(dup), pk, True))()
+    twice = np.arange(5000, dtype=np.int32)
+    twice[[3, 4]] = -2**31  # the key kept outside the blocks
+    with pytest.raises(L.TdpError, match="DUP_BUILD"):
+        Q.GroupbyQuery(n, [Q.Key(g, 0, 1)], join=(dev(twice), pk, True))()
+    with pytest.raises(L.TdpError, match="TABLE_FULL"):  # 30,000 distinct keys against a bound of 1000
+        Q.GroupbyQuery(n, [Q.Key(g, 0, 1)], join=(dev(np.arange(30_000, dtype=np.int32)), pk, False, 0, 1000))()
+    # an empty build side, then a full one on a fresh plan
+    r = Q.GroupbyQuery(n, [Q.Key(g, 0, 1)], join=(dev(np.zeros(0, np.int32)), pk, True))()
+    assert r["k0"].numel() == 0
