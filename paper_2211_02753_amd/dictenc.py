@@ -13,7 +13,7 @@ from __future__ import annotations
 import torch
 
 from . import _lib as L
-from .query import check_flags
+from .query import _count_status, _read, check_flags
 
 
 def _status(dev):
@@ -28,15 +28,13 @@ def encode(strs: torch.Tensor, max_distinct: int = 0):
     n, width = strs.shape
     dev = strs.device
     md = max_distinct or n
-    dict_buf = torch.zeros((max(md, 1), width), dtype=torch.uint8, device=dev)
+    dict_buf = torch.empty((max(md, 1), width), dtype=torch.uint8, device=dev)
     codes = torch.empty(max(n, 1), dtype=torch.int32, device=dev)
-    d_n = torch.zeros(1, dtype=torch.int64, device=dev)
-    st = _status(dev)
+    both, d_n, st = _count_status(dev)
     ws = L.workspace(lib.tdp_dict_build_workspace_size(n, max_distinct), dev)
     L.check("tdp_dict_build", lib.tdp_dict_build(L.ptr(strs), n, width, int(max_distinct), L.ptr(dict_buf), L.ptr(d_n),
                                                  L.ptr(codes), L.ptr(st), L.ptr(ws), ws.numel(), L.stream_handle(dev)))
-    d = int(d_n.item())
-    check_flags(st, "tdp_dict_build")
+    d = _read(both, "tdp_dict_build")
     return dict_buf[:d], codes[:n]
 
 

@@ -14,8 +14,25 @@ def _status(device):
     return torch.zeros(1, dtype=torch.int32, device=device)
 
 
+def _count_status(device):
+    """Device words for a call's row or group count (int64 [1]) and its status
+    (int32 [1]), side by side so that one copy and one wait read both."""
+    both = torch.empty(2, dtype=torch.int64, device=device)
+    return both, both[:1], both.view(torch.int32)[2:3]
+
+
+def _read(both: torch.Tensor, what: str) -> int:
+    """The count of a finished call, after raising on its flags."""
+    m, st = both.tolist()
+    check_flag_bits(st & 0xFFFFFFFF, what)
+    return m
+
+
 def check_flags(d_status: torch.Tensor, what: str):
-    v = int(d_status.item())
+    check_flag_bits(int(d_status.item()), what)
+
+
+def check_flag_bits(v: int, what: str):
     if v:
         names = [n for n, b in [("KEY_DOMAIN", L.FLAG_KEY_DOMAIN), ("DUP_BUILD", L.FLAG_DUP_BUILD),
                                 ("GROUP_RANGE", L.FLAG_GROUP_RANGE), ("TABLE_FULL", L.FLAG_TABLE_FULL),
@@ -29,16 +46,13 @@ def filter(col: torch.Tensor, op: str, literal: int, sel: torch.Tensor | None = 
     dev = col.device
     n_cand = col.numel() if sel is None else sel.numel()
     out = torch.empty(max(n_cand, 1), dtype=torch.int32, device=dev)
-    n_out = torch.zeros(1, dtype=torch.int64, device=dev)
-    st = _status(dev)
+    both, n_out, st = _count_status(dev)
     ws = L.workspace(lib.tdp_filter_workspace_size(n_cand), dev)
     c = L.col(col)
     L.check("tdp_filter", lib.tdp_filter(C.byref(c), L.CMP[op], int(literal), L.ptr(sel), n_cand if sel is not None else 0,
                                          L.ptr(out), out.numel(), L.ptr(n_out), L.ptr(st), L.ptr(ws), ws.numel(),
                                          L.stream_handle(dev)))
-    m = int(n_out.item())
-    check_flags(st, "tdp_filter")
-    return out[:m]
+    return out[:_read(both, "tdp_filter")]
 
 
 def hash_join(build_key: torch.Tensor, probe_key: torch.Tensor, probe_sel: torch.Tensor | None = None,
@@ -52,26 +66,20 @@ def hash_join(build_key: torch.Tensor, probe_key: torch.Tensor, probe_sel: torch
                    None if probe_sel is None else probe_sel.data_ptr(), 0 if probe_sel is None else probe_sel.numel(),
                    int(build_unique), int(load_pct), int(max_distinct))
     ws = L.workspace(lib.tdp_hash_join_workspace_size(C.byref(d)), dev)
-    n_out = torch.zeros(1, dtype=torch.int64, device=dev)
-    st = _status(dev)
+    both, n_out, st = _count_status(dev)
     s = L.stream_handle(dev)
     if count_only:
         L.check("tdp_hash_join", lib.tdp_hash_join(C.byref(d), L.JOIN_COUNT, None, None, 0, L.ptr(n_out), L.ptr(st),
                                                    L.ptr(ws), ws.numel(), s))
-        total = int(n_out.item())
-        check_flags(st, "tdp_hash_join")
-        return total
+        return _read(both, "tdp_hash_join")
     L.check("tdp_hash_join", lib.tdp_hash_join(C.byref(d), L.JOIN_COUNT, None, None, 0, L.ptr(n_out), L.ptr(st),
                                                L.ptr(ws), ws.numel(), s))
-    total = int(n_out.item())
-    check_flags(st, "tdp_hash_join")
+    total = _read(both, "tdp_hash_join")
     a = torch.empty(max(total, 1), dtype=torch.int32, device=dev)
     b = torch.empty(max(total, 1), dtype=torch.int32, device=dev)
     L.check("tdp_hash_join", lib.tdp_hash_join(C.byref(d), L.JOIN_PAIRS, L.ptr(a), L.ptr(b), total, L.ptr(n_out),
                                                L.ptr(st), L.ptr(ws), ws.numel(), s))
-    got = int(n_out.item())
-    check_flags(st, "tdp_hash_join")
-    assert got == total
+    assert _read(both, "tdp_hash_join") == total
     return a[:total], b[:total]
 
 
@@ -167,13 +175,13 @@ class GroupbyQuery:
             L.check("tdp_groupby_workspace_size", lib.tdp_groupby_agg(C.byref(d), None, None, None, 0, None))
         self.ws = L.workspace(ws_bytes, dev)
         i64 = dict(dtype=torch.int64, device=dev)
-        self.n_groups = torch.zeros(1, **i64)
+        self._both, self.n_groups, self.status = _count_status(dev)
+        self._both.zero_()
         self.key0 = torch.empty(self.cap, **i64)
         self.key1 = torch.empty(self.cap, **i64)
         self.sum = torch.empty(self.cap, **i64)
         self.count = torch.empty(self.cap, **i64)
         self.avg = torch.empty(self.cap, dtype=torch.float64, device=dev)
-        self.status = _status(dev)
         self.out = L.GroupbyOut(self.cap, self.n_groups.data_ptr(), self.key0.data_ptr(), self.key1.data_ptr(),
                                 self.sum.data_ptr(), self.count.data_ptr(), self.avg.data_ptr())
 
@@ -196,8 +204,7 @@ class GroupbyQuery:
                                                            L.ptr(self.ws), self.ws.numel(), s))
 
     def result(self):
-        m = int(self.n_groups.item())
-        check_flags(self.status, "tdp_groupby_agg")
+        m = _read(self._both, "tdp_groupby_agg")
         r = {"k0": self.key0[:m], "sum": self.sum[:m], "count": self.count[:m], "avg": self.avg[:m]}
         if len(self.keys) > 1:
             r["k1"] = self.key1[:m]
