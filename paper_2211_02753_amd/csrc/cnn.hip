@@ -17,7 +17,7 @@
 // weights in registers and stream 16-pixel blocks through the 16x16x32
 // instruction.  bf16 values are stored as uint16_t bit patterns and rounded
 // from float32 to nearest even.
-#include "common.hpp"
+#include "conv_lds.hpp"
 
 namespace tdp {
 
@@ -1174,6 +1174,9 @@ extern "C" int tdp_conv3x3_fwd_bf16(const uint16_t* x, const uint16_t* w, const 
         return launch_status("tdp_conv3x3_fwd_bf16");
     }
     const int64_t x_bytes = (int64_t)B * H * W * Cin * 2;
+    // 32 -> 64 channels: bands of rows in LDS, unless a row is too wide for one
+    if (M > 0 && Cin == 32 && Cout == 64 && a16(y) && conv_fwd_32_64(x, w, bias, B, H, W, relu, y, stream))
+        return launch_status("tdp_conv3x3_fwd_bf16");
     if (Cin == 32 && Cout % 16 == 0 && Cout <= 64 && a16(y) && x_bytes < (1ll << 31)) {
         if (M > 0) {
             // two workgroups of four waves per CU, each wave a contiguous range of 16-pixel blocks
@@ -1203,6 +1206,9 @@ extern "C" int tdp_conv3x3_dgrad_bf16(const uint16_t* dy, const uint16_t* w, con
     if (!a16(dy)) return fail(TDP_EINVAL, "tdp_conv3x3_dgrad_bf16: dy must be 16-byte aligned");
     const int64_t M = (int64_t)B * H * W;
     const int64_t dy_bytes = (int64_t)B * (H - 2) * (W - 2) * Cout * 2;
+    if (M > 0 && Cout == 64 && Cin == 32 && a16(w) && a16(dx) && a16(mask_act) &&
+        conv_dgrad_64_32(dy, w, mask_act, B, H, W, dx, stream))
+        return launch_status("tdp_conv3x3_dgrad_bf16");
     if (Cout == kDgCout && (Cin == 16 || Cin == 32) && a16(w) && a16(dx) && (!mask_act || ((uintptr_t)mask_act & 7) == 0) &&
         dy_bytes < (1ll << 31) && M * Cin * 2 < (1ll << 31)) {
         if (M > 0) {
@@ -1243,6 +1249,8 @@ extern "C" int tdp_conv3x3_wgrad_bf16(const uint16_t* x, const uint16_t* dy, int
         }
         return launch_status("tdp_conv3x3_wgrad_bf16");
     }
+    if (M > 0 && Cin == 32 && Cout == 64 && conv_wgrad_32_64(x, dy, B, H, W, dw, db, stream))
+        return launch_status("tdp_conv3x3_wgrad_bf16");
     ConvWgradOp op{x, dy, dw, H, W, Cin, H - 2, W - 2, Cout, M, 0, 9 * Cin};
     op.kchunk = split_chunk(op.K, ceil_div(op.M, kT) * ceil_div(op.N, kT));
     return launch_gemm(op, stream, "tdp_conv3x3_wgrad_bf16", db);
