@@ -31,28 +31,41 @@ struct LlpArgs {
     const float* W;  // [C][F]
     const float* b;  // [C]
     int64_t bag;
+    int bag_shift;   // log2(bag): a 64-bit division per row cost more than the rest of it
+};
+
+// The classifier in registers (features past F are zero).
+template <int C, int FM>
+struct LlpParams {
+    float w[C][FM], b[C];
+    __device__ __forceinline__ explicit LlpParams(const LlpArgs& a) {
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            b[c] = a.b[c];
+#pragma unroll
+            for (int f = 0; f < FM; ++f) w[c][f] = f < a.F ? a.W[c * a.F + f] : 0.0f;
+        }
+    }
 };
 
 // Class probabilities of one row: softmax of W x + b, float32.
-template <int C>
-__device__ __forceinline__ void llp_probs(const float* s_w, const float* s_b, const float x[kLlpMaxF], int F,
-                                          float p[C]) {
+template <int C, int FM>
+__device__ __forceinline__ void llp_probs(const LlpParams<C, FM>& m, const float x[FM], float p[C]) {
     float z[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-        float a = s_b[c];
+        float a = m.b[c];
 #pragma unroll
-        for (int f = 0; f < kLlpMaxF; ++f)
-            if (f < F) a = fmaf(s_w[c * kLlpMaxF + f], x[f], a);
+        for (int f = 0; f < FM; ++f) a = fmaf(m.w[c][f], x[f], a);  // zeros past F
         z[c] = a;
     }
-    float m = z[0];
+    float top = z[0];
 #pragma unroll
-    for (int c = 1; c < C; ++c) m = fmaxf(m, z[c]);
+    for (int c = 1; c < C; ++c) top = fmaxf(top, z[c]);
     float sum = 0.0f;
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-        z[c] = __expf(z[c] - m);
+        z[c] = __expf(z[c] - top);
         sum += z[c];
     }
     const float inv = 1.0f / sum;
@@ -60,14 +73,15 @@ __device__ __forceinline__ void llp_probs(const float* s_w, const float* s_b, co
     for (int c = 0; c < C; ++c) p[c] = z[c] * inv;
 }
 
-__device__ __forceinline__ void llp_load_row(const LlpArgs& a, int64_t row, float x[kLlpMaxF]) {
+template <int FM>
+__device__ __forceinline__ void llp_load_row(const LlpArgs& a, int64_t row, float x[FM]) {
 #pragma unroll
-    for (int f = 0; f < kLlpMaxF; ++f) x[f] = 0.0f;
+    for (int f = 0; f < FM; ++f) x[f] = 0.0f;
     if (row >= a.n) return;
     const float* src = a.X + row * a.F;
     if ((a.F & 3) == 0) {
 #pragma unroll
-        for (int f = 0; f < kLlpMaxF; f += 4) {
+        for (int f = 0; f < FM; f += 4) {
             if (f < a.F) {
                 const float4 q = *(const float4*)(src + f);
                 x[f] = q.x; x[f + 1] = q.y; x[f + 2] = q.z; x[f + 3] = q.w;
@@ -75,66 +89,97 @@ __device__ __forceinline__ void llp_load_row(const LlpArgs& a, int64_t row, floa
         }
     } else {
 #pragma unroll
-        for (int f = 0; f < kLlpMaxF; ++f)
+        for (int f = 0; f < FM; ++f)
             if (f < a.F) x[f] = src[f];
     }
 }
 
-__device__ __forceinline__ void llp_stage_params(const LlpArgs& a, int C, float* s_w, float* s_b) {
-    for (int i = threadIdx.x; i < C * kLlpMaxF; i += blockDim.x) {
-        const int c = i / kLlpMaxF, f = i % kLlpMaxF;
-        s_w[i] = f < a.F ? a.W[c * a.F + f] : 0.0f;
-    }
-    for (int c = threadIdx.x; c < C; c += blockDim.x) s_b[c] = a.b[c];
-    __syncthreads();
-}
-
-// Squared error of one bag's counts against T, its gradient written to dS
+// Squared error of one cell's count against T, its gradient written to dS
 // (float64 arithmetic, as the oracle's mean squared error).
-template <int C>
-__device__ __forceinline__ double llp_bag_loss(int64_t j, const double acc[C], float* S, const float* T, float* dS,
-                                               double inv_cells) {
-    double l = 0.0;
-#pragma unroll
-    for (int c = 0; c < C; ++c) {
-        const float sv = (float)acc[c];
-        S[j * C + c] = sv;
-        if (T) {
-            const double d = (double)sv - (double)T[j * C + c];
-            l += d * d;
-            dS[j * C + c] = (float)(2.0 * d * inv_cells);
-        }
-    }
-    return l;
+__device__ __forceinline__ double llp_cell_loss(int64_t cell, double acc, float* S, const float* T, float* dS,
+                                                double inv_cells) {
+    const float sv = (float)acc;
+    S[cell] = sv;
+    if (!T) return 0.0;
+    const double d = (double)sv - (double)T[cell];
+    dS[cell] = (float)(2.0 * d * inv_cells);
+    return d * d;
 }
 
-template <int C>
+// One butterfly step that also halves the values: the lanes with the bit
+// `off` keep the pair sum of b, the others that of a.
+__device__ __forceinline__ double llp_fold(double a, double b, int off, int lane) {
+    const bool hi = lane & off;
+    return (hi ? b : a) + __shfl_xor(hi ? a : b, off, kWave);
+}
+
+// FM: the features the kernel is built for, 8 or 16.  Two rows per lane are in
+// flight.
+template <int C, int FM>
 __global__ __launch_bounds__(kLlpThreads) void llp_fwd_kernel(LlpArgs a, float* S, const float* T, float* dS,
                                                               double* loss_part) {
-    __shared__ float s_w[kLlpMaxC * kLlpMaxF], s_b[kLlpMaxC];
     __shared__ double s_l[kLlpThreads / kWave];
-    llp_stage_params(a, C, s_w, s_b);
+    const LlpParams<C, FM> m(a);
     double lsum = 0.0;  // this lane's squared errors (lanes that write bags)
     const int lane = lane_id();
     const int64_t wave = ((int64_t)blockIdx.x * kLlpThreads + threadIdx.x) / kWave;
     const int64_t n_waves = (int64_t)gridDim.x * kLlpThreads / kWave;
-    const int64_t n_bags = (a.n + a.bag - 1) / a.bag;
+    const int64_t n_bags = (a.n + a.bag - 1) >> a.bag_shift;
     const double inv_cells = 1.0 / (double)(n_bags * C);
     if (a.bag <= kWave) {
         const int64_t units = (a.n + kWave - 1) / kWave;
-        for (int64_t u = wave; u < units; u += n_waves) {
-            const int64_t row = u * kWave + lane;
-            float x[kLlpMaxF], p[C];
-            llp_load_row(a, row, x);
-            llp_probs<C>(s_w, s_b, x, a.F, p);
-            double acc[C];
+        for (int64_t u = wave; u < units; u += 2 * n_waves) {
+            float x[2][FM], p[C];
+            double acc[2][C];
 #pragma unroll
-            for (int c = 0; c < C; ++c) acc[c] = row < a.n ? (double)p[c] : 0.0;
-            for (int off = 1; off < a.bag; off <<= 1) {
+            for (int k = 0; k < 2; ++k) llp_load_row<FM>(a, (u + k * n_waves) * kWave + lane, x[k]);
 #pragma unroll
-                for (int c = 0; c < C; ++c) acc[c] += __shfl_xor(acc[c], off, kWave);
+            for (int k = 0; k < 2; ++k) {
+                llp_probs<C, FM>(m, x[k], p);
+#pragma unroll
+                for (int c = 0; c < C; ++c) acc[k][c] = (u + k * n_waves) * kWave + lane < a.n ? (double)p[c] : 0.0;
             }
-            if ((lane & (a.bag - 1)) == 0 && row < a.n) lsum += llp_bag_loss<C>(row / a.bag, acc, S, T, dS, inv_cells);
+            // each bag's aligned group of lanes: the two units, then (even C)
+            // the classes, are folded into one another first, so that a
+            // step moves half the values of the one before
+            int off = (int)a.bag / 2, k = 0;
+            double v[C];
+            if (off == 0) {  // bags of one row: nothing to add
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const int64_t row = (u + q * n_waves) * kWave + lane;
+#pragma unroll
+                    for (int c = 0; c < C; ++c)
+                        if (row < a.n) lsum += llp_cell_loss(row * C + c, acc[q][c], S, T, dS, inv_cells);
+                }
+                continue;
+            }
+#pragma unroll
+            for (int c = 0; c < C; ++c) v[c] = llp_fold(acc[0][c], acc[1][c], off, lane);
+            k = lane & off ? 1 : 0;
+            off >>= 1;
+            int c0 = 0;
+            constexpr int H = C % 2 == 0 ? C / 2 : C;  // values after the classes are folded
+            const bool folded = C % 2 == 0 && off > 0;
+            if (folded) {
+#pragma unroll
+                for (int c = 0; c < H; ++c) v[c] = llp_fold(v[c], v[(c + H) % C], off, lane);
+                c0 = lane & off ? H : 0;
+                off >>= 1;
+            }
+            const int own = 2 * off - (off > 0);  // the lanes below this position repeat one sum
+            for (; off > 0; off >>= 1) {
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+                    if (c < H || !folded) v[c] += __shfl_xor(v[c], off, kWave);
+            }
+            // the first row of the lane's bag: a bag without one has no cells
+            const int64_t row = ((u + k * n_waves) * kWave + lane) & ~(a.bag - 1);
+            if ((lane & own) == 0 && row < a.n)
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+                    if (c < H || !folded)
+                        lsum += llp_cell_loss((row >> a.bag_shift) * C + c0 + c, v[c], S, T, dS, inv_cells);
         }
     } else {
         for (int64_t j = wave; j < n_bags; j += n_waves) {
@@ -142,19 +187,25 @@ __global__ __launch_bounds__(kLlpThreads) void llp_fwd_kernel(LlpArgs a, float* 
             double acc[C];
 #pragma unroll
             for (int c = 0; c < C; ++c) acc[c] = 0.0;
-            for (int64_t row = r0 + lane; row < r1; row += kWave) {
-                float x[kLlpMaxF], p[C];
-                llp_load_row(a, row, x);
-                llp_probs<C>(s_w, s_b, x, a.F, p);
+            for (int64_t row = r0 + lane; row < r1; row += 2 * kWave) {
+                float x[2][FM], p[C];
 #pragma unroll
-                for (int c = 0; c < C; ++c) acc[c] += (double)p[c];
+                for (int k = 0; k < 2; ++k) llp_load_row<FM>(a, row + k * kWave < r1 ? row + k * kWave : a.n, x[k]);
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    llp_probs<C, FM>(m, x[k], p);
+#pragma unroll
+                    for (int c = 0; c < C; ++c) acc[c] += row + k * kWave < r1 ? (double)p[c] : 0.0;
+                }
             }
 #pragma unroll
             for (int off = 1; off < kWave; off <<= 1) {
 #pragma unroll
                 for (int c = 0; c < C; ++c) acc[c] += __shfl_xor(acc[c], off, kWave);
             }
-            if (lane == 0) lsum += llp_bag_loss<C>(j, acc, S, T, dS, inv_cells);
+            if (lane == 0)
+#pragma unroll
+                for (int c = 0; c < C; ++c) lsum += llp_cell_loss(j * C + c, acc[c], S, T, dS, inv_cells);
         }
     }
     if (T) {  // the workgroup's squared errors, in a fixed order
@@ -190,60 +241,61 @@ __global__ __launch_bounds__(kLlpFinThreads) void llp_loss_finish_kernel(const d
 
 // Per-thread gradient terms over a grid-stride of rows, reduced to one
 // float64 partial row per workgroup: [C][kLlpMaxF] weights then [C] biases.
-template <int C>
+template <int C, int FM>
 __global__ __launch_bounds__(kLlpThreads) void llp_bwd_kernel(LlpArgs a, const float* __restrict__ dS, double* part) {
-    __shared__ float s_w[kLlpMaxC * kLlpMaxF], s_b[kLlpMaxC];
-    __shared__ double s_red[kLlpThreads / kWave];
-    llp_stage_params(a, C, s_w, s_b);
-    float gw[C][kLlpMaxF], gb[C];
+    __shared__ double s_red[kLlpThreads / kWave][C * (FM + 1)];
+    const LlpParams<C, FM> m(a);
+    float gw[C][FM], gb[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         gb[c] = 0.0f;
 #pragma unroll
-        for (int f = 0; f < kLlpMaxF; ++f) gw[c][f] = 0.0f;
+        for (int f = 0; f < FM; ++f) gw[c][f] = 0.0f;
     }
     const int64_t stride = (int64_t)gridDim.x * kLlpThreads;
-    for (int64_t row = (int64_t)blockIdx.x * kLlpThreads + threadIdx.x; row < a.n; row += stride) {
-        float x[kLlpMaxF], p[C], dp[C];
-        llp_load_row(a, row, x);
-        llp_probs<C>(s_w, s_b, x, a.F, p);
-        const float* d = dS + (row / a.bag) * C;
-        float s = 0.0f;
+    for (int64_t r0 = (int64_t)blockIdx.x * kLlpThreads + threadIdx.x; r0 < a.n; r0 += 2 * stride) {
+        float x[2][FM], dp[2][C];
 #pragma unroll
-        for (int c = 0; c < C; ++c) {
-            dp[c] = d[c];
-            s = fmaf(p[c], dp[c], s);
+        for (int k = 0; k < 2; ++k) {
+            const int64_t row = r0 + k * stride;
+            llp_load_row<FM>(a, row, x[k]);
+            const float* d = dS + ((row < a.n ? row : r0) >> a.bag_shift) * C;
+#pragma unroll
+            for (int c = 0; c < C; ++c) dp[k][c] = d[c];
         }
 #pragma unroll
-        for (int c = 0; c < C; ++c) {
-            const float dz = p[c] * (dp[c] - s);
-            gb[c] += dz;
+        for (int k = 0; k < 2; ++k) {
+            if (r0 + k * stride >= a.n) continue;
+            float p[C], s = 0.0f;
+            llp_probs<C, FM>(m, x[k], p);
 #pragma unroll
-            for (int f = 0; f < kLlpMaxF; ++f) gw[c][f] = fmaf(dz, x[f], gw[c][f]);
+            for (int c = 0; c < C; ++c) s = fmaf(p[c], dp[k][c], s);
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                const float dz = p[c] * (dp[k][c] - s);
+                gb[c] += dz;
+#pragma unroll
+                for (int f = 0; f < FM; ++f) gw[c][f] = fmaf(dz, x[k][f], gw[c][f]);
+            }
         }
     }
     // workgroup sums in float64, written as this workgroup's partial row
     const int lane = lane_id(), wv = threadIdx.x / kWave;
-    double* row = part + (int64_t)blockIdx.x * C * (kLlpMaxF + 1);
-    for (int k = 0; k < C * (kLlpMaxF + 1); ++k) {
-        const int c = k / (kLlpMaxF + 1), f = k % (kLlpMaxF + 1);
-        float v = 0.0f;
 #pragma unroll
-        for (int cc = 0; cc < C; ++cc)
+    for (int c = 0; c < C; ++c)
 #pragma unroll
-            for (int ff = 0; ff <= kLlpMaxF; ++ff)
-                if (cc == c && ff == f) v = ff < kLlpMaxF ? gw[cc][ff] : gb[cc];
-        double t = (double)v;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, kWave);
-        if (lane == 0) s_red[wv] = t;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double tot = 0.0;
-            for (int w = 0; w < kLlpThreads / kWave; ++w) tot += s_red[w];
-            row[k] = tot;
+        for (int f = 0; f <= FM; ++f) {
+            const double t = wave_sum((double)(f < FM ? gw[c][f < FM ? f : 0] : gb[c]));
+            if (lane == 0) s_red[wv][c * (FM + 1) + f] = t;
         }
-        __syncthreads();
+    __syncthreads();
+    double* row = part + (int64_t)blockIdx.x * C * (kLlpMaxF + 1);
+    for (int k = threadIdx.x; k < C * (kLlpMaxF + 1); k += kLlpThreads) {
+        const int c = k / (kLlpMaxF + 1), f = k % (kLlpMaxF + 1), at = f < FM ? f : FM;
+        double tot = 0.0;
+        if (f < FM || f == kLlpMaxF)
+            for (int w = 0; w < kLlpThreads / kWave; ++w) tot += s_red[w][c * (FM + 1) + at];
+        row[k] = tot;
     }
 }
 
@@ -333,6 +385,24 @@ int llp_check(const LlpArgs& a, int C, const char* fn) {
     return TDP_OK;
 }
 
+int log2_of(int64_t v) {
+    int s = 0;
+    while (s < 62 && ((int64_t)1 << s) < v) ++s;
+    return s;
+}
+
+template <int C>
+void llp_fwd(const LlpArgs& a, int grid, float* S, const float* T, float* dS, double* lp, hipStream_t s) {
+    if (a.F <= 8) llp_fwd_kernel<C, 8><<<grid, kLlpThreads, 0, s>>>(a, S, T, dS, lp);
+    else llp_fwd_kernel<C, kLlpMaxF><<<grid, kLlpThreads, 0, s>>>(a, S, T, dS, lp);
+}
+
+template <int C>
+void llp_bwd(const LlpArgs& a, int grid, const float* dS, double* part, hipStream_t s) {
+    if (a.F <= 8) llp_bwd_kernel<C, 8><<<grid, kLlpThreads, 0, s>>>(a, dS, part);
+    else llp_bwd_kernel<C, kLlpMaxF><<<grid, kLlpThreads, 0, s>>>(a, dS, part);
+}
+
 int llp_grid(int64_t n) {
     return (int)std::min<int64_t>(std::max<int64_t>(ceil_div(n, (int64_t)kLlpThreads * 16), 1), kLlpMaxGrid);
 }
@@ -357,7 +427,7 @@ extern "C" size_t tdp_llp_workspace_size(int32_t C) {
 extern "C" int tdp_llp_bag_count(const float* X, int64_t n, int32_t F, const float* W, const float* b, int32_t C,
                                  int64_t bag, float* S, const float* T, float* d_loss, float* dS, void* ws,
                                  size_t ws_bytes, hipStream_t stream) {
-    LlpArgs a{X, n, F, W, b, bag};
+    LlpArgs a{X, n, F, W, b, bag, log2_of(bag)};
     int rc = llp_check(a, C, "tdp_llp_bag_count");
     if (rc) return rc;
     if (n > 0 && !S) return fail(TDP_EINVAL, "tdp_llp_bag_count: null S");
@@ -371,9 +441,9 @@ extern "C" int tdp_llp_bag_count(const float* X, int64_t n, int32_t F, const flo
     double* lp = T ? wa.take<double>(kLlpFwdMaxGrid) : nullptr;
     const int grid = (int)std::min<int64_t>(std::max<int64_t>(ceil_div(n, (int64_t)kLlpThreads * 8), 1), kLlpFwdMaxGrid);
     switch (C) {
-        case 2: llp_fwd_kernel<2><<<grid, kLlpThreads, 0, stream>>>(a, S, T, dS, lp); break;
-        case 3: llp_fwd_kernel<3><<<grid, kLlpThreads, 0, stream>>>(a, S, T, dS, lp); break;
-        default: llp_fwd_kernel<4><<<grid, kLlpThreads, 0, stream>>>(a, S, T, dS, lp); break;
+        case 2: llp_fwd<2>(a, grid, S, T, dS, lp, stream); break;
+        case 3: llp_fwd<3>(a, grid, S, T, dS, lp, stream); break;
+        default: llp_fwd<4>(a, grid, S, T, dS, lp, stream); break;
     }
     if (T) {
         const int64_t n_bags = (n + bag - 1) / bag;
@@ -385,7 +455,7 @@ extern "C" int tdp_llp_bag_count(const float* X, int64_t n, int32_t F, const flo
 extern "C" int tdp_llp_bag_count_bwd(const float* X, int64_t n, int32_t F, const float* W, const float* b, int32_t C,
                                      int64_t bag, const float* dS, float* dW, float* db, void* ws, size_t ws_bytes,
                                      hipStream_t stream) {
-    LlpArgs a{X, n, F, W, b, bag};
+    LlpArgs a{X, n, F, W, b, bag, log2_of(bag)};
     int rc = llp_check(a, C, "tdp_llp_bag_count_bwd");
     if (rc) return rc;
     if (!dW || !db || (n > 0 && !dS)) return fail(TDP_EINVAL, "tdp_llp_bag_count_bwd: null dS, dW or db");
@@ -395,9 +465,9 @@ extern "C" int tdp_llp_bag_count_bwd(const float* X, int64_t n, int32_t F, const
     double* part = (double*)ws;
     const int grid = llp_grid(n);
     switch (C) {
-        case 2: llp_bwd_kernel<2><<<grid, kLlpThreads, 0, stream>>>(a, dS, part); break;
-        case 3: llp_bwd_kernel<3><<<grid, kLlpThreads, 0, stream>>>(a, dS, part); break;
-        default: llp_bwd_kernel<4><<<grid, kLlpThreads, 0, stream>>>(a, dS, part); break;
+        case 2: llp_bwd<2>(a, grid, dS, part, stream); break;
+        case 3: llp_bwd<3>(a, grid, dS, part, stream); break;
+        default: llp_bwd<4>(a, grid, dS, part, stream); break;
     }
     llp_bwd_finish_kernel<<<1, kLlpFinThreads, 0, stream>>>(part, grid, C, F, dW, db);
     return launch_status("tdp_llp_bag_count_bwd");
@@ -405,7 +475,7 @@ extern "C" int tdp_llp_bag_count_bwd(const float* X, int64_t n, int32_t F, const
 
 extern "C" int tdp_llp_predict(const float* X, int64_t n, int32_t F, const float* W, const float* b, int32_t C,
                                int8_t* out, hipStream_t stream) {
-    LlpArgs a{X, n, F, W, b, 1};
+    LlpArgs a{X, n, F, W, b, 1, 0};
     int rc = llp_check(a, C, "tdp_llp_predict");
     if (rc) return rc;
     if (n > 0 && !out) return fail(TDP_EINVAL, "tdp_llp_predict: null out");

@@ -87,19 +87,59 @@ __device__ __forceinline__ void lds_add_f32(float* p, float v) {
     }
 }
 
-// Group j of a workgroup's LDS table kept as `copies` per-wave copies (one
-// per wave when the copies fit, so that compare-and-swap adds contend only
-// within a wave): the copies added in wave order in float64.
-__device__ __forceinline__ float sum_copies(const float* s_tab, int G, int copies, int j) {
-    if (copies == 1) return s_tab[j];
-    double a = 0.0;
-    for (int c = 0; c < copies; ++c) a += (double)s_tab[c * G + j];
-    return (float)a;
+// A 1024-thread forward keeps `copies` copies of its LDS group table: one per
+// wave when they fit the LDS budget (compare-and-swap adds then contend only
+// within a wave), and for few groups several per wave, lane l adding to copy l
+// mod copies-per-wave (64 lanes on 75 groups otherwise retry about five
+// times); else one.
+int table_copies(int64_t G) {
+    constexpr int waves = kFwdThreads / kWave;
+    if (G * waves > kMaxLdsFloats) return 1;
+    int copies = waves;
+    while (copies < 8 * waves && 2 * copies * G <= kMaxLdsFloats) copies *= 2;
+    return copies;
 }
 
-// Copies of an LDS group table a 1024-thread forward keeps: one per wave
-// when they fit the LDS budget, else one.
-int table_copies(int64_t G) { return G * (kFwdThreads / kWave) <= kMaxLdsFloats ? kFwdThreads / kWave : 1; }
+// This thread's copy.
+__device__ __forceinline__ int copy_of(int copies) {
+    constexpr int waves = kFwdThreads / kWave;
+    return copies <= waves ? (int)(threadIdx.x / kWave) % copies
+                           : (int)(threadIdx.x / kWave) + (int)(threadIdx.x & (copies / waves - 1)) * waves;
+}
+
+// The copies added in float64 and rounded once: out[j] for the workgroup's
+// groups j.  For few groups several threads share a group's copies, their
+// float64 parts in the table's own LDS (at least kSumLdsBytes).
+constexpr size_t kSumLdsBytes = kFwdThreads * sizeof(double);
+
+__device__ __forceinline__ void sum_copies(float* s_tab, int G, int copies, float* out) {
+    int share = 1;  // threads per group, a power of two
+    while (2 * share <= copies && 2 * share * G <= kFwdThreads) share *= 2;
+    if (share == 1) {
+        for (int j = threadIdx.x; j < G; j += kFwdThreads) {
+            double a = 0.0;
+            for (int c = 0; c < copies; ++c) a += (double)s_tab[c * G + j];
+            out[j] = (float)a;
+        }
+        return;
+    }
+    // share * G <= kFwdThreads: each thread has at most one part
+    const int j = (int)threadIdx.x / share, k = (int)threadIdx.x & (share - 1);
+    double a = 0.0;
+    if (j < G)
+        for (int c = k; c < copies; c += share) a += (double)s_tab[c * G + j];
+    double* s_part = (double*)s_tab;
+    __syncthreads();
+    s_part[threadIdx.x] = a;
+    __syncthreads();
+    if (k == 0 && j < G) {
+        for (int q = 1; q < share; ++q) a += s_part[threadIdx.x + q];
+        out[j] = (float)a;
+    }
+}
+
+// LDS of a forward workgroup.
+size_t fwd_lds(int copies, int64_t G) { return std::max((size_t)copies * G * sizeof(float), kSumLdsBytes); }
 
 __device__ __forceinline__ float logistic_t(float z, float& wd) {
     const float t = __expf(-fabsf(z));
@@ -198,6 +238,7 @@ __global__ __launch_bounds__(kFinishThreads) void soft_rows_finish_kernel(SoftWs
     const int c = threadIdx.x % kRfCols, sl = threadIdx.x / kRfCols;
     const int64_t j = (int64_t)blockIdx.x * kRfCols + c;
     double acc = 0.0;
+    const double target = T && sl == 0 && j < GK ? (double)T[j] : 0.0;  // in flight with the rows
     if (j < GK) {
         for (int r0 = sl; r0 < nrows; r0 += 16 * kRfSlices) {
             float t[16];
@@ -219,7 +260,7 @@ __global__ __launch_bounds__(kFinishThreads) void soft_rows_finish_kernel(SoftWs
         for (int k = 0; k < kRfSlices; ++k) tot += s_acc[k][c];
         S[j] = (float)tot;
         if (T) {
-            const double d = tot - (double)T[j];
+            const double d = tot - target;
             part = d * d;
             dS[j] = (float)(2.0 * d / (double)GK);
         }
@@ -229,6 +270,11 @@ __global__ __launch_bounds__(kFinishThreads) void soft_rows_finish_kernel(SoftWs
         return;
     }
     const double wg_part = block_sum_f64(part);
+    if (gridDim.x == 1) {
+        if (threadIdx.x == 0) *d_loss = (float)(wg_part / (double)GK);
+        release_scalars(ws, status);
+        return;
+    }
     if (threadIdx.x == 0) ws.part[blockIdx.x] = wg_part;
     if (!tree_arrive(&ws.tick[0], gridDim.x)) return;
     double v = 0.0;
@@ -410,7 +456,8 @@ __device__ __forceinline__ void load_xvg4(const float* __restrict__ x, const flo
 
 // Each thread takes two groups of four rows per step (rows i0.. and
 // i0 + half-stride..), issuing all six vector loads before the first
-// scatter-add, so twice the bytes are in flight per wave.
+// scatter-add, so twice the bytes are in flight per wave (the next step's
+// loads as well: 34 us for 10M rows and 1000 groups against 31).
 template <bool LDS>
 __global__ __launch_bounds__(kFwdThreads) void soft_fg_fwd_kernel(const float* __restrict__ x,
                                                                    const float* __restrict__ v,
@@ -418,9 +465,9 @@ __global__ __launch_bounds__(kFwdThreads) void soft_fg_fwd_kernel(const float* _
                                                                    const float* __restrict__ d_c, float inv_tau, int G,
                                                                    int copies, SoftWs ws, float* S, const float* T,
                                                                    float* d_loss, float* dS, int32_t* status) {
-    extern __shared__ float s_tab[];
+    extern __shared__ __attribute__((aligned(8))) float s_tab[];
     double* acc = ws.acc;
-    const int tab = (int)(threadIdx.x / kWave) % copies * G;  // this wave's copy of the table
+    const int tab = copy_of(copies) * G;
     if (LDS) {
         for (int j = threadIdx.x; j < copies * G; j += kFwdThreads) s_tab[j] = 0.0f;
         __syncthreads();
@@ -449,11 +496,12 @@ __global__ __launch_bounds__(kFwdThreads) void soft_fg_fwd_kernel(const float* _
     }
     if (LDS) {
         __syncthreads();
-        for (int j = threadIdx.x; j < G; j += kFwdThreads) ws.rows[(int64_t)blockIdx.x * G + j] = sum_copies(s_tab, G, copies, j);
+        sum_copies(s_tab, G, copies, ws.rows + (int64_t)blockIdx.x * G);
     }
 }
 
-template <bool LDS>
+// TAU: the temperature's gradient too.
+template <bool LDS, bool TAU>
 __global__ __launch_bounds__(kSoftThreads) void soft_fg_bwd_kernel(const float* __restrict__ x,
                                                                    const float* __restrict__ v,
                                                                    const int32_t* __restrict__ g, int64_t n,
@@ -502,7 +550,7 @@ __global__ __launch_bounds__(kSoftThreads) void soft_fg_bwd_kernel(const float* 
             dvs[e] = d * w;
             dxs[e] = -t;
             part += t;
-            part_tau -= t * z;  // dw/dtau = -w (1 - w) z / tau
+            if (TAU) part_tau -= t * z;  // dw/dtau = -w (1 - w) z / tau
         }
         if (full) {
             *(float4*)(dv + i0) = make_float4(dvs[0], dvs[1], dvs[2], dvs[3]);
@@ -518,6 +566,7 @@ __global__ __launch_bounds__(kSoftThreads) void soft_fg_bwd_kernel(const float* 
     }
     const double tot = block_sum_f64((double)part);
     if (threadIdx.x == 0) ws.part[blockIdx.x] = tot;
+    if (!TAU) return;
     const double tot_tau = block_sum_f64((double)part_tau);
     if (threadIdx.x == 0) ws.part2[blockIdx.x] = tot_tau;
 }
@@ -606,128 +655,191 @@ struct SqDev {
     const void* kp[2];
     int32_t kdt[2];
     int64_t lo[2], card[2];
+    int wide;                 // an int64 column, or a key domain that 32-bit differences do not decide
     int G;
     const void* a;            // value column, or null for COUNT
     int32_t adt;
 };
 
-// Four consecutive values from row i0 (a multiple of 4) as float32 / int64;
-// rows at or past n read 0.  Columns are 16-byte aligned.
-__device__ __forceinline__ void sq_load4f(const void* p, int dt, int64_t i0, int64_t n, float v[4]) {
-    if (i0 + 4 <= n) {
-        if (dt == TDP_F32) {
-            const float4 q = *(const float4*)((const float*)p + i0);
-            v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
-        } else if (dt == TDP_I32) {
-            const int4 q = *(const int4*)((const int32_t*)p + i0);
-            v[0] = (float)q.x; v[1] = (float)q.y; v[2] = (float)q.z; v[3] = (float)q.w;
-        } else if (dt == TDP_I8) {
-            const char4 q = *(const char4*)((const int8_t*)p + i0);
-            v[0] = (float)q.x; v[1] = (float)q.y; v[2] = (float)q.z; v[3] = (float)q.w;
-        } else {
-            const longlong2 a = *(const longlong2*)((const int64_t*)p + i0);
-            const longlong2 b = *(const longlong2*)((const int64_t*)p + i0 + 2);
-            v[0] = (float)a.x; v[1] = (float)a.y; v[2] = (float)b.x; v[3] = (float)b.y;
-        }
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            float t = 0.0f;
-            if (i0 + e < n) {
-                if (dt == TDP_F32) t = ((const float*)p)[i0 + e];
-                else if (dt == TDP_I32) t = (float)((const int32_t*)p)[i0 + e];
-                else if (dt == TDP_I8) t = (float)((const int8_t*)p)[i0 + e];
-                else t = (float)((const int64_t*)p)[i0 + e];
+// Four consecutive values of a column from row i0 (a multiple of 4; columns
+// are 16-byte aligned) as they lie in memory, rows at or past n as zeros: the
+// loads of every column are issued before the first conversion (a conversion
+// beside its load made each column wait for the one before).  WIDE: int64
+// columns too, whose upper two values are in b.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+template <bool WIDE>
+struct SqRaw {
+    u32x4 a;
+};
+template <>
+struct SqRaw<true> {
+    u32x4 a, b;
+};
+
+template <bool WIDE>
+__device__ __forceinline__ SqRaw<WIDE> sq_load(const void* p, int dt, int64_t i0, int64_t n) {
+    SqRaw<WIDE> r;
+    r.a = u32x4{0, 0, 0, 0};
+    if constexpr (WIDE) {
+        r.b = u32x4{0, 0, 0, 0};
+        if (dt == TDP_I64) {
+            if (i0 + 4 <= n) {
+                r.a = *(const u32x4*)((const int64_t*)p + i0);
+                r.b = *(const u32x4*)((const int64_t*)p + i0 + 2);
+            } else {
+                const u32x2* q = (const u32x2*)p + i0;
+                if (i0 < n) r.a.lo = q[0];
+                if (i0 + 1 < n) r.a.hi = q[1];
+                if (i0 + 2 < n) r.b.lo = q[2];
             }
-            v[e] = t;
+            return r;
         }
     }
+    if (i0 + 4 <= n) {
+        if (dt == TDP_I8) r.a[0] = *(const uint32_t*)((const int8_t*)p + i0);
+        else r.a = *(const u32x4*)((const int32_t*)p + i0);
+    } else if (dt == TDP_I8) {
+        const uint8_t* q = (const uint8_t*)p + i0;
+        if (i0 < n) r.a[0] = q[0];
+        if (i0 + 1 < n) r.a[0] |= (uint32_t)q[1] << 8;
+        if (i0 + 2 < n) r.a[0] |= (uint32_t)q[2] << 16;
+    } else {
+        const uint32_t* q = (const uint32_t*)p + i0;
+        if (i0 < n) r.a[0] = q[0];
+        if (i0 + 1 < n) r.a[1] = q[1];
+        if (i0 + 2 < n) r.a[2] = q[2];
+    }
+    return r;
 }
 
-__device__ __forceinline__ void sq_load4i(const void* p, int dt, int64_t i0, int64_t n, int64_t v[4]) {
-    if (i0 + 4 <= n) {
-        if (dt == TDP_I32) {
-            const int4 q = *(const int4*)((const int32_t*)p + i0);
-            v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
-        } else if (dt == TDP_I8) {
-            const char4 q = *(const char4*)((const int8_t*)p + i0);
-            v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
-        } else {
-            const longlong2 a = *(const longlong2*)((const int64_t*)p + i0);
-            const longlong2 b = *(const longlong2*)((const int64_t*)p + i0 + 2);
-            v[0] = a.x; v[1] = a.y; v[2] = b.x; v[3] = b.y;
-        }
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            int64_t t = 0;
-            if (i0 + e < n) {
-                if (dt == TDP_I32) t = ((const int32_t*)p)[i0 + e];
-                else if (dt == TDP_I8) t = ((const int8_t*)p)[i0 + e];
-                else t = ((const int64_t*)p)[i0 + e];
-            }
-            v[e] = t;
-        }
-    }
+// Value E of an int8 or int32 column, and of any integer column.
+template <int E, bool WIDE>
+__device__ __forceinline__ int32_t sq_i32(const SqRaw<WIDE>& r, int dt) {
+    return dt == TDP_I8 ? (int32_t)(int8_t)(r.a[0] >> (8 * E)) : (int32_t)r.a[E];
 }
 
-// Dense group id of four rows; -1 for a row outside its key domain (which
-// raises the flag) or past the end.
-__device__ __forceinline__ void sq_gids(const SqDev& d, int64_t i0, int64_t gid[4], int32_t* flags) {
-    int64_t k0[4], k1[4] = {0, 0, 0, 0};
-    sq_load4i(d.kp[0], d.kdt[0], i0, d.n, k0);
-    if (d.n_keys > 1) sq_load4i(d.kp[1], d.kdt[1], i0, d.n, k1);
-    const int64_t c1 = d.n_keys > 1 ? d.card[1] : 1;
+template <int E>
+__device__ __forceinline__ int64_t sq_i64(const SqRaw<true>& r, int dt) {
+    if (dt != TDP_I64) return sq_i32<E>(r, dt);
+    const uint32_t lo = E < 2 ? r.a[E % 2 * 2] : r.b[E % 2 * 2], hi = E < 2 ? r.a[E % 2 * 2 + 1] : r.b[E % 2 * 2 + 1];
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+template <int E, bool WIDE>
+__device__ __forceinline__ float sq_float(const SqRaw<WIDE>& r, int dt) {
+    if (dt == TDP_F32) return __uint_as_float(r.a[E]);
+    if constexpr (WIDE)
+        if (dt == TDP_I64) return (float)sq_i64<E>(r, dt);
+    return (float)sq_i32<E>(r, dt);
+}
+
+template <bool WIDE>
+__device__ __forceinline__ void sq_floats(const SqRaw<WIDE>& r, int dt, float v[4]) {
+    v[0] = sq_float<0>(r, dt);
+    v[1] = sq_float<1>(r, dt);
+    v[2] = sq_float<2>(r, dt);
+    v[3] = sq_float<3>(r, dt);
+}
+
+// Every column of four rows (NJ: the conjuncts the kernel is built for).
+template <int NJ, bool WIDE>
+struct SqRows {
+    SqRaw<WIDE> key[2], a, pr[NJ];
+};
+
+template <int NJ, bool WIDE>
+__device__ __forceinline__ void sq_load_rows(const SqDev& d, int64_t i0, SqRows<NJ, WIDE>& r) {
+    const SqRaw<WIDE> none = {};
+    r.key[0] = sq_load<WIDE>(d.kp[0], d.kdt[0], i0, d.n);
+    r.key[1] = d.n_keys > 1 ? sq_load<WIDE>(d.kp[1], d.kdt[1], i0, d.n) : none;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int64_t u0 = k0[e] - d.lo[0];
-        const int64_t u1 = d.n_keys > 1 ? k1[e] - d.lo[1] : 0;
-        const bool in = u0 >= 0 && u0 < d.card[0] && u1 >= 0 && u1 < c1;
-        if (i0 + e >= d.n) {
-            gid[e] = -1;
-        } else if (!in) {
-            raise_flag(flags, TDP_FLAG_KEY_DOMAIN);
-            gid[e] = -1;
-        } else {
-            gid[e] = u0 * c1 + u1;
-        }
+    for (int j = 0; j < NJ; ++j) r.pr[j] = j < d.J ? sq_load<WIDE>(d.pr[j].p, d.pr[j].dt, i0, d.n) : none;
+    r.a = d.a ? sq_load<WIDE>(d.a, d.adt, i0, d.n) : none;
+}
+
+// Dense group id of a row (fewer than 2^16 groups); -1 outside its key domain
+// (which raises the flag) or past the end.  Without WIDE the keys have at most
+// 32 bits and domains that 32-bit differences decide.
+template <int E, int NJ, bool WIDE>
+__device__ __forceinline__ int32_t sq_gid(const SqDev& d, const SqRows<NJ, WIDE>& r, int64_t i0, uint32_t c1,
+                                          int32_t* flags) {
+    bool in;
+    uint32_t u0, u1 = 0;
+    if constexpr (WIDE) {
+        const int64_t w0 = sq_i64<E>(r.key[0], d.kdt[0]) - d.lo[0];
+        const int64_t w1 = d.n_keys > 1 ? sq_i64<E>(r.key[1], d.kdt[1]) - d.lo[1] : 0;
+        in = w0 >= 0 && w0 < d.card[0] && w1 >= 0 && w1 < (int64_t)c1;
+        u0 = (uint32_t)w0;
+        u1 = (uint32_t)w1;
+    } else {
+        u0 = (uint32_t)sq_i32<E>(r.key[0], d.kdt[0]) - (uint32_t)d.lo[0];
+        if (d.n_keys > 1) u1 = (uint32_t)sq_i32<E>(r.key[1], d.kdt[1]) - (uint32_t)d.lo[1];
+        in = u0 < (uint32_t)d.card[0] && u1 < c1;
     }
+    if (i0 + E >= d.n) return -1;
+    if (!in) {
+        raise_flag(flags, TDP_FLAG_KEY_DOMAIN);
+        return -1;
+    }
+    return (int32_t)(u0 * c1 + u1);
+}
+
+template <int NJ, bool WIDE>
+__device__ __forceinline__ void sq_gids(const SqDev& d, const SqRows<NJ, WIDE>& r, int64_t i0, int32_t gid[4],
+                                        int32_t* flags) {
+    const uint32_t c1 = d.n_keys > 1 ? (uint32_t)d.card[1] : 1u;
+    gid[0] = sq_gid<0>(d, r, i0, c1, flags);
+    gid[1] = sq_gid<1>(d, r, i0, c1, flags);
+    gid[2] = sq_gid<2>(d, r, i0, c1, flags);
+    gid[3] = sq_gid<3>(d, r, i0, c1, flags);
+}
+
+// sigma(z) and 1 - sigma(z) = sigma(-z), neither from a difference.
+__device__ __forceinline__ float logistic_pair(float z, float& other) {
+    const float t = __expf(-fabsf(z));
+    const float r = __builtin_amdgcn_rcpf(1.0f + t), tr = t * r;
+    other = z >= 0.0f ? tr : r;
+    return z >= 0.0f ? r : tr;
 }
 
 // Forward: each 1024-thread workgroup adds w * e of its rows into an LDS
 // table (one partial row per workgroup, reduced in fixed order afterwards),
 // or into the float64 accumulator when the table exceeds LDS.
-template <bool LDS>
+template <bool LDS, int NJ, bool WIDE>
 __global__ __launch_bounds__(kFwdThreads) void soft_query_fwd_kernel(SqDev d, int copies, SoftWs ws) {
-    extern __shared__ float s_tab[];
-    const int tab = (int)(threadIdx.x / kWave) % copies * d.G;  // this wave's copy of the table
+    extern __shared__ __attribute__((aligned(8))) float s_tab[];
+    const int tab = copy_of(copies) * d.G;
     if (LDS) {
         for (int j = threadIdx.x; j < copies * d.G; j += kFwdThreads) s_tab[j] = 0.0f;
         __syncthreads();
     }
-    float c[kSqMaxPreds], itau[kSqMaxPreds];
+    float c[NJ], itau[NJ];  // the sign of a conjunct's direction in itau
 #pragma unroll
-    for (int j = 0; j < kSqMaxPreds; ++j) {
+    for (int j = 0; j < NJ; ++j) {
         c[j] = j < d.J ? d.c[j] : 0.0f;
         const float t = j < d.J ? d.tau[j] : 1.0f;
         if (!(t > 0.0f && t < INFINITY) && threadIdx.x == 0) raise_flag(ws.flags, TDP_FLAG_BAD_PARAM);
-        itau[j] = 1.0f / t;
+        itau[j] = d.pr[j].s * (1.0f / t);
     }
     const int64_t stride = (int64_t)gridDim.x * kFwdThreads * 4;
     for (int64_t i0 = ((int64_t)blockIdx.x * kFwdThreads + threadIdx.x) * 4; i0 < d.n; i0 += stride) {
         float w[4] = {1.0f, 1.0f, 1.0f, 1.0f}, ev[4] = {1.0f, 1.0f, 1.0f, 1.0f};
-        int64_t gid[4];
-        sq_gids(d, i0, gid, ws.flags);
-        if (d.a) sq_load4f(d.a, d.adt, i0, d.n, ev);
+        int32_t gid[4];
+        SqRows<NJ, WIDE> rows;
+        sq_load_rows(d, i0, rows);
+        sq_gids(d, rows, i0, gid, ws.flags);
+        if (d.a) sq_floats(rows.a, d.adt, ev);
 #pragma unroll
-        for (int j = 0; j < kSqMaxPreds; ++j) {
+        for (int j = 0; j < NJ; ++j) {
             if (j >= d.J) break;
             float x[4];
-            sq_load4f(d.pr[j].p, d.pr[j].dt, i0, d.n, x);
+            sq_floats(rows.pr[j], d.pr[j].dt, x);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 float wd;
-                w[e] *= logistic_t(d.pr[j].s * (c[j] - x[e]) * itau[j], wd);
+                w[e] *= logistic_t((c[j] - x[e]) * itau[j], wd);
             }
         }
 #pragma unroll
@@ -742,14 +854,13 @@ __global__ __launch_bounds__(kFwdThreads) void soft_query_fwd_kernel(SqDev d, in
     }
     if (LDS) {
         __syncthreads();
-        for (int j = threadIdx.x; j < d.G; j += kFwdThreads)
-            ws.rows[(int64_t)blockIdx.x * d.G + j] = sum_copies(s_tab, d.G, copies, j);
+        sum_copies(s_tab, d.G, copies, ws.rows + (int64_t)blockIdx.x * d.G);
     }
 }
 
 // Backward: recomputes every factor; per-workgroup float64 partials of
-// dc[j] and dtau[j], and optionally de per row.
-template <bool LDS>
+// dc[j] and (TAU) dtau[j], and optionally de per row.
+template <bool LDS, int NJ, bool WIDE, bool TAU>
 __global__ __launch_bounds__(kSoftThreads) void soft_query_bwd_kernel(SqDev d, const float* __restrict__ dS,
                                                                       float* __restrict__ de, SoftWs ws) {
     extern __shared__ float s_ds[];
@@ -759,34 +870,32 @@ __global__ __launch_bounds__(kSoftThreads) void soft_query_bwd_kernel(SqDev d, c
         __syncthreads();
         tab = s_ds;
     }
-    float c[kSqMaxPreds], itau[kSqMaxPreds], pc[kSqMaxPreds], pt[kSqMaxPreds];
+    float c[NJ], itau[NJ], pc[NJ], pt[NJ];
 #pragma unroll
-    for (int j = 0; j < kSqMaxPreds; ++j) {
+    for (int j = 0; j < NJ; ++j) {
         c[j] = j < d.J ? d.c[j] : 0.0f;
-        itau[j] = 1.0f / (j < d.J ? d.tau[j] : 1.0f);
+        itau[j] = d.pr[j].s * (1.0f / (j < d.J ? d.tau[j] : 1.0f));
         pc[j] = pt[j] = 0.0f;
     }
     const int64_t stride = (int64_t)gridDim.x * kSoftThreads * 4;
     for (int64_t i0 = ((int64_t)blockIdx.x * kSoftThreads + threadIdx.x) * 4; i0 < d.n; i0 += stride) {
         float ev[4] = {1.0f, 1.0f, 1.0f, 1.0f};
-        int64_t gid[4];
-        sq_gids(d, i0, gid, nullptr);
-        if (d.a) sq_load4f(d.a, d.adt, i0, d.n, ev);
-        float z[kSqMaxPreds][4], om[kSqMaxPreds][4], w[4] = {1.0f, 1.0f, 1.0f, 1.0f};
+        int32_t gid[4];
+        SqRows<NJ, WIDE> rows;
+        sq_load_rows(d, i0, rows);
+        sq_gids(d, rows, i0, gid, nullptr);
+        if (d.a) sq_floats(rows.a, d.adt, ev);
+        float z[TAU ? NJ : 1][4], om[NJ][4], w[4] = {1.0f, 1.0f, 1.0f, 1.0f};
 #pragma unroll
-        for (int j = 0; j < kSqMaxPreds; ++j) {
+        for (int j = 0; j < NJ; ++j) {
             if (j >= d.J) break;
             float x[4];
-            sq_load4f(d.pr[j].p, d.pr[j].dt, i0, d.n, x);
+            sq_floats(rows.pr[j], d.pr[j].dt, x);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                float wd;
-                z[j][e] = d.pr[j].s * (c[j] - x[e]) * itau[j];
-                const float sg = logistic_t(z[j][e], wd);
-                // 1 - sigma(z): w (1 - w) / w where sigma >= 1/2, else 1 - sigma
-                // (neither form cancels on its side)
-                om[j][e] = z[j][e] >= 0.0f ? wd / sg : 1.0f - sg;
-                w[e] *= sg;
+                const float ze = (c[j] - x[e]) * itau[j];
+                w[e] *= logistic_pair(ze, om[j][e]);
+                if (TAU) z[j][e] = ze;
             }
         }
         float dv4[4];
@@ -796,11 +905,11 @@ __global__ __launch_bounds__(kSoftThreads) void soft_query_bwd_kernel(SqDev d, c
             dv4[e] = ds * w[e];
             const float t = ds * ev[e] * w[e];
 #pragma unroll
-            for (int j = 0; j < kSqMaxPreds; ++j) {
+            for (int j = 0; j < NJ; ++j) {
                 if (j >= d.J) break;
                 const float u = t * om[j][e] * itau[j];
-                pc[j] += u * d.pr[j].s;
-                pt[j] -= u * z[j][e];
+                pc[j] += u;
+                if (TAU) pt[j] -= u * d.pr[j].s * z[j][e];
             }
         }
         if (de) {
@@ -812,9 +921,12 @@ __global__ __launch_bounds__(kSoftThreads) void soft_query_bwd_kernel(SqDev d, c
             }
         }
     }
-    for (int j = 0; j < d.J; ++j) {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        if (j >= d.J) break;
         const double a = block_sum_f64((double)pc[j]);
         if (threadIdx.x == 0) ws.partq[(int64_t)j * kMaxGrid + blockIdx.x] = a;
+        if (!TAU) continue;
         const double b = block_sum_f64((double)pt[j]);
         if (threadIdx.x == 0) ws.partq[(int64_t)(kSqMaxPreds + j) * kMaxGrid + blockIdx.x] = b;
     }
@@ -1233,7 +1345,7 @@ extern "C" int tdp_soft_filter_groupby(const float* x, const float* v, const int
         const int64_t wgs = ceil_div(std::max<int64_t>(n, 1), (int64_t)kFwdThreads * 16);
         const int grid = (int)std::min<int64_t>(std::min<int64_t>(wgs, 256), kRowFloats / G);
         const int copies = table_copies(G);
-        soft_fg_fwd_kernel<true><<<grid, kFwdThreads, (size_t)copies * G * sizeof(float), stream>>>(
+        soft_fg_fwd_kernel<true><<<grid, kFwdThreads, fwd_lds(copies, G), stream>>>(
             x, v, g, n, d_c, 1.0f / tau, G, copies, s, S, T, d_loss, dS, d_status);
         launch_reduce(s, grid, G, S, T, d_loss, dS, d_status, stream);
     } else {
@@ -1258,12 +1370,15 @@ extern "C" int tdp_soft_filter_groupby_bwd(const float* x, const float* v, const
     if (rc) return rc;
     SoftWs s = soft_layout(ws, nullptr);
     const int grid = soft_grid(n, 16);
-    if (G <= kMaxLdsFloats)
-        soft_fg_bwd_kernel<true><<<grid, kSoftThreads, G * sizeof(float), stream>>>(x, v, g, n, d_c, 1.0f / tau, G, dS,
-                                                                                   dv, dx, s, d_dc);
+    auto run = [&](auto kernel, size_t lds) {
+        kernel<<<grid, kSoftThreads, lds, stream>>>(x, v, g, n, d_c, 1.0f / tau, G, dS, dv, dx, s, d_dc);
+    };
+    if (G > kMaxLdsFloats)
+        run(soft_fg_bwd_kernel<false, true>, 0);
+    else if (d_dtau)
+        run(soft_fg_bwd_kernel<true, true>, G * sizeof(float));
     else
-        soft_fg_bwd_kernel<false><<<grid, kSoftThreads, 0, stream>>>(x, v, g, n, d_c, 1.0f / tau, G, dS, dv, dx, s,
-                                                                     d_dc);
+        run(soft_fg_bwd_kernel<true, false>, G * sizeof(float));
     soft_scalar_finish_kernel<<<1, kSoftThreads, 0, stream>>>(s, grid, d_dc, d_dtau);
     return launch_status("tdp_soft_filter_groupby_bwd");
 }
@@ -1386,12 +1501,30 @@ int sq_prepare(const tdp_groupby_desc* d, const float* d_c, const float* d_tau, 
         q.card[i] = d->key_card[i];
     }
     q.G = (int)G;
+    // key - lo, taken mod 2^32, is below the cardinality exactly when it lies
+    // in the domain: no 32-bit key is 2^32 - 65536 or more below such a lo
+    for (int i = 0; i < d->n_keys; ++i)
+        q.wide |= d->key[i].dtype == TDP_I64 || d->key_lo[i] < INT32_MIN || d->key_lo[i] >= INT32_MAX - 65536;
+    for (int j = 0; j < J; ++j) q.wide |= q.pr[j].dt == TDP_I64;
     if (d->expr == TDP_EXPR_COL) {
         if ((rc = col_ok(d->a, true, "value column"))) return rc;
         q.a = d->a.data;
         q.adt = d->a.dtype;
+        q.wide |= q.adt == TDP_I64;
     }
     return TDP_OK;
+}
+
+// The kernels built for at most NJ conjuncts, 1, 2 or all four.
+template <int NJ, bool WIDE>
+void sq_fwd(const SqDev& q, int grid, int copies, const SoftWs& s, hipStream_t stream) {
+    soft_query_fwd_kernel<true, NJ, WIDE><<<grid, kFwdThreads, fwd_lds(copies, q.G), stream>>>(q, copies, s);
+}
+template <int NJ, bool WIDE>
+void sq_bwd(const SqDev& q, int grid, const float* dS, float* de, bool tau, const SoftWs& s, hipStream_t stream) {
+    const size_t lds = q.G * sizeof(float);
+    if (tau) soft_query_bwd_kernel<true, NJ, WIDE, true><<<grid, kSoftThreads, lds, stream>>>(q, dS, de, s);
+    else soft_query_bwd_kernel<true, NJ, WIDE, false><<<grid, kSoftThreads, lds, stream>>>(q, dS, de, s);
 }
 
 }  // namespace
@@ -1410,10 +1543,13 @@ extern "C" int tdp_soft_query(const tdp_groupby_desc* d, const float* d_c, const
         const int64_t wgs = ceil_div(std::max<int64_t>(q.n, 1), (int64_t)kFwdThreads * 16);
         const int grid = (int)std::min<int64_t>(std::min<int64_t>(wgs, 256), kRowFloats / q.G);
         const int copies = table_copies(q.G);
-        soft_query_fwd_kernel<true><<<grid, kFwdThreads, (size_t)copies * q.G * sizeof(float), stream>>>(q, copies, s);
+        if (q.wide) sq_fwd<kSqMaxPreds, true>(q, grid, copies, s, stream);
+        else if (q.J <= 1) sq_fwd<1, false>(q, grid, copies, s, stream);
+        else if (q.J == 2) sq_fwd<2, false>(q, grid, copies, s, stream);
+        else sq_fwd<kSqMaxPreds, false>(q, grid, copies, s, stream);
         launch_reduce(s, grid, q.G, S, T, d_loss, dS, d_status, stream);
     } else {
-        soft_query_fwd_kernel<false><<<(soft_grid(q.n, 16) + 3) / 4, kFwdThreads, 0, stream>>>(q, 1, s);
+        soft_query_fwd_kernel<false, kSqMaxPreds, true><<<(soft_grid(q.n, 16) + 3) / 4, kFwdThreads, 0, stream>>>(q, 1, s);
         launch_reduce(s, 0, q.G, S, T, d_loss, dS, d_status, stream);
     }
     return launch_status("tdp_soft_query");
@@ -1430,10 +1566,17 @@ extern "C" int tdp_soft_query_bwd(const tdp_groupby_desc* d, const float* d_c, c
     if ((rc = check_ws(ws, ws_bytes, "tdp_soft_query_bwd"))) return rc;
     SoftWs s = soft_layout(ws, nullptr);
     const int grid = soft_grid(q.n, 16);
-    if (q.G <= kMaxLdsFloats)
-        soft_query_bwd_kernel<true><<<grid, kSoftThreads, q.G * sizeof(float), stream>>>(q, dS, de, s);
+    const bool tau = d_dtau != nullptr;
+    if (q.G > kMaxLdsFloats)
+        soft_query_bwd_kernel<false, kSqMaxPreds, true, true><<<grid, kSoftThreads, 0, stream>>>(q, dS, de, s);
+    else if (q.wide)
+        sq_bwd<kSqMaxPreds, true>(q, grid, dS, de, tau, s, stream);
+    else if (q.J <= 1)
+        sq_bwd<1, false>(q, grid, dS, de, tau, s, stream);
+    else if (q.J == 2)
+        sq_bwd<2, false>(q, grid, dS, de, tau, s, stream);
     else
-        soft_query_bwd_kernel<false><<<grid, kSoftThreads, 0, stream>>>(q, dS, de, s);
+        sq_bwd<kSqMaxPreds, false>(q, grid, dS, de, tau, s, stream);
     if (q.J > 0) soft_query_finish_kernel<<<1, kSoftThreads, 0, stream>>>(s, grid, q.J, d_dc, d_dtau);
     return launch_status("tdp_soft_query_bwd");
 }
