@@ -2091,15 +2091,19 @@ __global__ __launch_bounds__(kRpProbeThreads) void rp_probe_kernel(GbDev d, RpDe
 constexpr int kPaggGroups = 4096;
 constexpr int kPaggShift = 12;
 constexpr int kPaggMaxParts = 256;
+constexpr int kPaggThreads = 1024;
+constexpr int kPaggTile = 4096;        // rows a workgroup orders at once (four per thread)
+constexpr int kPaggMaxWgs = 2 * kCUs;  // two workgroups per CU (63 KB of LDS each)
 
 struct PaggDev {
     uint16_t* rg;                  // [n_rec] group within its partition
     uint32_t* rc;                  // [n_rec] count the record adds
     unsigned long long* rv;        // [n_rec] value it adds
-    uint32_t* off;                 // [n_tiles][np] counts, then offsets within the partition
+    uint32_t* off;                 // [n_wg][np] counts, then offsets within the partition
     uint32_t* ptot;                // [np]
     uint32_t* pstart;              // [np + 1]
-    int64_t n_tiles;
+    int n_wg;                      // workgroups of the histogram and staging passes
+    int64_t wg_tiles;              // consecutive tiles of each
     int np;
 };
 
@@ -2139,54 +2143,54 @@ __device__ __forceinline__ void eval_gids(const GbDev& d, int64_t r0, bool qual[
 }
 
 template <class S>
-__global__ __launch_bounds__(kThreads) void pagg_hist_kernel(GbDev d, PaggDev pg) {
+__global__ __launch_bounds__(kPaggThreads) void pagg_hist_kernel(GbDev d, PaggDev pg) {
     __shared__ uint32_t h[kPaggMaxParts];
-    for (int64_t tile = blockIdx.x; tile < pg.n_tiles; tile += gridDim.x) {
-        for (int p = threadIdx.x; p < pg.np; p += kThreads) h[p] = 0;
-        __syncthreads();
+    if (threadIdx.x < kPaggMaxParts) h[threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t t1 = (int64_t)(blockIdx.x + 1) * pg.wg_tiles;
+    for (int64_t tile = (int64_t)blockIdx.x * pg.wg_tiles; tile < t1; ++tile) {
+        const int64_t r0 = tile * kPaggTile + (int64_t)threadIdx.x * 4;
+        if (r0 >= d.n_cand) break;
+        bool qual[4];
+        int64_t gid[4];
+        if (r0 + 4 <= d.n_cand)
+            eval_gids<S, true>(d, r0, qual, gid);
+        else
+            eval_gids<S, false>(d, r0, qual, gid);
 #pragma unroll
-        for (int j = 0; j < kStageTile / (kThreads * 4); ++j) {
-            const int64_t r0 = tile * kStageTile + j * kThreads * 4 + (int64_t)threadIdx.x * 4;
-            bool qual[4];
-            int64_t gid[4];
-            if (r0 + 4 <= d.n_cand)
-                eval_gids<S, true>(d, r0, qual, gid);
-            else
-                eval_gids<S, false>(d, r0, qual, gid);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (qual[e]) atomicAdd(&h[gid[e] >> kPaggShift], 1u);
-        }
-        __syncthreads();
-        for (int p = threadIdx.x; p < pg.np; p += kThreads) pg.off[tile * pg.np + p] = h[p];
+        for (int e = 0; e < 4; ++e)
+            if (qual[e]) atomicAdd(&h[gid[e] >> kPaggShift], 1u);
     }
+    __syncthreads();
+    if (threadIdx.x < pg.np) pg.off[(int64_t)blockIdx.x * pg.np + threadIdx.x] = h[threadIdx.x];
 }
 
-// Workgroup p: exclusive prefix of partition p's tile counts (in place) and
-// the partition's total.
-__global__ __launch_bounds__(256) void pagg_colscan_kernel(PaggDev pg) {
-    __shared__ uint32_t s_w[kThreads / kWave];
-    const int p = blockIdx.x, lane = lane_id(), wave = threadIdx.x / kWave;
-    const int64_t per = ceil_div(pg.n_tiles, (int64_t)kThreads);
-    const int64_t t0 = threadIdx.x * per, t1 = t0 + per < pg.n_tiles ? t0 + per : pg.n_tiles;
-    uint32_t sum = 0;
-    for (int64_t t = t0; t < t1; ++t) sum += pg.off[t * pg.np + p];
-    uint32_t incl = sum;
+// Per partition: exclusive prefix of the workgroups' counts (in place) and
+// the partition's total.  A workgroup takes 16 partitions; thread (slice,
+// column) the counts of at most 16 workgroups, all in flight together.
+constexpr int kPaggScanRows = kPaggMaxWgs / 64;
+__global__ __launch_bounds__(1024) void pagg_colscan_kernel(PaggDev pg) {
+    __shared__ uint32_t s_sum[64][16];
+    const int c = threadIdx.x & 15, sl = threadIdx.x >> 4, p = blockIdx.x * 16 + c;
+    uint32_t v[kPaggScanRows], sum = 0;
 #pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const uint32_t u = __shfl_up(incl, o, kWave);
-        if (lane >= o) incl += u;
+    for (int k = 0; k < kPaggScanRows; ++k) {
+        const int w = sl * kPaggScanRows + k;
+        v[k] = p < pg.np && w < pg.n_wg ? pg.off[(int64_t)w * pg.np + p] : 0u;
     }
-    if (lane == kWave - 1) s_w[wave] = incl;
+#pragma unroll
+    for (int k = 0; k < kPaggScanRows; ++k) sum += v[k];
+    s_sum[sl][c] = sum;
     __syncthreads();
-    uint32_t run = incl - sum;
-    for (int w = 0; w < wave; ++w) run += s_w[w];
-    for (int64_t t = t0; t < t1; ++t) {
-        const uint32_t v = pg.off[t * pg.np + p];
-        pg.off[t * pg.np + p] = run;
-        run += v;
+    uint32_t run = 0;
+    for (int q = 0; q < sl; ++q) run += s_sum[q][c];
+#pragma unroll
+    for (int k = 0; k < kPaggScanRows; ++k) {
+        const int w = sl * kPaggScanRows + k;
+        if (p < pg.np && w < pg.n_wg) pg.off[(int64_t)w * pg.np + p] = run;
+        run += v[k];
     }
-    if (threadIdx.x == kThreads - 1) pg.ptot[p] = run;
+    if (sl == 63 && p < pg.np) pg.ptot[p] = run;
 }
 
 // One workgroup: partition starts (exclusive prefix of the totals).
@@ -2208,67 +2212,81 @@ __global__ __launch_bounds__(256) void pagg_start_kernel(PaggDev pg) {
     if (p == pg.np - 1) pg.pstart[pg.np] = start + tot;
 }
 
+// A workgroup walks its run of tiles, four rows of a tile per thread: the
+// rows are evaluated (a join's random table line among it: with 256 threads of
+// sixteen rows each, eight waves per CU, those lines came at 37 per ns), ranked
+// in their partition by LDS counters, ordered by partition in LDS and written
+// behind the workgroup's records of the tiles before.
 template <int JM, class S>
-__global__ __launch_bounds__(kThreads) void pagg_stage_kernel(GbDev d, PaggDev pg) {
-    __shared__ unsigned long long s_val[kStageTile];
-    __shared__ uint32_t s_cnt[kStageTile];
-    __shared__ uint16_t s_grp[kStageTile];
-    __shared__ uint8_t s_part[kStageTile];
+__global__ __launch_bounds__(kPaggThreads) void pagg_stage_kernel(GbDev d, PaggDev pg) {
+    __shared__ unsigned long long s_val[kPaggTile];
+    __shared__ uint32_t s_cnt[kPaggTile];
+    __shared__ uint16_t s_grp[kPaggTile];
+    __shared__ uint8_t s_part[kPaggTile];
+    // counts of the tile, their exclusive prefix, and where the partition's next record goes less that prefix
     __shared__ uint32_t cnt[kPaggMaxParts], pref[kPaggMaxParts], base[kPaggMaxParts];
-    __shared__ uint32_t s_w[kThreads / kWave];
-    const int lane = lane_id(), wave = threadIdx.x / kWave;
-    for (int64_t tile = blockIdx.x; tile < pg.n_tiles; tile += gridDim.x) {
-        // this tile's records per partition, from the histogram pass
-        uint32_t c = 0;
-        const int p = threadIdx.x;
-        if (p < pg.np) {
-            cnt[p] = 0;
-            base[p] = pg.pstart[p] + pg.off[tile * pg.np + p];
-            c = (tile + 1 < pg.n_tiles ? pg.off[(tile + 1) * pg.np + p] : pg.ptot[p]) - pg.off[tile * pg.np + p];
-        }
-        uint32_t incl = c;
+    __shared__ uint32_t s_w[kPaggMaxParts / kWave];
+    const int lane = lane_id(), wave = threadIdx.x / kWave, p = threadIdx.x;
+    uint32_t next = 0;  // thread p < np: the partition's next record
+    if (p < pg.np) next = pg.pstart[p] + pg.off[(int64_t)blockIdx.x * pg.np + p];
+    if (p < kPaggMaxParts) cnt[p] = 0;
+    lds_barrier();
+    const int64_t t1 = (int64_t)(blockIdx.x + 1) * pg.wg_tiles;
+    for (int64_t tile = (int64_t)blockIdx.x * pg.wg_tiles; tile < t1 && tile * kPaggTile < d.n_cand; ++tile) {
+        const int64_t r0 = tile * kPaggTile + (int64_t)threadIdx.x * 4;
+        bool ok[4], qual[4];
+        int64_t gid[4];
+        unsigned long long val[4], rcnt[4];
+        if (r0 + 4 <= d.n_cand)
+            eval_rows<JM, false, S, true>(d, r0, ok, qual, gid, val, rcnt);
+        else
+            eval_rows<JM, false, S, false>(d, r0, ok, qual, gid, val, rcnt);
+        uint32_t rank[4];
 #pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const uint32_t u = __shfl_up(incl, o, kWave);
-            if (lane >= o) incl += u;
-        }
-        if (lane == kWave - 1) s_w[wave] = incl;
-        __syncthreads();
-        uint32_t ex = incl - c;
-        for (int w = 0; w < wave; ++w) ex += s_w[w];
-        if (p < pg.np) pref[p] = ex;
-        __syncthreads();
+        for (int e = 0; e < 4; ++e) rank[e] = qual[e] ? atomicAdd(&cnt[gid[e] >> kPaggShift], 1u) : 0u;
+        lds_barrier();
+        uint32_t c = 0, incl = 0;
+        if (p < kPaggMaxParts) {
+            c = cnt[p];
+            incl = c;
 #pragma unroll
-        for (int j = 0; j < kStageTile / (kThreads * 4); ++j) {
-            const int64_t r0 = tile * kStageTile + j * kThreads * 4 + (int64_t)threadIdx.x * 4;
-            bool ok[4], qual[4];
-            int64_t gid[4];
-            unsigned long long val[4], rcnt[4];
-            if (r0 + 4 <= d.n_cand)
-                eval_rows<JM, false, S, true>(d, r0, ok, qual, gid, val, rcnt);
-            else
-                eval_rows<JM, false, S, false>(d, r0, ok, qual, gid, val, rcnt);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (!qual[e]) continue;
-                const int part = (int)(gid[e] >> kPaggShift);
-                const uint32_t pos = pref[part] + atomicAdd(&cnt[part], 1u);
-                s_val[pos] = ok[e] ? val[e] : 0ull;
-                s_cnt[pos] = ok[e] ? (uint32_t)rcnt[e] : 0u;
-                s_grp[pos] = (uint16_t)(gid[e] & (kPaggGroups - 1));
-                s_part[pos] = (uint8_t)part;
+            for (int o = 1; o < kWave; o <<= 1) {
+                const uint32_t u = __shfl_up(incl, o, kWave);
+                if (lane >= o) incl += u;
             }
+            if (lane == kWave - 1) s_w[wave] = incl;
         }
-        __syncthreads();
-        const uint32_t total = pref[pg.np - 1] + cnt[pg.np - 1];
-        for (uint32_t i = threadIdx.x; i < total; i += kThreads) {
-            const int part = s_part[i];
-            const uint32_t at = base[part] + (i - pref[part]);
+        lds_barrier();
+        if (p < kPaggMaxParts) {
+            uint32_t ex = incl - c;
+            for (int w = 0; w < wave; ++w) ex += s_w[w];
+            pref[p] = ex;
+            base[p] = next - ex;
+            next += c;
+            cnt[p] = 0;
+        }
+        uint32_t total = 0;
+#pragma unroll
+        for (int w = 0; w < kPaggMaxParts / kWave; ++w) total += s_w[w];
+        lds_barrier();
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (!qual[e]) continue;
+            const int part = (int)(gid[e] >> kPaggShift);
+            const uint32_t pos = pref[part] + rank[e];
+            s_val[pos] = ok[e] ? val[e] : 0ull;
+            s_cnt[pos] = ok[e] ? (uint32_t)rcnt[e] : 0u;
+            s_grp[pos] = (uint16_t)(gid[e] & (kPaggGroups - 1));
+            s_part[pos] = (uint8_t)part;
+        }
+        lds_barrier();
+        for (uint32_t i = threadIdx.x; i < total; i += kPaggThreads) {
+            const uint32_t at = base[s_part[i]] + i;
             pg.rv[at] = s_val[i];
             pg.rc[at] = s_cnt[i];
             pg.rg[at] = s_grp[i];
         }
-        __syncthreads();
+        lds_barrier();
     }
 }
 
@@ -2731,7 +2749,6 @@ int make_plan(const tdp_groupby_desc* d, Plan& p) {
              p.G <= (int64_t)kPaggMaxParts * kPaggGroups && p.n_cand >= (1 << 20) && p.n_cand < (1ll << 31);
     if (p.pagg) {
         p.pagg_np = (int)ceil_div(p.G, kPaggGroups);
-        p.stage_tiles = ceil_div(p.n_cand, kStageTile);
     }
     p.lds_part = p.acc == ACC_LDS && !p.radix && !p.staged;
     if (p.lds_part) {
@@ -2792,10 +2809,11 @@ WsLayout layout(const Plan& p, const tdp_groupby_desc* d, void* ws) {
         pg.rg = wa.take<uint16_t>(nrec);
         pg.rc = wa.take<uint32_t>(nrec);
         pg.rv = wa.take<unsigned long long>(nrec);
-        pg.off = wa.take<uint32_t>((size_t)p.stage_tiles * p.pagg_np);
+        pg.wg_tiles = ceil_div(ceil_div(p.n_cand, kPaggTile), kPaggMaxWgs);
+        pg.n_wg = (int)ceil_div(ceil_div(p.n_cand, kPaggTile), pg.wg_tiles);
+        pg.off = wa.take<uint32_t>((size_t)pg.n_wg * p.pagg_np);
         pg.ptot = wa.take<uint32_t>(p.pagg_np);
         pg.pstart = wa.take<uint32_t>(p.pagg_np + 1);
-        pg.n_tiles = p.stage_tiles;
         pg.np = p.pagg_np;
     }
     if (p.radix) {
@@ -2894,11 +2912,10 @@ void launch_gb(const GbDev& g, bool sel, int sig, int nblocks, int threads, size
 
 template <int JM, class S>
 void launch_pagg_sig(const GbDev& g, const PaggDev& pg, hipStream_t s) {
-    const int nw = (int)std::min<int64_t>(pg.n_tiles, kStageGrid);
-    pagg_hist_kernel<S><<<nw, kThreads, 0, s>>>(g, pg);
-    pagg_colscan_kernel<<<pg.np, 256, 0, s>>>(pg);
+    pagg_hist_kernel<S><<<pg.n_wg, kPaggThreads, 0, s>>>(g, pg);
+    pagg_colscan_kernel<<<(unsigned)ceil_div(pg.np, 16), 1024, 0, s>>>(pg);
     pagg_start_kernel<<<1, 256, 0, s>>>(pg);
-    pagg_stage_kernel<JM, S><<<nw, kThreads, 0, s>>>(g, pg);
+    pagg_stage_kernel<JM, S><<<pg.n_wg, kPaggThreads, 0, s>>>(g, pg);
     pagg_reduce_kernel<<<pg.np, kPaggRedThreads, 0, s>>>(g, pg);
 }
 

@@ -95,3 +95,18 @@ def test_small_build_flags():
     # an empty build side, then a full one on a fresh plan
     r = Q.GroupbyQuery(n, [Q.Key(g, 0, 1)], join=(dev(np.zeros(0, np.int32)), pk, True))()
     assert r["k0"].numel() == 0
+
+
+# one tile a workgroup, the first second tile, a workgroup whose last tile is one row
+@pytest.mark.parametrize("n", [1 << 20, (512 << 12) + 1, (512 << 12) + 4097])
+@pytest.mark.parametrize("G", [2049, 4097, 1_000_000])
+def test_partitioned_aggregation_tiles(n, G):
+    rng = np.random.default_rng(n + G)
+    k = rng.integers(-5, G - 5, n).astype(np.int32)
+    v = rng.integers(-2**62, 2**62, n)
+    day = rng.integers(0, 100, n).astype(np.int32)
+    print("partitioned aggregation", n, G, flush=True)
+    got = Q.GroupbyQuery(n, [Q.Key(dev(k), -5, G)], expr=L.EXPR_COL, a=Q.Operand(dev(v)), pred=(dev(day), "<", 37))
+    want = oracle.query(n, keys=[(k, 0)], expr=oracle.EXPR_COL, a=(v, 0), pred=(day, "<", 37))
+    _same(got(), want, 1)
+    _same(got(), want, 1)
