@@ -1,16 +1,18 @@
 // Predicate scan with stream compaction (WHERE col <cmp> literal).
 //
-// One pass over the column.  Each workgroup (4 waves) takes the next tile of
+// One pass over the column.  Each workgroup (16 waves) takes the next tile of
 // 16384 candidates from an atomic ticket, so every tile it waits on belongs
 // to a workgroup that is already running.  Each lane reads 16 contiguous
-// bytes per round (fully coalesced), keeps the survivors of its 64 rows as a
+// bytes per round (fully coalesced), keeps the survivors of its 16 rows as a
 // bit mask in one register, and the wave counts them.  The tile's exclusive
-// offset comes from a decoupled look-back over per-tile (flag, value) words;
-// then each wave writes its survivors in order: a per-round exclusive prefix
-// of per-lane counts (one ballot per count bit) places each survivor's row id
-// in the wave's LDS stage, from which consecutive lanes store consecutive
-// dwords.
+// offset comes from a decoupled look-back over per-tile (flag, value) words,
+// 64 tiles at a time; then each wave writes its survivors in order: a per-round
+// exclusive prefix of per-lane counts (one ballot per count bit) places each
+// survivor's row id in the wave's LDS stage, which leaves as aligned 16-byte
+// stores.
+#include <limits>
 #include <mutex>
+#include <type_traits>
 
 #include "common.hpp"
 
@@ -22,17 +24,50 @@ constexpr uint64_t kFlagAgg = 1ull << 62;
 constexpr uint64_t kFlagPrefix = 2ull << 62;
 constexpr uint64_t kValMask = (1ull << 62) - 1;
 constexpr int kSpinLimit = 1 << 24;
-constexpr int kFilterThreads = 256;
+// A tile is 16384 rows, 16 per lane of 1024 threads: with 64 rows per lane of
+// 256 threads the 60M-row scan took 150 us (its tiles filled the chip not quite
+// twice, all reading, then all writing), with 32 of 512 134 us, so 128 us.
+constexpr int kFilterThreads = 1024;
+constexpr int kLaneRows = 16;
 
 template <typename T, bool SEL>
 struct FilterShape {
     static constexpr int VEC = SEL ? 4 : 16 / (int)sizeof(T);
-    static constexpr int ROUNDS = 64 / VEC;
+    static constexpr int ROUNDS = kLaneRows / VEC;
     static constexpr int WAVE_ROWS = ROUNDS * kWave * VEC;
     static constexpr int TILE_ROWS = (kFilterThreads / kWave) * WAVE_ROWS;
     static constexpr int CBITS = VEC == 16 ? 5 : (VEC == 4 ? 3 : 2);
-    static constexpr int UNROLL = ROUNDS <= 16 ? ROUNDS : 8;
+    using U = typename std::conditional<sizeof(T) == 8, uint64_t, uint32_t>::type;
 };
+
+// v <cmp> lit as one range test: (v - lo) mod 2^bits <= span, negated or not.
+// Columns of at most 32 bits compare in 32 bits (the literal beyond their
+// range makes the test constant).
+template <typename U>
+struct RangeTest {
+    U lo, span;
+    bool neg;
+    __device__ __forceinline__ bool operator()(U v) const { return (v - lo <= span) != neg; }
+};
+
+template <typename U>
+RangeTest<U> range_test(int cmp, int64_t lit) {
+    using I = typename std::make_signed<U>::type;
+    const int64_t min = std::numeric_limits<I>::min(), max = std::numeric_limits<I>::max();
+    const RangeTest<U> all{(U)(I)min, std::numeric_limits<U>::max(), false};
+    RangeTest<U> none = all;
+    none.neg = true;
+    auto range = [](int64_t lo, int64_t hi, bool neg) { return RangeTest<U>{(U)(I)lo, (U)((uint64_t)hi - (uint64_t)lo), neg}; };
+    const bool above = lit > max, below = lit < min;  // than every value
+    switch (cmp) {
+        case TDP_LT: return above ? all : below || lit == min ? none : range(min, lit - 1, false);
+        case TDP_LE: return above ? all : below ? none : range(min, lit, false);
+        case TDP_GT: return below ? all : above || lit == max ? none : range(lit + 1, max, false);
+        case TDP_GE: return below ? all : above ? none : range(lit, max, false);
+        case TDP_EQ: return above || below ? none : range(lit, lit, false);
+        default: return above || below ? all : range(lit, lit, true);
+    }
+}
 
 __global__ void filter_init_kernel(uint64_t* state, int64_t ntiles, uint32_t* ticket, int64_t* d_n_out,
                                    int32_t* d_status) {
@@ -46,59 +81,69 @@ __global__ void filter_init_kernel(uint64_t* state, int64_t ntiles, uint32_t* ti
 }
 
 // Exclusive offset of `tile` from the tiles before it; publishes its own
-// inclusive prefix.  Run by one thread.
+// inclusive prefix.  Run by one wave: lane l looks at the l-th tile before the
+// window's end, and the window is done once every tile down to the nearest
+// published prefix (or all 64) has its word.  One thread walking back a tile
+// at a time waited a memory latency for each of the up to 2000 tiles in
+// flight.
 __device__ uint64_t tile_lookback(uint64_t* state, uint32_t tile, uint64_t agg, int32_t* status) {
-    if (tile == 0) {
-        __hip_atomic_store(&state[0], kFlagPrefix | agg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return 0;
-    }
-    __hip_atomic_store(&state[tile], kFlagAgg | agg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int lane = lane_id();
+    if (lane == 0)
+        __hip_atomic_store(&state[tile], (tile == 0 ? kFlagPrefix : kFlagAgg) | agg, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    if (tile == 0) return 0;
     uint64_t excl = 0;
-    int64_t j = (int64_t)tile - 1;
-    while (true) {
-        uint64_t s = 0;
+    for (int64_t end = (int64_t)tile - 1;; end -= kWave) {
+        const int64_t j = end - lane;
+        uint64_t s = j < 0 ? kFlagPrefix : 0;  // nothing lies before tile 0
+        uint64_t prefix = 0;
         int spins = 0;
         while (true) {
-            s = __hip_atomic_load(&state[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (s >> 62) break;
+            if (!(s >> 62)) s = __hip_atomic_load(&state[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint64_t ready = ballot((s >> 62) != 0);
+            prefix = ballot((s & ~kValMask) == kFlagPrefix);
+            // the tiles up to the nearest prefix, or the whole window
+            const uint64_t want = prefix ? prefix ^ (prefix - 1) : ~0ull;
+            if ((ready & want) == want) break;
             if (++spins >= kSpinLimit) {
-                raise_flag(status, TDP_FLAG_SPIN);
-                s = kFlagPrefix;
+                if (lane == 0) raise_flag(status, TDP_FLAG_SPIN);
+                prefix = 1ull << 63;
                 break;
             }
             __builtin_amdgcn_s_sleep(1);
         }
-        excl += s & kValMask;
-        if ((s & ~kValMask) == kFlagPrefix) break;
-        --j;
+        const uint64_t want = prefix ? prefix ^ (prefix - 1) : ~0ull;
+        excl += wave_sum_u64((want >> lane) & 1 ? s & kValMask : 0ull);
+        if (prefix) break;
     }
-    __hip_atomic_store(&state[tile], kFlagPrefix | (excl + agg), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane == 0)
+        __hip_atomic_store(&state[tile], kFlagPrefix | (excl + agg), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return excl;
 }
 
 template <typename T, bool SEL>
 __global__ __launch_bounds__(kFilterThreads) void filter_kernel(const T* __restrict__ col,
                                                                const int32_t* __restrict__ sel, int64_t n_cand,
-                                                               int cmp, int64_t lit, int32_t* __restrict__ out,
-                                                               int64_t* d_n_out, uint64_t* state, uint32_t* ticket,
+                                                               RangeTest<typename FilterShape<T, SEL>::U> test,
+                                                               int32_t* __restrict__ out, int64_t* d_n_out, uint64_t* state, uint32_t* ticket,
                                                                uint32_t ntiles, int32_t* status) {
     using S = FilterShape<T, SEL>;
     constexpr int VEC = S::VEC;
     __shared__ uint32_t s_tile;
     __shared__ uint64_t s_wave[kFilterThreads / kWave];
     __shared__ uint64_t s_excl;
-    __shared__ int32_t s_stage[kFilterThreads / kWave][kWave * VEC];
+    __shared__ __attribute__((aligned(16))) int32_t s_stage[kFilterThreads / kWave][kWave * kLaneRows + 4];
+    using U = typename S::U;
     if (threadIdx.x == 0) s_tile = atomicAdd(ticket, 1u);
     __syncthreads();
     const uint32_t tile = s_tile;
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
     const int64_t wbase = (int64_t)tile * S::TILE_ROWS + (int64_t)wave * S::WAVE_ROWS;
 
-    // Pass 1: predicate bits of this lane's rows (all loads of up to 16
-    // rounds in flight together).
-    uint64_t bits = 0;
-    constexpr int kUnroll = S::UNROLL;
-#pragma unroll kUnroll
+    // Pass 1: predicate bits of this lane's rows (all rounds' loads in flight
+    // together).
+    uint32_t bits = 0;
+#pragma unroll
     for (int r = 0; r < S::ROUNDS; ++r) {
         const int64_t r0 = wbase + ((int64_t)r * kWave + lane) * VEC;
         uint32_t m = 0;
@@ -114,7 +159,7 @@ __global__ __launch_bounds__(kFilterThreads) void filter_kernel(const T* __restr
                 }
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    if (r0 + e < n_cand && cmp_i64((int64_t)col[rows[e]], cmp, lit)) m |= 1u << e;
+                    if (r0 + e < n_cand && test((U)col[rows[e]])) m |= 1u << e;
             } else {
                 T v[VEC];
                 if (r0 + VEC <= n_cand) {
@@ -126,50 +171,59 @@ __global__ __launch_bounds__(kFilterThreads) void filter_kernel(const T* __restr
                 }
 #pragma unroll
                 for (int e = 0; e < VEC; ++e)
-                    if (r0 + e < n_cand && cmp_i64((int64_t)v[e], cmp, lit)) m |= 1u << e;
+                    m |= (uint32_t)test((U)v[e]) << e;
+                if (r0 + VEC > n_cand) m &= (1u << (n_cand - r0)) - 1u;
             }
         }
-        bits |= (uint64_t)m << (r * VEC);
+        bits |= m << (r * VEC);
     }
-    const uint32_t wtot = wave_sum<uint32_t>((uint32_t)__popcll(bits));
+    const uint32_t wtot = wave_sum<uint32_t>((uint32_t)__popc(bits));
     if (lane == 0) s_wave[wave] = wtot;
     __syncthreads();
 
     // Tile offset by decoupled look-back.
-    if (threadIdx.x == 0) {
+    if (wave == 0) {
         uint64_t agg = 0;
         for (int w = 0; w < kFilterThreads / kWave; ++w) agg += s_wave[w];
-        uint64_t excl = tile_lookback(state, tile, agg, status);
-        s_excl = excl;
-        if (tile == ntiles - 1) *d_n_out = (int64_t)(excl + agg);
+        const uint64_t excl = tile_lookback(state, tile, agg, status);
+        if (lane == 0) {
+            s_excl = excl;
+            if (tile == ntiles - 1) *d_n_out = (int64_t)(excl + agg);
+        }
     }
     __syncthreads();
     uint64_t running = s_excl;
     for (int w = 0; w < wave; ++w) running += s_wave[w];
     if (wtot == 0) return;
 
-    // Pass 2: write survivors in candidate order, one round at a time through
-    // the wave's LDS stage (at most kWave * VEC ids per round).
+    // Pass 2: write survivors in candidate order through the wave's LDS stage,
+    // which starts as many ids past a 16-byte boundary as its destination does.
     int32_t* stage = s_stage[wave];
-    constexpr uint32_t kMask = (1u << VEC) - 1u;
+    constexpr uint32_t kMask = (uint32_t)((1ull << VEC) - 1);
+    int32_t* dst = out + running;
+    const uint32_t skew = (uint32_t)((uintptr_t)dst >> 2) & 3u;
+    uint32_t end = skew;
+#pragma unroll
     for (int r = 0; r < S::ROUNDS; ++r) {
-        const uint32_t m = (uint32_t)(bits >> (r * VEC)) & kMask;
+        const uint32_t m = (bits >> (r * VEC)) & kMask;
         uint32_t prefix, total;
         wave_count_scan<S::CBITS>((uint32_t)__popc(m), prefix, total);
-        if (total == 0) continue;
-        if (m) {
-            const int64_t r0 = wbase + ((int64_t)r * kWave + lane) * VEC;
-            uint32_t p = prefix;
+        const int64_t r0 = wbase + ((int64_t)r * kWave + lane) * VEC;
+        uint32_t p = end + prefix;
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) {
-                if ((m >> e) & 1u) stage[p++] = SEL ? sel[r0 + e] : (int32_t)(r0 + e);
-            }
+        for (int e = 0; e < VEC; ++e)
+            if ((m >> e) & 1u) stage[p++] = SEL ? sel[r0 + e] : (int32_t)(r0 + e);
+        end += total;
+    }
+    wave_lds_sync();
+    int32_t* base = dst - skew;
+    for (uint32_t i = lane * 4; i < end; i += kWave * 4) {
+        if (i >= skew && i + 4 <= end) {
+            *(int4*)&base[i] = *(const int4*)&stage[i];
+        } else {
+            for (uint32_t e = i; e < i + 4; ++e)
+                if (e >= skew && e < end) base[e] = stage[e];
         }
-        wave_lds_sync();
-        int32_t* dst = out + running;
-        for (uint32_t j = lane; j < total; j += kWave) dst[j] = stage[j];
-        wave_lds_sync();  // the stage is read before the next round fills it
-        running += total;
     }
 }
 
@@ -200,7 +254,8 @@ int launch_filter(const void* col, const int32_t* sel, int64_t n_cand, int cmp, 
     filter_init_kernel<<<ib, 256, 0, s>>>(state, ntiles, ticket, d_n_out, d_status);
     if (ntiles > 0) {
         filter_kernel<T, SEL><<<(uint32_t)ntiles, kFilterThreads, 0, s>>>(
-            (const T*)col, sel, n_cand, cmp, lit, out, d_n_out, state, ticket, (uint32_t)ntiles, d_status);
+            (const T*)col, sel, n_cand, range_test<typename S::U>(cmp, lit), out, d_n_out, state, ticket,
+            (uint32_t)ntiles, d_status);
     }
     return launch_status("tdp_filter");
 }

@@ -110,3 +110,39 @@ def test_partitioned_aggregation_tiles(n, G):
     want = oracle.query(n, keys=[(k, 0)], expr=oracle.EXPR_COL, a=(v, 0), pred=(day, "<", 37))
     _same(got(), want, 1)
     _same(got(), want, 1)
+
+
+# every comparison with literals at, beside and beyond the ends of the column's type, outputs that start at each
+# position of a 16-byte unit, tiles that end inside a lane's group of rows
+@pytest.mark.parametrize("dtype", [np.int8, np.int32, np.int64])
+@pytest.mark.parametrize("n", [3, 1023, 16_383, 49_153, 200_003])
+def test_filter_literals_and_alignment(dtype, n):
+    import ctypes as C
+    rng = np.random.default_rng(n)
+    info = np.iinfo(dtype)
+    col = rng.integers(info.min, info.max, n, dtype=dtype, endpoint=True)
+    col[rng.integers(0, n, 5)] = info.min
+    col[rng.integers(0, n, 5)] = info.max
+    d = dev(col)
+    lib, s = L.load(), L.stream_handle(torch.device(DEV))
+    ws = L.workspace(lib.tdp_filter_workspace_size(n), DEV)
+    tail = torch.zeros(2, dtype=torch.int64, device=DEV)
+    lits = [info.min, info.min + 1, 0, int(col[0]), info.max - 1, info.max]
+    if dtype != np.int64:
+        lits += [info.min - 1, info.max + 1, -2**63, 2**63 - 1]
+    print("filter", dtype.__name__, n, flush=True)
+    for k, op in enumerate(["<", "<=", ">", ">=", "==", "!="]):
+        for i, lit in enumerate(lits):
+            out = torch.full((n + 8,), -7, dtype=torch.int32, device=DEV)
+            dst = out[(k + i) % 4:]
+            c = L.col(d)
+            L.check("filter", lib.tdp_filter(C.byref(c), L.CMP[op], int(lit), None, 0, L.ptr(dst), n, L.ptr(tail),
+                                             L.ptr(tail[1:]), L.ptr(ws), ws.numel(), s))
+            m = int(tail[0])
+            x = col.astype(object)
+            want = np.nonzero({"<": x < lit, "<=": x <= lit, ">": x > lit, ">=": x >= lit, "==": x == lit,
+                               "!=": x != lit}[op].astype(bool))[0]
+            got = out.cpu().numpy()
+            at = (k + i) % 4
+            assert m == len(want) and np.array_equal(got[at:at + m], want), (op, lit)
+            assert np.all(got[:at] == -7) and np.all(got[at + m:] == -7), (op, lit)  # nothing beside the survivors
