@@ -1183,6 +1183,7 @@ constexpr int kRpProbeThreads = 512;   // threads of the probing kernel (two wor
 constexpr int kRpBktBits = 12;         // buckets of an LDS sub-table (4096 x 16 bytes)
 constexpr int kRpSlots = 8;            // 16-bit slots per bucket
 constexpr int kRpMaxTags = 20480;      // tag entries of one LDS sub-table, padding included (load <= 5/8)
+constexpr int kRpAccCopies = 128;      // LDS copies of the sums of few groups
 constexpr int kRpOvf = 256;            // tags that found both their buckets full
 constexpr uint32_t kRpItemRec = 65536;  // probe records per work item
 constexpr int64_t kRpTargetTags = 15000;   // build keys per partition the partition count aims at
@@ -1825,16 +1826,17 @@ __device__ __forceinline__ int rp_count(const uint4* bkt, const uint32_t* ovf, u
     return c;
 }
 
-// Whether any 16-bit half of the four words of a bucket equals e
-// (a half of w ^ (e, e) is zero; the borrow of a zero low half can only
-// mark the high half too, when the low half already matched).
+// Whether any 16-bit half of the four words of a bucket equals e: the
+// smallest of the eight halves of w ^ (e, e) is zero (the borrow of a zero low
+// half can only mark the high half too, when the low half already matched).
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ bool rp_has(const uint4& x, uint32_t e) {
     const uint32_t pat = e | (e << 16);
-    const uint32_t w[4] = {x.x ^ pat, x.y ^ pat, x.z ^ pat, x.w ^ pat};
-    uint32_t z = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) z |= (w[q] - 0x00010001u) & ~w[q];
-    return (z & 0x80008000u) != 0;
+    auto half = [&](uint32_t w) { return __builtin_bit_cast(u16x2, w ^ pat); };
+    const u16x2 m = __builtin_elementwise_min(__builtin_elementwise_min(half(x.x), half(x.y)),
+                                              __builtin_elementwise_min(half(x.z), half(x.w)));
+    const uint32_t z = __builtin_bit_cast(uint32_t, m);
+    return (((z - 0x00010001u) & ~z) & 0x80008000u) != 0;
 }
 
 // Whether every slot of a bucket is taken (a stored entry has bit 15 set).
@@ -1857,13 +1859,19 @@ __device__ __forceinline__ bool rp_full(const uint4& x) {
 // entry whose home bucket holds it too, or as a list entry found twice);
 // with several, every tag of the partition must be found once in its own
 // sub-table and nowhere else.  Workgroups beyond the last item leave at once
-// (register accumulators) or add nothing (LDS accumulators).
+// (register accumulators) or add nothing (LDS accumulators).  Bound by vector
+// instructions per record (60M records over 10M build keys: 191 us, of which
+// reading the records takes about 100; 222 us with sums selected among
+// registers and eight compares per bucket).
 template <int ACC>
 __global__ __launch_bounds__(kRpProbeThreads) void rp_probe_kernel(GbDev d, RpDev r, int check_dup) {
     __shared__ uint4 bkt[1 << kRpBktBits];   // 8 x uint16 per bucket
-    __shared__ uint32_t s_claim[(1 << kRpBktBits) / 2];  // 16-bit claim counters, two per word
+    // 16-bit claim counters, two per word, while the table is built; then the
+    // register accumulators' sums, [kRegMaxG][kRpAccCopies]
+    __shared__ __attribute__((aligned(8))) uint32_t s_claim[(1 << kRpBktBits) / 2];
     __shared__ uint32_t ovf[kRpOvf];
     __shared__ uint32_t n_ovf;
+    static_assert(kRegMaxG * kRpAccCopies * 2 <= (1 << kRpBktBits) / 2, "the sums fit the claims' words");
     __shared__ int s_p;
     extern __shared__ unsigned long long s_tab[];  // ACC_LDS: [G] sums then [G] counts
     unsigned long long rs[kRegMaxG];
@@ -1894,7 +1902,6 @@ __global__ __launch_bounds__(kRpProbeThreads) void rp_probe_kernel(GbDev d, RpDe
         const int fbits = r.tbits - kRpBktBits;
         const uint32_t fmask = (1u << fbits) - 1u, tmask = (1u << r.tbits) - 1u;
         const uint32_t skip = rp_skip(r), wide = rp_wide(r);
-        const int G = (int)d.G;
         for (uint32_t t0 = tb;; t0 += kRpMaxTags) {
             const uint32_t t1 = te - t0 > (uint32_t)kRpMaxTags ? t0 + kRpMaxTags : te;
             for (int i = threadIdx.x; i < (1 << kRpBktBits); i += kRpProbeThreads) bkt[i] = make_uint4(0, 0, 0, 0);
@@ -1992,10 +1999,20 @@ __global__ __launch_bounds__(kRpProbeThreads) void rp_probe_kernel(GbDev d, RpDe
                 }
             }
             // records: eight per thread and step (four 16-byte loads), the
-            // next step's loads issued before this step's lookups.  Counts
-            // of the register accumulators go to eight 8-bit fields of one
-            // word (at most kRpItemRec / kRpProbeThreads rows per thread and
-            // pass), unpacked after the pass.
+            // next step's loads issued before this step's lookups.  For up
+            // to kRegMaxG groups a value goes to its group's sum by one LDS
+            // add (each lane of a wave on a copy of its own: selecting
+            // among the groups' registers took a third of the kernel's
+            // vector instructions), a count to one of eight 8-bit fields of
+            // a word (at most kRpItemRec / kRpProbeThreads rows per thread
+            // and pass), unpacked after the pass.
+            unsigned long long* s_sum = (unsigned long long*)s_claim;
+            if (ACC == ACC_REG) {
+                __syncthreads();  // the claims are read no more
+                for (int i = threadIdx.x; i < kRegMaxG * kRpAccCopies; i += kRpProbeThreads) s_sum[i] = 0;
+                __syncthreads();
+            }
+            unsigned long long* my_sum = s_sum + (threadIdx.x & (kRpAccCopies - 1));
             static_assert(kRpItemRec / kRpProbeThreads < 256, "8-bit count fields");
             unsigned long long pcnt = 0;
             constexpr int kLd = 4;
@@ -2046,22 +2063,22 @@ __global__ __launch_bounds__(kRpProbeThreads) void rp_probe_kernel(GbDev d, RpDe
                                                                        : (unsigned long long)(int64_t)(int32_t)y[e];
                     if (ACC == ACC_REG) {
                         pcnt += hit ? 1ull << (8u * g) : 0ull;
-#pragma unroll
-                        for (int q = 0; q < kRegMaxG; ++q) {
-                            if (q >= G) break;
-                            rs[q] += hit && g == (uint32_t)q ? v : 0ull;
-                        }
+                        if (hit) atomicAdd(my_sum + g * kRpAccCopies, v);
                     } else if (hit) {
                         acc_row<ACC>(d, rs, rs, s_tab, (int64_t)g, v, 1ull);
                     }
                 }
               }
             }
+            __syncthreads();  // the sub-table is rebuilt next
             if (ACC == ACC_REG) {
 #pragma unroll
-                for (int q = 0; q < kRegMaxG; ++q) rc32[q] += (uint32_t)(pcnt >> (8 * q)) & 0xFFu;
+                for (int q = 0; q < kRegMaxG; ++q) {
+                    rc32[q] += (uint32_t)(pcnt >> (8 * q)) & 0xFFu;
+                    if (threadIdx.x < kRpAccCopies) rs[q] += s_sum[q * kRpAccCopies + threadIdx.x];
+                }
+                __syncthreads();  // the sums become claims again
             }
-            __syncthreads();  // the sub-table is rebuilt next
             if (t1 >= te) break;
         }
     }
