@@ -5,6 +5,8 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <limits>
+#include <type_traits>
 
 #include "../../include/tdp.h"
 
@@ -163,6 +165,35 @@ __device__ __forceinline__ void raise_flag(int32_t* status, int flag) {
 
 __device__ __forceinline__ uint64_t load_acquire_u64(const uint64_t* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// v <cmp> lit as one range test: (v - lo) mod 2^bits <= span, negated or not.
+// Columns of at most 32 bits compare in 32 bits (the literal beyond their
+// range makes the test constant).
+template <typename U>
+struct RangeTest {
+    U lo, span;
+    bool neg;
+    __device__ __forceinline__ bool operator()(U v) const { return (v - lo <= span) != neg; }
+};
+
+template <typename U>
+__host__ __device__ inline RangeTest<U> range_test(int cmp, int64_t lit) {
+    using I = typename std::make_signed<U>::type;
+    const int64_t min = std::numeric_limits<I>::min(), max = std::numeric_limits<I>::max();
+    const RangeTest<U> all{(U)(I)min, std::numeric_limits<U>::max(), false};
+    RangeTest<U> none = all;
+    none.neg = true;
+    auto range = [](int64_t lo, int64_t hi, bool neg) { return RangeTest<U>{(U)(I)lo, (U)((uint64_t)hi - (uint64_t)lo), neg}; };
+    const bool above = lit > max, below = lit < min;  // than every value
+    switch (cmp) {
+        case TDP_LT: return above ? all : below || lit == min ? none : range(min, lit - 1, false);
+        case TDP_LE: return above ? all : below ? none : range(min, lit, false);
+        case TDP_GT: return below ? all : above || lit == max ? none : range(lit + 1, max, false);
+        case TDP_GE: return below ? all : above ? none : range(lit, max, false);
+        case TDP_EQ: return above || below ? none : range(lit, lit, false);
+        default: return above || below ? all : range(lit, lit, true);
+    }
 }
 
 // Fill helpers (used instead of memset so that callers may capture calls

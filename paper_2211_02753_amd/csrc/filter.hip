@@ -10,9 +10,7 @@
 // exclusive prefix of per-lane counts (one ballot per count bit) places each
 // survivor's row id in the wave's LDS stage, which leaves as aligned 16-byte
 // stores.
-#include <limits>
 #include <mutex>
-#include <type_traits>
 
 #include "common.hpp"
 
@@ -39,35 +37,6 @@ struct FilterShape {
     static constexpr int CBITS = VEC == 16 ? 5 : (VEC == 4 ? 3 : 2);
     using U = typename std::conditional<sizeof(T) == 8, uint64_t, uint32_t>::type;
 };
-
-// v <cmp> lit as one range test: (v - lo) mod 2^bits <= span, negated or not.
-// Columns of at most 32 bits compare in 32 bits (the literal beyond their
-// range makes the test constant).
-template <typename U>
-struct RangeTest {
-    U lo, span;
-    bool neg;
-    __device__ __forceinline__ bool operator()(U v) const { return (v - lo <= span) != neg; }
-};
-
-template <typename U>
-RangeTest<U> range_test(int cmp, int64_t lit) {
-    using I = typename std::make_signed<U>::type;
-    const int64_t min = std::numeric_limits<I>::min(), max = std::numeric_limits<I>::max();
-    const RangeTest<U> all{(U)(I)min, std::numeric_limits<U>::max(), false};
-    RangeTest<U> none = all;
-    none.neg = true;
-    auto range = [](int64_t lo, int64_t hi, bool neg) { return RangeTest<U>{(U)(I)lo, (U)((uint64_t)hi - (uint64_t)lo), neg}; };
-    const bool above = lit > max, below = lit < min;  // than every value
-    switch (cmp) {
-        case TDP_LT: return above ? all : below || lit == min ? none : range(min, lit - 1, false);
-        case TDP_LE: return above ? all : below ? none : range(min, lit, false);
-        case TDP_GT: return below ? all : above || lit == max ? none : range(lit + 1, max, false);
-        case TDP_GE: return below ? all : above ? none : range(lit, max, false);
-        case TDP_EQ: return above || below ? none : range(lit, lit, false);
-        default: return above || below ? all : range(lit, lit, true);
-    }
-}
 
 __global__ void filter_init_kernel(uint64_t* state, int64_t ntiles, uint32_t* ticket, int64_t* d_n_out,
                                    int32_t* d_status) {

@@ -1465,104 +1465,164 @@ __global__ __launch_bounds__(kRpThreads) void rp_build_scatter_kernel(const int3
     }
 }
 
+// A column's values of four consecutive rows, held as loaded (widened where
+// they are used, so that nothing waits for the load before then): DT > 0 a
+// static type, 0 no column, -1 the type read at run time.
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+typedef int64_t i64x2 __attribute__((ext_vector_type(2)));
+template <int DT>
+struct Quad {
+    int64_t v[4];
+    __device__ __forceinline__ int64_t at(int e) const { return v[e]; }
+    template <bool FULL>
+    __device__ __forceinline__ void load(const ColDev& c, int64_t r0, int64_t n) {
+        const int64_t rows[4] = {r0, r0 + 1, r0 + 2, r0 + 3};
+        bool in[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) in[e] = FULL || r0 + e < n;
+        read4(c, true, r0, n, rows, rows, in, v);
+    }
+};
+template <>
+struct Quad<0> {
+    __device__ __forceinline__ int64_t at(int) const { return 0; }
+    template <bool FULL>
+    __device__ __forceinline__ void load(const ColDev&, int64_t, int64_t) {}
+};
+template <>
+struct Quad<TDP_I8> {
+    uint32_t v;
+    __device__ __forceinline__ int32_t at(int e) const { return (int32_t)(v << (24 - 8 * e)) >> 24; }
+    template <bool FULL>
+    __device__ __forceinline__ void load(const ColDev& c, int64_t r0, int64_t n) {
+        if (FULL) {
+            v = *(const uint32_t*)((const int8_t*)c.p + r0);
+        } else {
+            v = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v |= r0 + e < n ? (uint32_t)((const uint8_t*)c.p)[r0 + e] << (8 * e) : 0u;
+        }
+    }
+};
+template <>
+struct Quad<TDP_I32> {
+    i32x4 v;
+    __device__ __forceinline__ int32_t at(int e) const { return v[e]; }
+    template <bool FULL>
+    __device__ __forceinline__ void load(const ColDev& c, int64_t r0, int64_t n) {
+        const int32_t* p = (const int32_t*)c.p;
+        if (FULL) {
+            v = *(const i32x4*)(p + r0);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = r0 + e < n ? p[r0 + e] : 0;
+        }
+    }
+};
+template <>
+struct Quad<TDP_I64> {
+    i64x2 u, w;
+    __device__ __forceinline__ int64_t at(int e) const { return e < 2 ? u[e & 1] : w[e & 1]; }
+    template <bool FULL>
+    __device__ __forceinline__ void load(const ColDev& c, int64_t r0, int64_t n) {
+        const int64_t* p = (const int64_t*)c.p;
+        if (FULL) {
+            u = *(const i64x2*)(p + r0);
+            w = *(const i64x2*)(p + r0 + 2);
+        } else {
+            u[0] = r0 < n ? p[r0] : 0;
+            u[1] = r0 + 1 < n ? p[r0 + 1] : 0;
+            w[0] = r0 + 2 < n ? p[r0 + 2] : 0;
+            w[1] = r0 + 3 < n ? p[r0 + 3] : 0;
+        }
+    }
+};
+
 // The columns of four rows as loaded, so a workgroup can issue the loads
 // of its next sub-chunk before it orders the current one (the loads stay in
 // flight across its barriers).
-struct Raw4 {
-    int64_t pv[4], k0[4], k1[4], av[4], bv[4];
-    int32_t pk[4];
+template <class S>
+struct RpRaw {
+    Quad<S::P> pred;
+    Quad<S::K0> k0;
+    Quad<S::K1> k1;
+    Quad<S::A> a;
+    Quad<S::B> b;
+    Quad<TDP_I32> pk;
+
+    template <bool FULL>
+    __device__ __forceinline__ void load_as(const GbDev& d, int64_t r0) {
+        constexpr bool STATIC = S::P >= 0;
+        if (STATIC || d.has_pred) pred.template load<FULL>(d.pred, r0, d.n_cand);
+        k0.template load<FULL>(d.key[0], r0, d.n_cand);
+        if (STATIC || d.n_keys > 1) k1.template load<FULL>(d.key[1], r0, d.n_cand);
+        if (STATIC || d.expr != TDP_EXPR_NONE) a.template load<FULL>(d.a, r0, d.n_cand);
+        if (STATIC || d.expr == TDP_EXPR_MUL || d.expr == TDP_EXPR_MUL_CONST_SUB) b.template load<FULL>(d.b, r0, d.n_cand);
+        ColDev c{};
+        c.p = d.probe_key;
+        pk.template load<FULL>(c, r0, d.n_cand);
+    }
+    __device__ __forceinline__ void load(const GbDev& d, int64_t r0) {
+        if (r0 + 4 <= d.n_cand) load_as<true>(d, r0);
+        else load_as<false>(d, r0);
+    }
 };
 
-template <class S, bool FULL>
-__device__ __forceinline__ void rp_load4(const GbDev& d, int64_t r0, Raw4& w) {
-    constexpr bool STATIC = S::P >= 0;
-    const int64_t rows[4] = {r0, r0 + 1, r0 + 2, r0 + 3};
-    const int64_t brows[4] = {0, 0, 0, 0};
-    bool in[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) in[e] = FULL || r0 + e < d.n_cand;
-    const bool need_a = STATIC ? S::A > 0 : d.expr != TDP_EXPR_NONE;
-    const bool need_b = STATIC ? S::B > 0 : (d.expr == TDP_EXPR_MUL || d.expr == TDP_EXPR_MUL_CONST_SUB);
-    const bool has_pred = STATIC ? S::P > 0 : d.has_pred != 0;
-    const int n_keys = STATIC ? (S::K1 > 0 ? 2 : 1) : d.n_keys;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) w.pv[e] = w.k1[e] = w.av[e] = w.bv[e] = 0;
-    if constexpr (STATIC) {
-        if constexpr (S::P > 0) colread<S::P, TDP_SIDE_PROBE, false, FULL>(d.pred, r0, d.n_cand, rows, brows, in, w.pv);
-        colread<S::K0, TDP_SIDE_PROBE, false, FULL>(d.key[0], r0, d.n_cand, rows, brows, in, w.k0);
-        if constexpr (S::K1 > 0) colread<S::K1, TDP_SIDE_PROBE, false, FULL>(d.key[1], r0, d.n_cand, rows, brows, in, w.k1);
-        if constexpr (S::A > 0) colread<S::A, TDP_SIDE_PROBE, false, FULL>(d.a, r0, d.n_cand, rows, brows, in, w.av);
-        if constexpr (S::B > 0) colread<S::B, TDP_SIDE_PROBE, false, FULL>(d.b, r0, d.n_cand, rows, brows, in, w.bv);
-    } else {
-        if (has_pred) read4(d.pred, true, r0, d.n_cand, rows, brows, in, w.pv);
-        read4(d.key[0], true, r0, d.n_cand, rows, brows, in, w.k0);
-        if (n_keys > 1) read4(d.key[1], true, r0, d.n_cand, rows, brows, in, w.k1);
-        if (need_a) read4(d.a, true, r0, d.n_cand, rows, brows, in, w.av);
-        if (need_b) read4(d.b, true, r0, d.n_cand, rows, brows, in, w.bv);
-    }
-    if (FULL) {
-        const int4 q = *(const int4*)(d.probe_key + r0);
-        w.pk[0] = q.x; w.pk[1] = q.y; w.pk[2] = q.z; w.pk[3] = q.w;
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) w.pk[e] = in[e] ? d.probe_key[r0 + e] : 0;
-    }
+// What the rows of a scatter workgroup have in common, computed once.
+struct RpConst {
+    RangeTest<uint32_t> test;  // of a predicate column of at most 32 bits
+    bool k32;                  // the key domains lie in int32
+    int32_t lo0, lo1;
+    uint32_t cd0, cd1;
+    int64_t fx, fk;            // second factor of a product: (b ^ fx) + fk
+};
+
+template <class S>
+__device__ __forceinline__ RpConst rp_const(const GbDev& d) {
+    RpConst c;
+    c.test = range_test<uint32_t>(d.pred_cmp, d.pred_lit);
+    auto in32 = [&](int i) {
+        return d.lo[i] >= -((int64_t)1 << 31) && d.lo[i] + d.card[i] <= ((int64_t)1 << 31);
+    };
+    c.k32 = in32(0) && (d.n_keys < 2 || in32(1));
+    c.lo0 = (int32_t)d.lo[0];
+    c.lo1 = d.n_keys > 1 ? (int32_t)d.lo[1] : 0;
+    c.cd0 = (uint32_t)d.card[0];
+    c.cd1 = d.n_keys > 1 ? (uint32_t)d.card[1] : 1u;
+    c.fx = d.expr == TDP_EXPR_MUL ? 0 : -1;  // k - b = ~b + (k + 1)
+    c.fk = d.expr == TDP_EXPR_MUL ? 0 : (int64_t)((unsigned long long)d.k + 1ull);
+    return c;
 }
 
-// Qualification, group id and value of four loaded rows, as stage_eval
-// computes them (further conjuncts of the WHERE clause are read here).  The
-// same arithmetic runs in 32 bits where the operands provably fit: a 32- or
-// 8-bit predicate column against a literal that fits in int32, 8-bit group
-// keys with domain bounds within +-2^30 (their differences and the dense id,
-// at most 2^27, fit in int32), and a value a * (k - b) or a * b whose
-// factors fit in int32 on every row of the wave (one 32 x 32 -> 64-bit
-// multiply instead of a 64 x 64-bit one).
+// High half that differs from the sign of the low half: zero when v fits in int32.
+__device__ __forceinline__ uint32_t beyond32(int64_t v) {
+    return (uint32_t)((uint64_t)v >> 32) ^ (uint32_t)((int32_t)v >> 31);
+}
+
+// Records and partitions of the first nrow of four loaded rows: qualification,
+// group id and value as stage_eval computes them (further conjuncts of the
+// WHERE clause are read here).  The same arithmetic runs in 32 bits where the
+// operands provably fit: a predicate column of at most 32 bits (one range
+// test), keys of at most 32 bits whose domain lies in int32 (k - lo modulo 2^32
+// is below the domain's size only for the keys inside it), and a value
+// a * (k - b) or a * b whose factors fit in int32 on every row of the wave (one
+// 32 x 32 -> 64-bit multiply instead of a 64 x 64-bit one).
 template <class S>
-__device__ __forceinline__ void rp_finish4(const GbDev& d, int64_t r0, const Raw4& w, bool ok[4], uint16_t gid[4],
-                                           unsigned long long val[4]) {
+__device__ __forceinline__ void rp_records4(const GbDev& d, const RpDev& r, const RpConst& c, const RpRaw<S>& w,
+                                            int64_t r0, int nrow, uint2 rec[4], uint32_t part[4]) {
     constexpr bool STATIC = S::P >= 0;
-    constexpr bool NARROW_P = STATIC && (S::P == TDP_I32 || S::P == TDP_I8);
-    constexpr bool NARROW_K = STATIC && S::K0 == TDP_I8 && (S::K1 <= 0 || S::K1 == TDP_I8);
-    const bool has_pred = STATIC ? S::P > 0 : d.has_pred != 0;
+    constexpr bool NARROW_K = STATIC && (S::K0 == TDP_I8 || S::K0 == TDP_I32) &&
+                              (S::K1 == 0 || S::K1 == TDP_I8 || S::K1 == TDP_I32);
     const int n_keys = STATIC ? (S::K1 > 0 ? 2 : 1) : d.n_keys;
+    bool ok[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) ok[e] = r0 + e < d.n_cand;
-    if (has_pred) {
-        if (NARROW_P && d.pred_lit == (int64_t)(int32_t)d.pred_lit) {
-            const int32_t lit = (int32_t)d.pred_lit;
-            int32_t x[4];
+    for (int e = 0; e < 4; ++e) ok[e] = e < nrow;
+    if constexpr (S::P == TDP_I32 || S::P == TDP_I8) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) x[e] = (int32_t)w.pv[e];
-            switch (d.pred_cmp) {
-                case TDP_LT:
+        for (int e = 0; e < 4; ++e) ok[e] = ok[e] && c.test((uint32_t)w.pred.at(e));
+    } else if (STATIC ? S::P > 0 : d.has_pred != 0) {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) ok[e] = ok[e] && x[e] < lit;
-                    break;
-                case TDP_LE:
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) ok[e] = ok[e] && x[e] <= lit;
-                    break;
-                case TDP_GT:
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) ok[e] = ok[e] && x[e] > lit;
-                    break;
-                case TDP_GE:
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) ok[e] = ok[e] && x[e] >= lit;
-                    break;
-                case TDP_EQ:
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) ok[e] = ok[e] && x[e] == lit;
-                    break;
-                default:
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) ok[e] = ok[e] && x[e] != lit;
-                    break;
-            }
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) ok[e] = ok[e] && cmp_i64(w.pv[e], d.pred_cmp, d.pred_lit);
-        }
+        for (int e = 0; e < 4; ++e) ok[e] = ok[e] && cmp_i64(w.pred.at(e), d.pred_cmp, d.pred_lit);
     }
     if constexpr (S::MORE) {
         if (d.n_more > 0) {
@@ -1571,50 +1631,58 @@ __device__ __forceinline__ void rp_finish4(const GbDev& d, int64_t r0, const Raw
             more_preds4(d, true, r0, rows, brows, ok);
         }
     }
-    const int64_t c1 = n_keys > 1 ? d.card[1] : 1;
-    constexpr int64_t kB = (int64_t)1 << 30;
-    const bool k32 = NARROW_K && d.lo[0] >= -kB && d.lo[0] <= kB && (n_keys < 2 || (d.lo[1] >= -kB && d.lo[1] <= kB));
-    if (k32) {
-        const int32_t lo0 = (int32_t)d.lo[0], lo1 = n_keys > 1 ? (int32_t)d.lo[1] : 0;
-        const int32_t cd0 = (int32_t)d.card[0], cd1 = (int32_t)c1;  // the product of the domains is at most 2^27
-        bool bad = false;
+    uint32_t gid[4];
+    bool use[4], bad = false;
+    if (NARROW_K && c.k32) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const int32_t u0 = (int32_t)w.k0[e] - lo0;
-            const int32_t u1 = n_keys > 1 ? (int32_t)w.k1[e] - lo1 : 0;
-            const bool in = u0 >= 0 && u0 < cd0 && u1 >= 0 && u1 < cd1;
+            const uint32_t u0 = (uint32_t)w.k0.at(e) - (uint32_t)c.lo0;
+            const uint32_t u1 = n_keys > 1 ? (uint32_t)w.k1.at(e) - (uint32_t)c.lo1 : 0u;
+            const bool in = u0 < c.cd0 && (n_keys < 2 || u1 < c.cd1);
             bad = bad || (ok[e] && !in);
-            gid[e] = in ? (uint16_t)(u0 * cd1 + u1) : kSkipGid;
+            use[e] = ok[e] && in;
+            gid[e] = n_keys > 1 ? u0 * c.cd1 + u1 : u0;
         }
-        if (bad) raise_flag(d.status, TDP_FLAG_KEY_DOMAIN);
     } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const int64_t u0 = w.k0[e] - d.lo[0];
-            const int64_t u1 = n_keys > 1 ? w.k1[e] - d.lo[1] : 0;
-            const bool in = u0 >= 0 && u0 < d.card[0] && u1 >= 0 && u1 < c1;
-            if (ok[e] && !in) raise_flag(d.status, TDP_FLAG_KEY_DOMAIN);
-            gid[e] = in ? (uint16_t)(u0 * c1 + u1) : kSkipGid;
+            const uint64_t u0 = (uint64_t)w.k0.at(e) - (uint64_t)d.lo[0];
+            const uint64_t u1 = n_keys > 1 ? (uint64_t)w.k1.at(e) - (uint64_t)d.lo[1] : 0ull;
+            const bool in = u0 < (uint64_t)d.card[0] && u1 < c.cd1;
+            bad = bad || (ok[e] && !in);
+            use[e] = ok[e] && in;
+            gid[e] = (uint32_t)u0 * c.cd1 + (uint32_t)u1;
         }
     }
+    if (bad) raise_flag(d.status, TDP_FLAG_KEY_DOMAIN);
+    unsigned long long val[4];
     if (d.expr == TDP_EXPR_MUL || d.expr == TDP_EXPR_MUL_CONST_SUB) {
         int64_t f2[4];
-        bool fit = true;
+        uint32_t far = 0;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            f2[e] = d.expr == TDP_EXPR_MUL ? w.bv[e] : (int64_t)((unsigned long long)d.k - (unsigned long long)w.bv[e]);
-            fit = fit && w.av[e] == (int64_t)(int32_t)w.av[e] && f2[e] == (int64_t)(int32_t)f2[e];
+            f2[e] = (int64_t)((uint64_t)(w.b.at(e) ^ c.fx) + (uint64_t)c.fk);
+            far |= beyond32(w.a.at(e)) | beyond32(f2[e]);
         }
-        if (ballot(!fit) == 0) {
+        if (ballot(far != 0) == 0) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) val[e] = (unsigned long long)((int64_t)(int32_t)w.av[e] * (int64_t)(int32_t)f2[e]);
+            for (int e = 0; e < 4; ++e) val[e] = (unsigned long long)((int64_t)(int32_t)w.a.at(e) * (int64_t)(int32_t)f2[e]);
         } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) val[e] = (unsigned long long)w.av[e] * (unsigned long long)f2[e];
+            for (int e = 0; e < 4; ++e) val[e] = (unsigned long long)w.a.at(e) * (unsigned long long)f2[e];
         }
     } else {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) val[e] = d.expr == TDP_EXPR_COL ? (unsigned long long)w.av[e] : 0ull;
+        for (int e = 0; e < 4; ++e) val[e] = d.expr == TDP_EXPR_COL ? (unsigned long long)w.a.at(e) : 0ull;
+    }
+    const uint32_t tmask = (1u << r.tbits) - 1u, skip = rp_skip(r), wide = rp_wide(r);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const uint32_t h = hash32((uint32_t)w.pk.at(e));
+        const bool fits = beyond32((int64_t)val[e]) == 0;
+        const uint32_t fld = !use[e] ? skip : (fits ? gid[e] : (wide | gid[e]));
+        rec[e] = make_uint2((fld << r.tbits) | (h & tmask), fits ? (uint32_t)val[e] : (uint32_t)r0 + e);
+        part[e] = h >> r.tbits;
     }
 }
 
@@ -1628,7 +1696,11 @@ __device__ __forceinline__ void rp_finish4(const GbDev& d, int64_t r0, const Raw
 // each); the rest, fewer than kRpUnit records, is carried to the next
 // sub-chunk.  Every row in range takes a record, so the regions the
 // histogram sized are filled exactly.  Each thread owns kPpt consecutive
-// partitions in the per-partition steps.
+// partitions in the per-partition steps.  Bound by memory and by the barriers
+// of the one workgroup that fits on a CU (60M rows of 26 bytes into 1024
+// partitions: 502 us, 2.0 GB of which take 417 us at the rate of a copy; 535 us
+// with the columns widened as they were loaded, which waited for each).  Chunks of
+// 8192 rows, or fewer LDS reads per unit, made no difference or were slower.
 template <class S>
 __global__ __launch_bounds__(kRpScatThreads) void rp_scatter_kernel(GbDev d, RpDev r) {
     constexpr int kMaxP = 1 << kRpMaxPBits;
@@ -1648,7 +1720,7 @@ __global__ __launch_bounds__(kRpScatThreads) void rp_scatter_kernel(GbDev d, RpD
     __shared__ uint32_t s_units;
     const int64_t w = blockIdx.x;
     const int tid = threadIdx.x, P = r.P;
-    const uint32_t tmask = (1u << r.tbits) - 1u, skip = rp_skip(r), wide = rp_wide(r);
+    const uint32_t skip = rp_skip(r);
     for (int q = tid; q < P; q += kRpScatThreads) {
         s_cur[q] = r.pstart[q] + r.pcnt[w * P + q];
         s_end[q] = r.pstart[q] + (w + 1 < r.pw ? r.pcnt[(w + 1) * P + q] : r.ptot[q]);
@@ -1657,49 +1729,20 @@ __global__ __launch_bounds__(kRpScatThreads) void rp_scatter_kernel(GbDev d, RpD
     }
     lds_barrier();
     const int64_t lo = w * r.prows, hi = lo + r.prows < d.n_cand ? lo + r.prows : d.n_cand;
-    Raw4 raw;
-    if (lo < hi) {
-        const int64_t r0 = lo + (int64_t)tid * 4;
-        if (r0 + 4 <= d.n_cand) rp_load4<S, true>(d, r0, raw);
-        else rp_load4<S, false>(d, r0, raw);
-    }
+    const RpConst cn = rp_const<S>(d);
+    RpRaw<S> raw;
+    if (lo + (int64_t)tid * 4 < hi) raw.load(d, lo + (int64_t)tid * 4);
     for (int64_t base = lo; base < hi; base += kRpSub) {
         const int64_t r0 = base + (int64_t)tid * 4;
-        bool ok[4];
-        int32_t pk[4];
-        uint16_t gid[4];
-        unsigned long long val[4];
-        rp_finish4<S>(d, r0, raw, ok, gid, val);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) pk[e] = raw.pk[e];
-        // the next sub-chunk's loads, in flight while this one is ordered
-        {
-            const int64_t n0 = r0 + kRpSub;
-            if (base + kRpSub < hi) {
-                if (n0 + 4 <= d.n_cand) rp_load4<S, true>(d, n0, raw);
-                else rp_load4<S, false>(d, n0, raw);
-            }
-        }
+        const int nrow = (int)(hi - r0 < 4 ? hi - r0 : 4);  // none if not above 0
         uint2 rec[4];
         uint32_t rank[4];
+        rp_records4<S>(d, r, cn, raw, r0, nrow, rec, rank);
+        // the next sub-chunk's loads, in flight while this one is ordered
+        if (r0 + kRpSub < hi) raw.load(d, r0 + kRpSub);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const uint32_t h = hash32((uint32_t)pk[e]);
-            const int64_t v = (int64_t)val[e];
-            const bool use = ok[e] && gid[e] != kSkipGid;
-            const bool fits = v == (int64_t)(int32_t)v;
-            const uint32_t fld = !use ? skip : (fits ? (uint32_t)gid[e] : (wide | (uint32_t)gid[e]));
-            rec[e] = make_uint2((fld << r.tbits) | (h & tmask), fits ? (uint32_t)(int32_t)v : (uint32_t)(r0 + e));
-            rank[e] = h >> r.tbits;
-        }
-        if (r0 + 4 <= d.n_cand) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) rank[e] |= atomicAdd(&s_cnt[rank[e]], 1u) << 16;
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (r0 + e < d.n_cand) rank[e] |= atomicAdd(&s_cnt[rank[e]], 1u) << 16;
-        }
+        for (int e = 0; e < 4; ++e)
+            if (e < nrow) rank[e] |= atomicAdd(&s_cnt[rank[e]], 1u) << 16;
         lds_barrier();
         {
             // the thread's kPpt partitions: record counts (at most kRpSub) in
@@ -1731,7 +1774,7 @@ __global__ __launch_bounds__(kRpScatThreads) void rp_scatter_kernel(GbDev d, RpD
         lds_barrier();
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            if (r0 + e < d.n_cand) {
+            if (e < nrow) {
                 const uint32_t q = rank[e] & 0xFFFFu;
                 s_rec[s_pref[q] + (rank[e] >> 16)] = rec[e];
             }
@@ -1860,7 +1903,7 @@ __device__ __forceinline__ bool rp_full(const uint4& x) {
 // with several, every tag of the partition must be found once in its own
 // sub-table and nowhere else.  Workgroups beyond the last item leave at once
 // (register accumulators) or add nothing (LDS accumulators).  Bound by vector
-// instructions per record (60M records over 10M build keys: 191 us, of which
+// instructions per record (60M records over 15M build keys: 191 us, of which
 // reading the records takes about 100; 222 us with sums selected among
 // registers and eight compares per bucket).
 template <int ACC>
