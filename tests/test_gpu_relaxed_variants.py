@@ -106,3 +106,26 @@ def test_llp_variants(n, F, classes, bag):
     dz = np.abs(p * (dp - (p * dp).sum(1, keepdims=True)))
     assert np.all(np.abs(gW.cpu().numpy() - wW) <= 1e-5 * (dz.T @ np.abs(X.astype(np.float64))) + 1e-30)
     assert np.all(np.abs(gb.cpu().numpy() - wb) <= 1e-5 * dz.sum(0) + 1e-30)
+
+
+# workgroups of the segmented probability counts: one group per wave, groups looped over at the least and the most
+# workgroups and between
+@pytest.mark.parametrize("groups,rows", [(16_383, 1), (16_385, 3), (150_001, 11), (131_073, 65)])
+def test_segmented_counts_over_many_groups(groups, rows):
+    from paper_2211_02753_amd import soft
+    rng = np.random.default_rng(groups)
+    lens = rng.integers(max(rows - 1, 1), rows + 2, groups)
+    seg = np.concatenate([[0], np.cumsum(lens)]).astype(I64)
+    n = int(seg[-1])
+    p, q = rng.random((n, 2), dtype=F32), rng.random((n, 1), dtype=F32)
+    d = rng.standard_normal((groups, 2)).astype(F32)
+    print("segmented counts", groups, n, flush=True)
+    st = torch.zeros(1, dtype=torch.int32, device=DEV)
+    S = soft.soft_pe_groupby(t(p), t(q), t(seg), groups, status=st).cpu().numpy().reshape(groups, 2)
+    assert int(st.item()) == 0
+    want = np.add.reduceat(p.astype(np.float64) * q, seg[:-1], axis=0)
+    assert np.all(np.abs(S - want) <= 1e-5 * want + 1e-30)
+    dp, dq = soft.soft_pe_groupby_bwd(t(p), t(q), t(seg), t(d.reshape(groups, 2, 1)))
+    dr = np.repeat(d.astype(np.float64), lens, axis=0)
+    assert np.all(np.abs(dp.cpu().numpy() - dr * q) <= 1e-6 * np.abs(dr * q))
+    assert np.all(np.abs(dq.cpu().numpy()[:, 0] - (dr * p).sum(1)) <= 1e-6 * np.abs(dr * p).sum(1))
