@@ -12,11 +12,12 @@
 // slow dimension) and what the epilogue does (bias + ReLU and a bf16 store;
 // a ReLU mask; a float32 atomic add for split-K products).  Layer shapes
 // that this tile fits badly have kernels of their own: a single input
-// channel (nine products per output) runs on the vector ALUs, and the
-// 32 -> 64 channel convolution's forward and input gradient keep the
-// weights in registers and stream 16-pixel blocks through the 16x16x32
-// instruction.  bf16 values are stored as uint16_t bit patterns and rounded
-// from float32 to nearest even.
+// channel (nine products per output) runs on the vector ALUs; convolutions
+// between 32 and 64 channels work on bands of rows in LDS (conv_lds.hip), and
+// where their rows are too wide for that, or for other channel counts of the
+// same form, the forward and input gradient keep the weights in registers and
+// stream 16-pixel blocks through the 16x16x32 instruction.  bf16 values are
+// stored as uint16_t bit patterns and rounded from float32 to nearest even.
 #include "conv_lds.hpp"
 
 namespace tdp {

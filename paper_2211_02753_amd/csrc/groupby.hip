@@ -5,13 +5,16 @@
 // declared domains and adds the row's value and count to a privatised
 // accumulator:
 //   G <= 8     per-thread registers, wave-reduced, one partial per workgroup;
-//   G <= 2048  an LDS table per workgroup, merged with global atomics;
+//   G <= 2048  an LDS table per workgroup (copies of it per lane for few
+//              groups), written as the workgroup's partial row;
 //   larger     global atomics on the dense table, or (many rows, at most
 //              2^20 groups) the partitioned aggregation further below.
-// For G <= 4096 one workgroup of a separate finishing kernel emits the
-// non-empty groups in key order; larger tables are emitted by three small
-// kernels (count per chunk, scan of the chunk counts, write), or ranked by
-// the top-k kernels.  The opt-in partitioned (staged) probe is also below.
+// Partial rows of up to 256 groups are summed and the non-empty groups emitted
+// in key order by one workgroup of a separate finishing kernel; more groups are
+// summed into the dense table first, which one workgroup emits up to G = 4096,
+// and three small kernels beyond (count per chunk, scan of the chunk counts,
+// write), or the top-k kernels rank.  The radix-partitioned probe of large
+// keys-only joins and the opt-in staged probe are also below.
 #include <type_traits>
 
 #include "hash.hpp"

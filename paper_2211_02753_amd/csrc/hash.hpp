@@ -187,8 +187,8 @@ constexpr int kAggScatThreads = 1024;    // threads of the unit scatter (one gro
 constexpr int64_t kDirectRows = 65536;
 
 struct BuildScratch {
-    bool direct = false;
-    bool lds = false;
+    bool direct = false;    // one workgroup per probing block reads all build keys (no histograms, no bucketing)
+    bool lds = false;       // bucketed, then built block by block in LDS
     int nw = 0;             // histogram workgroups
     int threads = 0;        // threads of a histogram / scatter workgroup (512 or 1024)
     int64_t chunk = 0;      // build rows per histogram workgroup
