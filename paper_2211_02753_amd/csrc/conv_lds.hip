@@ -248,6 +248,11 @@ constexpr int kWgThreads = 512;
 constexpr int kWgMaxOut = 576;  // output pixels of a band
 constexpr int kWgMaxIn = 624;   // input pixels under one tap row
 constexpr int kWgShares = 85;   // 3 x 85 workgroups: one per CU (133 KB of LDS each)
+// Each share adds its sums to all of dw with atomics, so small batches take few:
+// both gradients of 6 and 12 images of 26 x 26 take 15.2 and 17.0 us with shares
+// of 288 pixels or more, 15.0 and 17.7 with 192, 16.0 and 20.8 with 96, 19.3 and
+// 19.9 with as many shares as there are rows and CUs for.
+constexpr int kWgMinPx = 288;
 
 __device__ __forceinline__ s16x4 read_tr(const unsigned char* p) {
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p);
@@ -434,7 +439,9 @@ bool conv_dgrad_64_32(const uint16_t* dy, const uint16_t* w, const uint16_t* mas
 bool conv_wgrad_32_64(const uint16_t* x, const uint16_t* dy, int B, int H, int W, float* dw, float* db, hipStream_t s) {
     const int most = std::min(std::min(kWgMaxOut / (W - 2), kWgMaxIn / W), H - 2);
     if (most < 1) return false;
-    const int rows = band_rows(H - 2, most, B, kWgShares), bands = (int)ceil_div(H - 2, rows);
+    // bands: as many as there are shares of at least kWgMinPx pixels, one each
+    const int64_t shares_px = std::min<int64_t>(std::max<int64_t>((int64_t)B * (H - 2) * (W - 2) / kWgMinPx, 1), kWgShares);
+    const int rows = band_rows(H - 2, most, 1, (int)std::max<int64_t>(shares_px / B, 1)), bands = (int)ceil_div(H - 2, rows);
     const int64_t items = (int64_t)B * bands;
     if (items >= (1ll << 30)) return false;
     // every share the same number of bands, but for the last ones
