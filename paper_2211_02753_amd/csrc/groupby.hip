@@ -623,7 +623,7 @@ __device__ void merge_and_finish(const GbDev& d, const unsigned long long* rs, c
         }
     } else if (ACC == ACC_LDS) {
         __syncthreads();
-        for (int64_t g = threadIdx.x; g < d.G; g += kThreads) {
+        for (int64_t g = threadIdx.x; g < d.G; g += blockDim.x) {
             const unsigned long long c = s_tab[d.G + g];
             if (c) {
                 atomicAdd(&d.gtab[2 * g], s_tab[g]);

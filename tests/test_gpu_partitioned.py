@@ -155,3 +155,37 @@ def test_auto_takes_the_partitioned_probe_for_large_keys_only_joins():
     assert L.stage_time()[1] == 0
     L.stage_timer(L.STAGE_NONE)
     _cmp(got, _scaled_o(f2, d2))
+
+
+@pytest.mark.parametrize("groups", [255, 256, 257, 300, 511])
+def test_partitioned_probe_groups_around_the_accumulators_workgroup(groups):
+    """The LDS accumulators of a probing workgroup are added to the result once
+    per group, also where there are fewer (or more) groups than its threads or
+    than 256: sums and counts bit for bit."""
+    n, nb = 200_003, 20_011
+    rng = np.random.default_rng(groups)
+    pk = rng.permutation(np.arange(nb, dtype=np.int32))
+    fk = rng.integers(0, nb + 500, n).astype(np.int32)  # some miss
+    gk = rng.integers(0, groups, n).astype(np.int32)
+    val = rng.integers(-2**35, 2**35, n)
+    print(f"partitioned probe: {groups} groups", flush=True)
+    got = Q.GroupbyQuery(n, [Q.Key(t(gk), 0, groups)], expr=L.EXPR_COL, a=Q.Operand(t(val)),
+                         join=(t(pk), t(fk), True), strategy=L.PROBE_PARTITIONED)()
+    _cmp(got, oracle.query(n, keys=[(gk, 0)], expr=oracle.EXPR_COL, a=(val, 0), join=(fk, pk)))
+
+
+def test_auto_partitioned_probe_with_more_than_256_groups():
+    n, nb, groups = (1 << 22) + 1001, (1 << 18) + 17, 301
+    rng = np.random.default_rng(8)
+    pk = rng.permutation(np.arange(nb, dtype=np.int32))
+    fk = rng.integers(0, nb, n).astype(np.int32)
+    gk = rng.integers(0, groups, n).astype(np.int32)
+    val = rng.integers(-1000, 1000, n)
+    q = Q.GroupbyQuery(n, [Q.Key(t(gk), 0, groups)], expr=L.EXPR_COL, a=Q.Operand(t(val)), join=(t(pk), t(fk), True))
+    L.stage_timer(L.STAGE_RP_SCATTER)
+    got = q()
+    torch.cuda.synchronize()
+    launches = L.stage_time()[1]
+    L.stage_timer(L.STAGE_NONE)
+    assert launches == 1  # the call does take the partitioned probe
+    _cmp(got, oracle.query(n, keys=[(gk, 0)], expr=oracle.EXPR_COL, a=(val, 0), join=(fk, pk)))
