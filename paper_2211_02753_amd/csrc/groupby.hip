@@ -1585,7 +1585,7 @@ __device__ __forceinline__ RpConst rp_const(const GbDev& d) {
     RpConst c;
     c.test = range_test<uint32_t>(d.pred_cmp, d.pred_lit);
     auto in32 = [&](int i) {
-        return d.lo[i] >= -((int64_t)1 << 31) && d.lo[i] + d.card[i] <= ((int64_t)1 << 31);
+        return d.lo[i] >= -((int64_t)1 << 31) && d.lo[i] <= ((int64_t)1 << 31) - d.card[i];  // lo + card may overflow
     };
     c.k32 = in32(0) && (d.n_keys < 2 || in32(1));
     c.lo0 = (int32_t)d.lo[0];

@@ -63,3 +63,24 @@ def test_key_domains_at_the_ends_of_int32(lo, wide_key):
     out[n // 3] = I32.max if lo < 0 else I32.min  # outside the domain, also modulo 2**32
     with pytest.raises(Exception, match="KEY_DOMAIN"):
         q(out)()
+
+
+@pytest.mark.parametrize("lo", [2**63 - 7, 2**63 - 100, -2**63])
+@pytest.mark.parametrize("second", [False, True])
+def test_key_domains_at_the_ends_of_int64(lo, second):
+    """A domain next to the end of int64 holds no int32 key, whatever its
+    bounds are modulo 2^32 or 2^64."""
+    n, card = 20_003, 7
+    rng = np.random.default_rng(6)
+    pk = np.arange(3000, dtype=np.int32)
+    fk = rng.integers(0, 3000, n).astype(np.int32)
+    low = lo & 0xFFFFFFFF  # the domain's first key modulo 2^32
+    key = np.full(n, low - (1 << 32) if low >> 31 else low, np.int64).astype(np.int32)
+    key += rng.integers(0, card, n).astype(np.int32) if lo < 0 or lo == 2**63 - 7 else 0
+    keys = [Q.Key(t(key), lo, card)]
+    if second:
+        keys = [Q.Key(t(np.zeros(n, np.int8)), 0, 1)] + keys
+    q = Q.GroupbyQuery(n, keys, expr=L.EXPR_COL, a=Q.Operand(t(fk.astype(np.int64))), join=(t(pk), t(fk), True),
+                       strategy=L.PROBE_PARTITIONED)
+    with pytest.raises(Exception, match="KEY_DOMAIN"):
+        q()
