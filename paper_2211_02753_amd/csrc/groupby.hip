@@ -2140,34 +2140,41 @@ __global__ __launch_bounds__(kRpProbeThreads) void rp_probe_kernel(GbDev d, RpDe
 // the global table costs two device-scope atomics per row, resolved beyond
 // the XCD caches.  Instead, rows are partitioned by group range (kPaggGroups
 // groups per partition) and each partition is reduced in LDS:
-//   1. pagg_hist_kernel: per tile of kStageTile rows, the qualifying rows of
-//      each partition (predicate and probe-side group keys only);
-//   2. pagg_colscan_kernel / pagg_start_kernel: offsets per (tile,
+//   1. pagg_hist_kernel: per tile of kPaggTile rows and per workgroup (an even
+//      run of tiles), the qualifying rows of each partition (predicate and
+//      probe-side group keys only);
+//   2. pagg_colscan_kernel / pagg_start_kernel: offsets per (workgroup,
 //      partition), partition-major;
 //   3. pagg_stage_kernel: evaluates every row once (predicate, join probe,
 //      group id, value) and writes a (group within partition, count, value)
 //      record for each qualifying row, sorted by partition in LDS so each
-//      tile writes contiguous runs; a row that finds no join partner leaves
-//      a record with count and value 0;
+//      tile writes contiguous runs, behind those of the workgroup's earlier
+//      tiles; a row that finds no join partner leaves a record with count
+//      and value 0;
 //   4. pagg_reduce_kernel: one workgroup per partition adds its records into
 //      an LDS table and writes the partition's slice of the dense table.
 constexpr int kPaggGroups = 4096;
 constexpr int kPaggShift = 12;
 constexpr int kPaggMaxParts = 256;
-constexpr int kPaggThreads = 1024;
-constexpr int kPaggTile = 4096;        // rows a workgroup orders at once (four per thread)
-constexpr int kPaggMaxWgs = 2 * kCUs;  // two workgroups per CU (63 KB of LDS each)
+constexpr int kPaggHistThreads = 1024;
+constexpr int kPaggThreads = 512;      // threads of a staging workgroup
+constexpr int kPaggTile = 4096;        // rows a workgroup orders at once
+constexpr int kPaggMaxWgs = 2 * kCUs;  // two workgroups per CU (64 KB of LDS each)
 
 struct PaggDev {
     uint16_t* rg;                  // [n_rec] group within its partition
     uint32_t* rc;                  // [n_rec] count the record adds
     unsigned long long* rv;        // [n_rec] value it adds
+    uint16_t* tcnt;                // [n_tiles][np] qualifying rows of each tile
     uint32_t* off;                 // [n_wg][np] counts, then offsets within the partition
     uint32_t* ptot;                // [np]
     uint32_t* pstart;              // [np + 1]
+    int64_t n_tiles;
     int n_wg;                      // workgroups of the histogram and staging passes
-    int64_t wg_tiles;              // consecutive tiles of each
     int np;
+
+    // First tile of workgroup w: the workgroups' runs differ by one tile at most.
+    __device__ __forceinline__ int64_t first_tile(int w) const { return n_tiles * w / n_wg; }
 };
 
 // Predicate and probe-side group keys of four rows: which rows qualify and
@@ -2206,26 +2213,36 @@ __device__ __forceinline__ void eval_gids(const GbDev& d, int64_t r0, bool qual[
 }
 
 template <class S>
-__global__ __launch_bounds__(kPaggThreads) void pagg_hist_kernel(GbDev d, PaggDev pg) {
-    __shared__ uint32_t h[kPaggMaxParts];
-    if (threadIdx.x < kPaggMaxParts) h[threadIdx.x] = 0;
-    __syncthreads();
-    const int64_t t1 = (int64_t)(blockIdx.x + 1) * pg.wg_tiles;
-    for (int64_t tile = (int64_t)blockIdx.x * pg.wg_tiles; tile < t1; ++tile) {
+__global__ __launch_bounds__(kPaggHistThreads) void pagg_hist_kernel(GbDev d, PaggDev pg) {
+    __shared__ uint32_t h[2][kPaggMaxParts];  // of this tile and of the next
+    const int p = threadIdx.x;
+    if (p < kPaggMaxParts) h[0][p] = h[1][p] = 0;
+    lds_barrier();
+    uint32_t sum = 0;  // thread p < np: the workgroup's rows of partition p
+    const int64_t t1 = pg.first_tile(blockIdx.x + 1);
+    int cur = 0;
+    for (int64_t tile = pg.first_tile(blockIdx.x); tile < t1; ++tile, cur ^= 1) {
         const int64_t r0 = tile * kPaggTile + (int64_t)threadIdx.x * 4;
-        if (r0 >= d.n_cand) break;
-        bool qual[4];
-        int64_t gid[4];
-        if (r0 + 4 <= d.n_cand)
-            eval_gids<S, true>(d, r0, qual, gid);
-        else
-            eval_gids<S, false>(d, r0, qual, gid);
+        if (r0 < d.n_cand) {
+            bool qual[4];
+            int64_t gid[4];
+            if (r0 + 4 <= d.n_cand)
+                eval_gids<S, true>(d, r0, qual, gid);
+            else
+                eval_gids<S, false>(d, r0, qual, gid);
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (qual[e]) atomicAdd(&h[gid[e] >> kPaggShift], 1u);
+            for (int e = 0; e < 4; ++e)
+                if (qual[e]) atomicAdd(&h[cur][gid[e] >> kPaggShift], 1u);
+        }
+        lds_barrier();
+        if (p < pg.np) {
+            const uint32_t c = h[cur][p];
+            h[cur][p] = 0;  // counted again two tiles on, behind the next tile's barrier
+            sum += c;
+            pg.tcnt[tile * pg.np + p] = (uint16_t)c;
+        }
     }
-    __syncthreads();
-    if (threadIdx.x < pg.np) pg.off[(int64_t)blockIdx.x * pg.np + threadIdx.x] = h[threadIdx.x];
+    if (p < pg.np) pg.off[(int64_t)blockIdx.x * pg.np + p] = sum;
 }
 
 // Per partition: exclusive prefix of the workgroups' counts (in place) and
@@ -2275,43 +2292,33 @@ __global__ __launch_bounds__(256) void pagg_start_kernel(PaggDev pg) {
     if (p == pg.np - 1) pg.pstart[pg.np] = start + tot;
 }
 
-// A workgroup walks its run of tiles, four rows of a tile per thread: the
-// rows are evaluated (a join's random table line among it: with 256 threads of
-// sixteen rows each, eight waves per CU, those lines came at 37 per ns), ranked
-// in their partition by LDS counters, ordered by partition in LDS and written
-// behind the workgroup's records of the tiles before.
+// A workgroup walks its run of tiles: the rows are evaluated (a join's random
+// table line among it), placed by partition in LDS and written behind the
+// workgroup's records of the tiles before.  Bound by those lines, one of 128
+// bytes per row of the 64 MB aggregate table (20M rows, 2M keys: 493 us).  512
+// threads place eight rows each, four at a time, so that the lines of some
+// wave are always on their way: 541 us with 256 threads of sixteen rows, 565
+// with 1024 of four, whose waves all wait for their lines, then all order.
 template <int JM, class S>
 __global__ __launch_bounds__(kPaggThreads) void pagg_stage_kernel(GbDev d, PaggDev pg) {
     __shared__ unsigned long long s_val[kPaggTile];
     __shared__ uint32_t s_cnt[kPaggTile];
     __shared__ uint16_t s_grp[kPaggTile];
     __shared__ uint8_t s_part[kPaggTile];
-    // counts of the tile, their exclusive prefix, and where the partition's next record goes less that prefix
-    __shared__ uint32_t cnt[kPaggMaxParts], pref[kPaggMaxParts], base[kPaggMaxParts];
+    // the partition's next place in the tile, and where its next record goes less its first place there
+    __shared__ uint32_t place[kPaggMaxParts], base[kPaggMaxParts];
     __shared__ uint32_t s_w[kPaggMaxParts / kWave];
     const int lane = lane_id(), wave = threadIdx.x / kWave, p = threadIdx.x;
-    uint32_t next = 0;  // thread p < np: the partition's next record
-    if (p < pg.np) next = pg.pstart[p] + pg.off[(int64_t)blockIdx.x * pg.np + p];
-    if (p < kPaggMaxParts) cnt[p] = 0;
-    lds_barrier();
-    const int64_t t1 = (int64_t)(blockIdx.x + 1) * pg.wg_tiles;
-    for (int64_t tile = (int64_t)blockIdx.x * pg.wg_tiles; tile < t1 && tile * kPaggTile < d.n_cand; ++tile) {
-        const int64_t r0 = tile * kPaggTile + (int64_t)threadIdx.x * 4;
-        bool ok[4], qual[4];
-        int64_t gid[4];
-        unsigned long long val[4], rcnt[4];
-        if (r0 + 4 <= d.n_cand)
-            eval_rows<JM, false, S, true>(d, r0, ok, qual, gid, val, rcnt);
-        else
-            eval_rows<JM, false, S, false>(d, r0, ok, qual, gid, val, rcnt);
-        uint32_t rank[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) rank[e] = qual[e] ? atomicAdd(&cnt[gid[e] >> kPaggShift], 1u) : 0u;
-        lds_barrier();
-        uint32_t c = 0, incl = 0;
+    const int64_t t1 = pg.first_tile(blockIdx.x + 1);
+    int64_t tile = pg.first_tile(blockIdx.x);
+    uint32_t next = 0, c = 0;  // thread p < np: the partition's next record, and its rows of the tile
+    if (p < pg.np) {
+        next = pg.pstart[p] + pg.off[(int64_t)blockIdx.x * pg.np + p];
+        c = pg.tcnt[tile * pg.np + p];
+    }
+    for (; tile < t1; ++tile) {
+        uint32_t incl = c;
         if (p < kPaggMaxParts) {
-            c = cnt[p];
-            incl = c;
 #pragma unroll
             for (int o = 1; o < kWave; o <<= 1) {
                 const uint32_t u = __shfl_up(incl, o, kWave);
@@ -2323,24 +2330,35 @@ __global__ __launch_bounds__(kPaggThreads) void pagg_stage_kernel(GbDev d, PaggD
         if (p < kPaggMaxParts) {
             uint32_t ex = incl - c;
             for (int w = 0; w < wave; ++w) ex += s_w[w];
-            pref[p] = ex;
+            place[p] = ex;
             base[p] = next - ex;
             next += c;
-            cnt[p] = 0;
         }
         uint32_t total = 0;
 #pragma unroll
         for (int w = 0; w < kPaggMaxParts / kWave; ++w) total += s_w[w];
+        if (p < pg.np && tile + 1 < t1) c = pg.tcnt[(tile + 1) * pg.np + p];
         lds_barrier();
+#pragma unroll 1
+        for (int j = 0; j < kPaggTile / (kPaggThreads * 4); ++j) {
+            const int64_t r0 = tile * kPaggTile + ((int64_t)j * kPaggThreads + threadIdx.x) * 4;
+            bool ok[4], qual[4];
+            int64_t gid[4];
+            unsigned long long val[4], rcnt[4];
+            if (r0 + 4 <= d.n_cand)
+                eval_rows<JM, false, S, true>(d, r0, ok, qual, gid, val, rcnt);
+            else
+                eval_rows<JM, false, S, false>(d, r0, ok, qual, gid, val, rcnt);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            if (!qual[e]) continue;
-            const int part = (int)(gid[e] >> kPaggShift);
-            const uint32_t pos = pref[part] + rank[e];
-            s_val[pos] = ok[e] ? val[e] : 0ull;
-            s_cnt[pos] = ok[e] ? (uint32_t)rcnt[e] : 0u;
-            s_grp[pos] = (uint16_t)(gid[e] & (kPaggGroups - 1));
-            s_part[pos] = (uint8_t)part;
+            for (int e = 0; e < 4; ++e) {
+                if (!qual[e]) continue;
+                const int part = (int)(gid[e] >> kPaggShift);
+                const uint32_t pos = atomicAdd(&place[part], 1u);
+                s_val[pos] = ok[e] ? val[e] : 0ull;
+                s_cnt[pos] = ok[e] ? (uint32_t)rcnt[e] : 0u;
+                s_grp[pos] = (uint16_t)(gid[e] & (kPaggGroups - 1));
+                s_part[pos] = (uint8_t)part;
+            }
         }
         lds_barrier();
         for (uint32_t i = threadIdx.x; i < total; i += kPaggThreads) {
@@ -2872,8 +2890,9 @@ WsLayout layout(const Plan& p, const tdp_groupby_desc* d, void* ws) {
         pg.rg = wa.take<uint16_t>(nrec);
         pg.rc = wa.take<uint32_t>(nrec);
         pg.rv = wa.take<unsigned long long>(nrec);
-        pg.wg_tiles = ceil_div(ceil_div(p.n_cand, kPaggTile), kPaggMaxWgs);
-        pg.n_wg = (int)ceil_div(ceil_div(p.n_cand, kPaggTile), pg.wg_tiles);
+        pg.n_tiles = ceil_div(p.n_cand, kPaggTile);
+        pg.n_wg = (int)std::min<int64_t>(pg.n_tiles, kPaggMaxWgs);
+        pg.tcnt = wa.take<uint16_t>((size_t)pg.n_tiles * p.pagg_np);
         pg.off = wa.take<uint32_t>((size_t)pg.n_wg * p.pagg_np);
         pg.ptot = wa.take<uint32_t>(p.pagg_np);
         pg.pstart = wa.take<uint32_t>(p.pagg_np + 1);
@@ -2975,7 +2994,7 @@ void launch_gb(const GbDev& g, bool sel, int sig, int nblocks, int threads, size
 
 template <int JM, class S>
 void launch_pagg_sig(const GbDev& g, const PaggDev& pg, hipStream_t s) {
-    pagg_hist_kernel<S><<<pg.n_wg, kPaggThreads, 0, s>>>(g, pg);
+    pagg_hist_kernel<S><<<pg.n_wg, kPaggHistThreads, 0, s>>>(g, pg);
     pagg_colscan_kernel<<<(unsigned)ceil_div(pg.np, 16), 1024, 0, s>>>(pg);
     pagg_start_kernel<<<1, 256, 0, s>>>(pg);
     pagg_stage_kernel<JM, S><<<pg.n_wg, kPaggThreads, 0, s>>>(g, pg);

@@ -112,6 +112,23 @@ def test_partitioned_aggregation_tiles(n, G):
     _same(got(), want, 1)
 
 
+# whole tiles of one partition, runs of tiles that differ by one between workgroups, a join whose rows partly miss
+@pytest.mark.parametrize("tiles", [511, 513, 700])
+def test_partitioned_aggregation_sorted_groups(tiles):
+    n, G = (tiles << 12) - 5, 70_001
+    rng = np.random.default_rng(tiles)
+    k = np.sort(rng.integers(0, G, n)).astype(np.int32)
+    bk = np.repeat(np.arange(0, 3000, dtype=np.int32), 3)
+    bv, pk = rng.integers(-2**40, 2**40, len(bk)), rng.integers(0, 4000, n).astype(np.int32)
+    v = rng.integers(-2**20, 2**20, n)
+    print("partitioned aggregation, sorted groups", tiles, flush=True)
+    got = Q.GroupbyQuery(n, [Q.Key(dev(k), 0, G)], expr=L.EXPR_MUL, a=Q.Operand(dev(v)),
+                         b=Q.Operand(dev(bv), L.BUILD), join=(dev(bk), dev(pk), False))
+    want = oracle.query(n, keys=[(k, 0)], expr=oracle.EXPR_MUL, a=(v, 0), b=(bv, 1), join=(pk, bk))
+    _same(got(), want, 1)
+    _same(got(), want, 1)
+
+
 # every comparison with literals at, beside and beyond the ends of the column's type, outputs that start at each
 # position of a 16-byte unit, tiles that end inside a lane's group of rows
 @pytest.mark.parametrize("dtype", [np.int8, np.int32, np.int64])
