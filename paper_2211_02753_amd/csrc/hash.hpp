@@ -180,11 +180,30 @@ constexpr uint32_t kAggUnitMaxBlk = 1024;
 constexpr int kAggSub = 4096;            // rows the unit scatter orders at once (four per thread)
 constexpr int kAggScatThreads = 1024;    // threads of the unit scatter (one group per thread)
 
-// Small builds (fewer rows than kDirectRows) need no bucketing: one workgroup
-// per probing block reads every build key and inserts its block's in LDS.  A
-// table in memory filled by compare-and-swaps waits for its longest probe
-// sequence at device scope (10K keys: 13 us and 3 us of clearing; 4 us here).
-constexpr int64_t kDirectRows = 65536;
+// Builds of fewer than kSmallRows rows need no bucketing.  Two forms, a launch
+// each; where the line lies between them (build alone, launch gaps included):
+//   direct: one workgroup per probing block reads every build key and inserts
+//     its block's in LDS.  Keys and row ids, at most half full, 1K to 16K rows:
+//     8.9 to 14 us, the table in memory 14 to 25 (filled by compare-and-swaps, it
+//     waits for its longest probe sequence at device scope).  The time grows with
+//     the rows that each workgroup reads, not with their load of the table, so
+//     beyond kDirectFew rows only tables of at most kDirectSlots slots are built
+//     so: 30K rows in 65,536 slots 17 and 22 us, 33K in 131,072 17 and 14, 33K in
+//     524,288 (load 10 %) 16 and 11, 65K in 131,072 29 and 30.
+//   in memory: the rest.  Aggregate sides leave the direct form after
+//     kDirectAgg rows, because workgroups that add their own distinct keys to
+//     the table in memory serve skewed keys better (16K rows, a quarter as many
+//     keys: 9 and 12 us; half the rows on one key 9 and 31; all distinct 18 and
+//     16; 65K rows, half of them on one key: 12, and 110 direct).
+constexpr int64_t kSmallRows = 65536;
+constexpr int64_t kDirectFew = 16384;
+constexpr int64_t kDirectAgg = 8192;
+constexpr uint32_t kDirectSlots = 65536;
+
+inline bool direct_build(TableKind kind, int64_t n_build, uint32_t cap) {
+    if (kind == TABLE_LIST || n_build >= kSmallRows) return false;
+    return kind == TABLE_AGG ? n_build <= kDirectAgg : n_build <= kDirectFew || cap <= kDirectSlots;
+}
 
 struct BuildScratch {
     bool direct = false;    // one workgroup per probing block reads all build keys (no histograms, no bucketing)
@@ -212,11 +231,11 @@ constexpr uint32_t kBuildSegRows = 16384;
 
 inline BuildScratch build_scratch_alloc(WsAlloc& wa, TableKind kind, int64_t n_build, uint32_t cap, bool with_sum) {
     BuildScratch b;
-    b.direct = kind != TABLE_LIST && n_build < kDirectRows;
+    b.direct = direct_build(kind, n_build, cap);
     if (b.direct || kind == TABLE_LIST || cap < kTableBlock) return b;
     b.gslots = build_group_slots(kind, cap);
     const uint32_t nblk = cap / b.gslots;
-    b.lds = nblk >= 1 && nblk <= 8192;
+    b.lds = n_build >= kSmallRows && nblk >= 1 && nblk <= 8192;
     if (!b.lds) return b;
     b.nblk = nblk;
     while ((1u << b.gshift) < b.gslots) ++b.gshift;

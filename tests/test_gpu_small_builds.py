@@ -78,6 +78,35 @@ def test_small_build_sides(nb, mode):
         _same(got, want, len(keys))
 
 
+# the last direct and the first memory build of each kind, by rows and by slots (load), the longest key list; distinct
+# keys, keys held by many rows, and many rows of the key kept outside the blocks
+@pytest.mark.parametrize("nb", [8192, 8193, 16_385, 65_535])
+@pytest.mark.parametrize("load", [0, 90])
+@pytest.mark.parametrize("mode", ["keys", "value", "agg", "hot", "empty", "count"])
+def test_small_build_forms(nb, load, mode):
+    rng = np.random.default_rng(nb + load)
+    n = 30_011
+    pool = np.unique(np.concatenate([[-2**31], rng.integers(-2**31, 2**31, 2 * nb)])).astype(np.int32)
+    uniq = rng.permutation(pool)[:nb]
+    if mode in ("keys", "value"):
+        bk = uniq
+    else:
+        bk = uniq[rng.integers(0, nb // 5, nb)]
+        if mode != "agg":
+            bk[rng.random(nb) < 0.5] = -2**31 if mode == "empty" else uniq[0]
+    pk = np.where(rng.random(n) < 0.9, bk[rng.integers(0, nb, n)], pool[rng.integers(0, len(pool), n)]).astype(np.int32)
+    g, v = rng.integers(0, 30, n).astype(np.int32), rng.integers(-2**40, 2**40, n)
+    b32 = rng.integers(-2**31, 2**31, nb).astype(np.int32)
+    print("build form", nb, load, mode, flush=True)
+    a = {"keys": (v, 0), "count": None}.get(mode, (b32, 1))
+    q = Q.GroupbyQuery(n, [Q.Key(dev(g), 0, 30)], expr=L.EXPR_NONE if a is None else L.EXPR_COL,
+                       a=None if a is None else Q.Operand(dev(a[0]), L.BUILD if a[1] else L.PROBE),
+                       join=(dev(bk), dev(pk), mode in ("keys", "value"), load))
+    want = oracle.query(n, keys=[(g, 0)], expr=oracle.EXPR_NONE if a is None else oracle.EXPR_COL, a=a, join=(pk, bk))
+    _same(q(), want, 1)
+    _same(q(), want, 1)
+
+
 def test_small_build_flags():
     n = 1000
     pk = dev(np.arange(n, dtype=np.int32))
