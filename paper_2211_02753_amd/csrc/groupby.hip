@@ -5,13 +5,14 @@
 // declared domains and adds the row's value and count to a privatised
 // accumulator:
 //   G <= 8     per-thread registers, wave-reduced, one partial per workgroup;
-//   G <= 2048  an LDS table per workgroup (copies of it per lane for few
-//              groups), written as the workgroup's partial row;
+//   G <= 2048  an LDS table per workgroup (up to eight copies of it for few
+//              groups), written as the workgroup's partial row, or added to
+//              the dense table where few rows leave little to add;
 //   larger     global atomics on the dense table, or (many rows, at most
 //              2^20 groups) the partitioned aggregation further below.
 // Partial rows of up to 256 groups are summed and the non-empty groups emitted
-// in key order by one workgroup of a separate finishing kernel; more groups are
-// summed into the dense table first, which one workgroup emits up to G = 4096,
+// in key order by one workgroup of a separate finishing kernel; more are summed
+// into the dense table first, which one workgroup emits up to G = 4096,
 // and three small kernels beyond (count per chunk, scan of the chunk counts,
 // write), or the top-k kernels rank.  The radix-partitioned probe of large
 // keys-only joins and the opt-in staged probe are also below.
@@ -36,6 +37,7 @@ constexpr int kThreads = 256;
 constexpr int kRegMaxG = 8;
 constexpr int kFinThreads = 1024;     // threads of the finalize over partial rows
 constexpr int kPartMaxG = 256;        // groups it takes
+constexpr int64_t kPartMaxCells = 48 << 10;  // and cells of the partial rows
 constexpr int kLdsMaxG = 2048;
 constexpr int kGbMaxThreads = 1024;   // threads of a fused kernel's workgroup with LDS accumulators
 constexpr int kLastBlockMaxG = 4096;
@@ -543,11 +545,12 @@ __device__ __forceinline__ void eval_rows(const GbDev& d, int64_t r0, bool ok[4]
     for (int e = 0; e < 4; ++e) cnt[e] = JM == J_AGG ? bcnt[e] : 1ull;
 }
 
-// With LDS accumulators a workgroup keeps d.lds_copies copies of its table,
-// lane l adding to copy l mod lds_copies, so that fewer lanes of an
-// instruction meet on one address, and writes their sum as one partial row.
+// With LDS accumulators and partial rows a workgroup keeps d.lds_copies copies
+// of its table, lane l adding to copy l mod lds_copies, so that fewer lanes of
+// an instruction meet on one address, and writes their sum as one partial row.
 // Merging the tables with device-scope atomics instead (2G per workgroup, all
-// on the same 2G words) bound the 1M-row, 75-group star join: 32 us.
+// on the same 2G words) bound the 1M-row, 75-group star join: 32 us.  Where few
+// workgroups do so (make_plan) that is the cheaper way.
 template <int ACC, int JM, bool SEL, class S>
 __global__ __launch_bounds__(ACC == ACC_LDS ? kGbMaxThreads : kThreads) void groupby_kernel(GbDev d) {
     extern __shared__ unsigned long long s_all[];  // ACC_LDS: [copies] of [G] sums then [G] counts
@@ -579,7 +582,7 @@ __global__ __launch_bounds__(ACC == ACC_LDS ? kGbMaxThreads : kThreads) void gro
     for (; r0 + 4 <= d.n_cand; r0 += stride) rows4(r0, std::true_type{});
     if (r0 < d.n_cand) rows4(r0, std::false_type{});
 
-    if (ACC == ACC_LDS) {
+    if (ACC == ACC_LDS && d.part) {
         __syncthreads();
         for (int64_t g = threadIdx.x; g < d.G; g += blockDim.x) {
             ulonglong2 v = make_ulonglong2(0ull, 0ull);
@@ -2604,7 +2607,8 @@ struct Plan {
     int acc = ACC_REG;
     int nblocks = 1;
     int threads = kThreads;  // of the fused kernel's workgroups
-    bool lds_part = false;   // fused kernel with LDS accumulators: one partial row per workgroup
+    bool lds_part = false;   // fused kernel with LDS accumulators: one partial row per workgroup (else added to gtab)
+    bool part_sum = false;   // partial rows are summed into the dense table before the finalize
     int lds_copies = 1;
     bool last_block_fin = true;
     int64_t n_cand = 0;
@@ -2831,13 +2835,27 @@ int make_plan(const tdp_groupby_desc* d, Plan& p) {
     if (p.pagg) {
         p.pagg_np = (int)ceil_div(p.G, kPaggGroups);
     }
-    p.lds_part = p.acc == ACC_LDS && !p.radix && !p.staged;
+    if (p.acc == ACC_LDS && !p.radix && !p.staged) {
+        // Partial rows cost a reduction of their own beyond kPartMaxG groups and
+        // for top-k, and their write-back at the kernel's end; adding the tables
+        // with device-scope atomics costs more the more workgroups there are,
+        // less where a join lets them end at different times.  Rows and atomics,
+        // us: no join, 75 groups, 100K rows 13.8 and 14.8, 262K 14 and 19; 300
+        // groups 100K 17 and 15, 200K 17.6 and 19; join (65K keys) 75 groups,
+        // 100K 21 and 18, 200K 21.5 and 21.3, 300K 23.6 and 25.8; 300 groups,
+        // 200K 23 and 20, 300K 25.4 and 26.3.
+        const bool more = p.G > kPartMaxG || p.topk;
+        p.lds_part = p.n_cand >= (p.jm != J_NONE ? (more ? 256 << 10 : 192 << 10) : more ? 128 << 10 : 0);
+    }
     if (p.lds_part) {
         // one workgroup per CU (one partial row each): small inputs are spread
         // over the CUs by workgroups of 256 threads, larger ones take 1024
         p.threads = p.n_cand >= (int64_t)kCUs * kThreads * 4 ? kGbMaxThreads : kThreads;
         p.nblocks = (int)std::min<int64_t>(std::max<int64_t>(ceil_div(p.n_cand, p.threads * 4), 1), kCUs);
         while (p.lds_copies < 8 && p.lds_copies * 2 * p.G <= kLdsMaxG) p.lds_copies *= 2;
+        // one workgroup sums and emits few cells (250 groups of 147 rows 16 us, by two kernels 17.4; of 256 rows
+        // 19.7 and 17.9)
+        p.part_sum = p.G > kPartMaxG || p.topk || p.nblocks * p.G > kPartMaxCells;
     }
     return TDP_OK;
 }
@@ -2867,7 +2885,7 @@ WsLayout layout(const Plan& p, const tdp_groupby_desc* d, void* ws) {
     L.zblock = wa.take<unsigned long long>((size_t)std::max<int64_t>(L.n_zero, 1));
     if (parts) {
         L.part = wa.take<unsigned long long>((size_t)p.nblocks * p.G * 2);
-        if (p.G > kPartMaxG || p.topk) L.gtab = wa.take<unsigned long long>((size_t)p.G * 2);  // the partial rows' sum
+        if (p.part_sum) L.gtab = wa.take<unsigned long long>((size_t)p.G * 2);
     } else {
         L.gtab = L.zblock;
     }

@@ -41,6 +41,30 @@ def test_partial_rows(G, n):
     assert np.array_equal(top["sum"].cpu().numpy(), want["sum"][order])
 
 
+# tables added to the dense one and partial rows on both sides of the lines between them, few and many cells
+@pytest.mark.parametrize("n", [3001, (128 << 10) - 1, 128 << 10, 192 << 10, (256 << 10) - 1, 256 << 10])
+@pytest.mark.parametrize("G", [9, 192, 193, 256, 300])
+@pytest.mark.parametrize("join", [False, True])
+def test_partial_rows_or_atomics(n, G, join):
+    rng = np.random.default_rng(n + G)
+    k, v = rng.integers(0, G, n).astype(np.int32), rng.integers(-2**62, 2**62, n)
+    bk, pk = rng.permutation(np.arange(5000, dtype=np.int32)), rng.integers(-50, 5050, n).astype(np.int32)
+    print("partial rows or atomics", n, G, join, flush=True)
+    want = oracle.query(n, keys=[(k, 0)], expr=oracle.EXPR_COL, a=(v, 0), join=(pk, bk) if join else None)
+    order = np.lexsort((want["k0"], -want["sum"].astype(object)))[:5]
+    dk, dv = dev(k), dev(v)
+    for topk in (0, 5):
+        q = Q.GroupbyQuery(n, [Q.Key(dk, 0, G)], expr=L.EXPR_COL, a=Q.Operand(dv), topk=topk,
+                           join=(dev(bk), dev(pk), True) if join else None)
+        for _ in range(2):  # the workspace is left ready
+            got = q()
+            if topk:
+                assert np.array_equal(got["k0"].cpu().numpy(), want["k0"][order])
+                assert np.array_equal(got["sum"].cpu().numpy(), want["sum"][order])
+            else:
+                _same(got, want, 1)
+
+
 # one row, one probing block, several, the last direct build and the first bucketed one
 @pytest.mark.parametrize("nb", [1, 2047, 2049, 10_000, 65_535, 65_536])
 @pytest.mark.parametrize("mode", ["keys", "i8", "i32", "value", "i64", "two", "agg", "aggcount"])
