@@ -1175,7 +1175,10 @@ extern "C" int tdp_conv3x3_fwd_bf16(const uint16_t* x, const uint16_t* w, const 
         return launch_status("tdp_conv3x3_fwd_bf16");
     }
     const int64_t x_bytes = (int64_t)B * H * W * Cin * 2;
-    // 32 -> 64 channels: bands of rows in LDS, unless a row is too wide for one
+    // 32 -> 64 channels: bands of rows in LDS, unless a row is too wide for one.  Also where a band is a row or two
+    // and most input rows are staged two or three times: 700K pixels in rows of 72, 100 and 125 columns 37, 47 and 42
+    // us, by the register kernel 47, 48 and 48; the input gradient of rows of 75 and 96 columns 68 and 59 us (177 and
+    // 178), the weight gradient of 578 columns 99 (143)
     if (M > 0 && Cin == 32 && Cout == 64 && a16(y) && conv_fwd_32_64(x, w, bias, B, H, W, relu, y, stream))
         return launch_status("tdp_conv3x3_fwd_bf16");
     if (Cin == 32 && Cout % 16 == 0 && Cout <= 64 && a16(y) && x_bytes < (1ll << 31)) {

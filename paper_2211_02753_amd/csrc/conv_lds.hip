@@ -48,11 +48,14 @@ uint32_t inv_small(int d) { return ((1u << 22) + d - 1) / d; }
 constexpr int kFwdThreads = 256;
 constexpr int kFwdMaxPx = 376;  // input pixels of a band
 
+// MANY: bands of several images.
+template <bool MANY>
 __global__ __launch_bounds__(kFwdThreads, 2) void conv_fwd_kernel(const uint16_t* __restrict__ x,
                                                                   const uint16_t* __restrict__ w,
-                                                                  const float* __restrict__ bias, int H, int W,
-                                                                  int relu, int rows, int bands, int items,
-                                                                  uint32_t inv_wo, uint16_t* __restrict__ y) {
+                                                                  const float* __restrict__ bias, int B, int H, int W,
+                                                                  int relu, int rows, int bands, int imgs, int items,
+                                                                  uint32_t inv_wo, uint32_t inv_ho,
+                                                                  uint16_t* __restrict__ y) {
     constexpr int kLoads = (kFwdMaxPx * 4 + kFwdThreads - 1) / kFwdThreads;
     __shared__ __attribute__((aligned(16))) unsigned char s_x[2][kFwdMaxPx * kXStride];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -71,17 +74,20 @@ __global__ __launch_bounds__(kFwdThreads, 2) void conv_fwd_kernel(const uint16_t
 #pragma unroll
         for (int r = 0; r < 4; ++r) bv[j][r] = bias ? bias[half * 32 + q * 8 + j * 4 + r] : 0.f;
     u32x4 pre[kLoads];
-    // the band of item it: output rows [oy0, oy0 + r), input rows [oy0, oy0 + r + 2)
-    auto band = [&](int it, int& b, int& oy0, int& r) {
-        b = it / bands;
-        oy0 = (it - b * bands) * rows;
+    // the band of item it: output rows [oy0, oy0 + r), input rows [oy0, oy0 + r + 2) of image b, or, where
+    // whole images fit (one band each), of ni images from b
+    auto band = [&](int it, int& b, int& oy0, int& r, int& ni) {
+        const int q = it / bands;
+        b = MANY ? q * imgs : q;
+        oy0 = (it - q * bands) * rows;
         r = Ho - oy0 < rows ? Ho - oy0 : rows;
+        ni = !MANY ? 1 : B - b < imgs ? B - b : imgs;
     };
     auto fetch = [&](int it) {
-        int b, oy0, r;
-        band(it, b, oy0, r);
+        int b, oy0, r, ni;
+        band(it, b, oy0, r, ni);
         const u32x4* src = (const u32x4*)(x + ((int64_t)b * H + oy0) * W * kCi);
-        const int n = (r + 2) * W * 4;
+        const int n = ni * (r + 2) * W * 4;
 #pragma unroll
         for (int k = 0; k < kLoads; ++k) {
             const int i = k * kFwdThreads + t;
@@ -89,9 +95,9 @@ __global__ __launch_bounds__(kFwdThreads, 2) void conv_fwd_kernel(const uint16_t
         }
     };
     auto stage = [&](int it, unsigned char* buf) {
-        int b, oy0, r;
-        band(it, b, oy0, r);
-        const int n = (r + 2) * W * 4;
+        int b, oy0, r, ni;
+        band(it, b, oy0, r, ni);
+        const int n = ni * (r + 2) * W * 4;
 #pragma unroll
         for (int k = 0; k < kLoads; ++k) {
             const int i = k * kFwdThreads + t;
@@ -105,15 +111,16 @@ __global__ __launch_bounds__(kFwdThreads, 2) void conv_fwd_kernel(const uint16_t
     for (; it < items; it += gridDim.x, cur ^= 1) {
         const int next = it + gridDim.x;
         if (next < items) fetch(next);
-        int b, oy0, r;
-        band(it, b, oy0, r);
-        const int npx = r * Wo;
+        int b, oy0, r, ni;
+        band(it, b, oy0, r, ni);
+        const int npx = ni * r * Wo;
         uint16_t* yo = y + ((int64_t)b * Ho + oy0) * Wo * kCo + half * 32 + q * 8;
         const unsigned char* buf = s_x[cur];
         for (int blk = set; blk * 16 < npx; blk += 2) {
             const int p = blk * 16 + (lane & 15), pc = p < npx ? p : npx - 1;
-            const int oy = div_small(pc, inv_wo);
-            const unsigned char* a = buf + (oy * W + pc - oy * Wo) * kXStride + q * 16;
+            // output row, counted over the band's images, and the input row it starts at (two more per image)
+            const int oy = div_small(pc, inv_wo), iy = MANY ? oy + 2 * div_small(oy, inv_ho) : oy;
+            const unsigned char* a = buf + (iy * W + pc - oy * Wo) * kXStride + q * 16;
             bf16x8 f[9];
 #pragma unroll
             for (int k = 0; k < 9; ++k) f[k] = *(const bf16x8*)(a + ((k / 3) * W + k % 3) * kXStride);
@@ -152,8 +159,9 @@ constexpr int kDgLoads = (kDgMaxPx * 8 + kDgThreads - 1) / kDgThreads;
 
 __global__ __launch_bounds__(kDgThreads, kDgPerCU) void conv_dgrad_kernel(const uint16_t* __restrict__ dy,
                                                                    const uint16_t* __restrict__ w,
-                                                                   const uint16_t* __restrict__ mask, int H, int W,
-                                                                   int rows, int bands, int items,
+                                                                   const uint16_t* __restrict__ mask, int B, int H, int W,
+                                                                   int rows, int bands, int imgs, int items,
+                                                                   uint32_t inv_wo, uint32_t inv_ho,
                                                                    uint16_t* __restrict__ dx) {
     constexpr int kBuf = kDgMaxPx * kYStride > kCo * 9 * kCi * 2 ? kDgMaxPx * kYStride : kCo * 9 * kCi * 2;
     __shared__ __attribute__((aligned(16))) unsigned char s_y[kBuf];
@@ -182,13 +190,16 @@ __global__ __launch_bounds__(kDgThreads, kDgPerCU) void conv_dgrad_kernel(const 
     }
     __syncthreads();
     for (int i = t; i < kDgMaxPx * kYStride / 16; i += kDgThreads) ((uint4*)s_y)[i] = make_uint4(0, 0, 0, 0);
-    const int pieces = (rows + 2) * Wo * 8;  // 16-byte pieces of a band's dy rows
-    const int row_pieces = Wo * 8;
+    const int row_pieces = Wo * 8;  // 16-byte pieces of a dy row
     for (int it = blockIdx.x; it < items; it += gridDim.x) {
-        const int b = it / bands, iy0 = (it - b * bands) * rows;
+        const int q2 = it / bands, b = q2 * imgs, iy0 = (it - q2 * bands) * rows;
+        const int ni = B - b < imgs ? B - b : imgs;
         {
+            // the dy rows of a band of one image, from two above it, those outside the image as zeros; or all of
+            // several images, each behind two rows that stay zero
             const u32x4* src = (const u32x4*)(dy + (int64_t)b * Ho * Wo * kCo);
-            const int first = (iy0 - 2) * row_pieces, total = Ho * row_pieces;
+            const int first = imgs > 1 ? 0 : (iy0 - 2) * row_pieces, total = ni * Ho * row_pieces;
+            const int pieces = imgs > 1 ? total : (rows + 2) * row_pieces;
             u32x4 pre[kDgLoads];
 #pragma unroll
             for (int k = 0; k < kDgLoads; ++k) {
@@ -200,12 +211,13 @@ __global__ __launch_bounds__(kDgThreads, kDgPerCU) void conv_dgrad_kernel(const 
             lds_barrier();  // the last band has been read
 #pragma unroll
             for (int k = 0; k < kDgLoads; ++k) {
-                const int i = k * kDgThreads + t, row = i / row_pieces, px = (i - row * row_pieces) >> 3;
-                if (i < pieces) *(u32x4*)&s_y[(row * W + px + 2) * kYStride + (i & 7) * 16] = pre[k];
+                const int i = k * kDgThreads + t, row = div_small(i >> 3, inv_wo);
+                const int at = row * W + (i >> 3) - row * Wo + (imgs > 1 ? 2 + 2 * div_small(row, inv_ho) : 0) * W;
+                if (i < pieces) *(u32x4*)&s_y[(at + 2) * kYStride + (i & 7) * 16] = pre[k];
             }
             lds_barrier();
         }
-        const int npx = (H - iy0 < rows ? H - iy0 : rows) * W;
+        const int npx = ni * (H - iy0 < rows ? H - iy0 : rows) * W;
         const int64_t out = ((int64_t)b * H + iy0) * W * kCi + half * 16 + q * 4;
         auto mask_of = [&](int blk) {  // the mask is read one block ahead
             const int p = blk * 16 + (lane & 15);
@@ -263,9 +275,10 @@ __device__ __forceinline__ bf16x8 join_tr(s16x4 lo, s16x4 hi) {
 }
 
 __global__ __launch_bounds__(kWgThreads) void conv_wgrad_kernel(const uint16_t* __restrict__ x,
-                                                                const uint16_t* __restrict__ dy, int H, int W,
-                                                                int rows, int bands, int items, int shares,
-                                                                int share_step, uint32_t inv_wo, float* dw, float* db) {
+                                                                const uint16_t* __restrict__ dy, int B, int H, int W,
+                                                                int rows, int bands, int imgs, int items, int shares,
+                                                                int share_step, uint32_t inv_wo, uint32_t inv_in,
+                                                                float* dw, float* db) {
     constexpr int kYLoads = kWgMaxOut * 8 / kWgThreads, kXLoads = (kWgMaxIn * 4 + kWgThreads - 1) / kWgThreads;
     // one more pixel of each: zeros, read in the place of pixels past the band
     __shared__ __attribute__((aligned(16))) unsigned char s_y[(kWgMaxOut + 1) * kYStride];
@@ -279,10 +292,12 @@ __global__ __launch_bounds__(kWgThreads) void conv_wgrad_kernel(const uint16_t* 
     if (t < kYStride / 16) *(uint4*)&s_y[kWgMaxOut * kYStride + t * 16] = make_uint4(0, 0, 0, 0);
     if (t < kXStride / 16) *(uint4*)&s_x[kWgMaxIn * kXStride + t * 16] = make_uint4(0, 0, 0, 0);
     u32x4 py[kYLoads], px[kXLoads];
+    // output rows of the band of item it, over its images (several only where each is one band)
     auto band_rows = [&](int it, int& b, int& oy0) {
-        b = it / bands;
-        oy0 = (it - b * bands) * rows;
-        return Ho - oy0 < rows ? Ho - oy0 : rows;
+        const int q = it / bands;
+        b = q * imgs;
+        oy0 = (it - q * bands) * rows;
+        return (B - b < imgs ? B - b : imgs) * (Ho - oy0 < rows ? Ho - oy0 : rows);
     };
     auto fetch = [&](int it) {
         int b, oy0;
@@ -297,8 +312,8 @@ __global__ __launch_bounds__(kWgThreads) void conv_wgrad_kernel(const uint16_t* 
         }
 #pragma unroll
         for (int k = 0; k < kXLoads; ++k) {
-            const int i = k * kWgThreads + t;
-            px[k] = xs[i < nx ? i : nx - 1];
+            const int i = k * kWgThreads + t < nx ? k * kWgThreads + t : nx - 1;
+            px[k] = xs[i + div_small(i >> 2, inv_in) * 2 * W * 4];  // two rows between the images' rows under the tap
         }
     };
     float bsum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // this thread's eight channels of dy
@@ -410,6 +425,15 @@ int band_rows(int total, int most, int B, int want) {
     return (int)ceil_div(total, bands);
 }
 
+// Images of a band, where each is one band and `most` fit: few enough that
+// `want` workgroups have work.  With one image a band whatever its size a
+// workgroup waited for the loads of each: 700K pixels in images of 5 x 5, weight
+// gradient 793 us, 35 so, 60 by the 64 x 64 tiles; forward 70, 21, 23; input
+// gradient 75, 41, 90; 16 x 16, weight gradient 133, 92, 112.
+int band_images(int bands, int most, int B, int want) {
+    return bands > 1 ? 1 : std::max(std::min(most, B / want), 1);
+}
+
 }  // namespace
 
 bool conv_fwd_32_64(const uint16_t* x, const uint16_t* w, const float* bias, int B, int H, int W, int relu,
@@ -417,10 +441,12 @@ bool conv_fwd_32_64(const uint16_t* x, const uint16_t* w, const float* bias, int
     const int most = std::min(kFwdMaxPx / W - 2, H - 2);
     if (most < 1) return false;
     const int rows = band_rows(H - 2, most, B, 2 * kCUs), bands = (int)ceil_div(H - 2, rows);
-    const int64_t items = (int64_t)B * bands;
+    const int imgs = band_images(bands, kFwdMaxPx / (H * W), B, 2 * kCUs);
+    const int64_t items = ceil_div(B, imgs) * bands;
     if (items >= (1ll << 30)) return false;
-    conv_fwd_kernel<<<(unsigned)std::min<int64_t>(items, 2 * kCUs), kFwdThreads, 0, s>>>(
-        x, w, bias, H, W, relu, rows, bands, (int)items, inv_small(W - 2), y);
+    const auto kernel = imgs > 1 ? conv_fwd_kernel<true> : conv_fwd_kernel<false>;
+    kernel<<<(unsigned)std::min<int64_t>(items, 2 * kCUs), kFwdThreads, 0, s>>>(
+        x, w, bias, B, H, W, relu, rows, bands, imgs, (int)items, inv_small(W - 2), inv_small(H - 2), y);
     return true;
 }
 
@@ -428,11 +454,13 @@ bool conv_dgrad_64_32(const uint16_t* dy, const uint16_t* w, const uint16_t* mas
                       hipStream_t s) {
     const int most = std::min((kDgMaxPx - 2) / W - 2, H);
     if (most < 1) return false;
-    const int rows = band_rows(H, most, B, kDgPerCU * kCUs), bands = (int)ceil_div(H, rows);
-    const int64_t items = (int64_t)B * bands;
+    // a workgroup first brings the weights through LDS: small calls take at most one per CU
+    const int rows = band_rows(H, most, B, kCUs / B * B), bands = (int)ceil_div(H, rows);
+    const int imgs = band_images(bands, ((kDgMaxPx - 2) / W - 2) / H, B + kCUs - 1, kCUs);
+    const int64_t items = ceil_div(B, imgs) * bands;
     if (items >= (1ll << 30)) return false;
-    conv_dgrad_kernel<<<(unsigned)std::min<int64_t>(items, kDgPerCU * kCUs), kDgThreads, 0, s>>>(dy, w, mask, H, W, rows, bands,
-                                                                                         (int)items, dx);
+    conv_dgrad_kernel<<<(unsigned)std::min<int64_t>(items, kDgPerCU * kCUs), kDgThreads, 0, s>>>(
+        dy, w, mask, B, H, W, rows, bands, imgs, (int)items, inv_small(W - 2), imgs > 1 ? inv_small(H - 2) : 0, dx);
     return true;
 }
 
@@ -442,13 +470,14 @@ bool conv_wgrad_32_64(const uint16_t* x, const uint16_t* dy, int B, int H, int W
     // bands: as many as there are shares of at least kWgMinPx pixels, one each
     const int64_t shares_px = std::min<int64_t>(std::max<int64_t>((int64_t)B * (H - 2) * (W - 2) / kWgMinPx, 1), kWgShares);
     const int rows = band_rows(H - 2, most, 1, (int)std::max<int64_t>(shares_px / B, 1)), bands = (int)ceil_div(H - 2, rows);
-    const int64_t items = (int64_t)B * bands;
+    const int imgs = band_images(bands, std::min(kWgMaxOut / ((H - 2) * (W - 2)), kWgMaxIn / ((H - 2) * W)), B, (int)shares_px);
+    const int64_t items = ceil_div(B, imgs) * bands;
     if (items >= (1ll << 30)) return false;
     // every share the same number of bands, but for the last ones
     const int shares = (int)ceil_div(items, ceil_div(items, (int64_t)kWgShares));
     const int step = (int)ceil_div(shares, 8) * 8;
-    conv_wgrad_kernel<<<3 * step, kWgThreads, 0, s>>>(x, dy, H, W, rows, bands, (int)items, shares, step,
-                                                      inv_small(W - 2), dw, db);
+    conv_wgrad_kernel<<<3 * step, kWgThreads, 0, s>>>(x, dy, B, H, W, rows, bands, imgs, (int)items, shares, step,
+                                                      inv_small(W - 2), imgs > 1 ? inv_small((H - 2) * W) : 0, dw, db);
     return true;
 }
 

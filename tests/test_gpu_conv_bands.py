@@ -64,6 +64,14 @@ def test_conv_bands(B, H, W):
     close_bf16(values(dx), ref_dx)
 
 
+# bands of several images: as many as fit, the last band with fewer, images of one output row or pixel, images that
+# fit twice under the weight gradient's limits and not under the forward's
+@pytest.mark.parametrize("B,H,W", [(5000, 3, 3), (1537, 5, 5), (1111, 8, 8), (1030, 3, 11), (1031, 9, 4), (530, 16, 16),
+                                   (260, 18, 18)])
+def test_conv_bands_of_small_images(B, H, W):
+    test_conv_bands(B, H, W)
+
+
 def test_conv_bands_keep_infinities_to_their_taps():
     """A value that is not finite reaches exactly the outputs whose taps touch it."""
     rng = np.random.default_rng(5)
@@ -72,6 +80,25 @@ def test_conv_bands_keep_infinities_to_their_taps():
     x[0, 0, W - 1, 3] = np.inf      # only taps with kx = 2 and ky = 0 see the corner
     x[1, 4, 0, 7] = np.nan          # only kx = 0
     dy[1, 2, W - 3, 5] = np.inf
+    xd, xv = bf16(x)
+    dyd, dyv = bf16(dy)
+    wd, w = bf16(rng.standard_normal((64, 3, 3, 32)) * 0.1)
+    y, dx, dw, db = run(xd, wd, dyd, None, None, B, H, W, 0)
+    with np.errstate(invalid="ignore"):
+        refs = (oracle.conv3x3_fwd(xv, w, np.zeros(64, np.float32), relu=False), oracle.conv3x3_dgrad(dyv, w, H, W),
+                *oracle.conv3x3_wgrad(xv, dyv))
+    for got, ref in zip((values(y), values(dx), dw.cpu().numpy(), db.cpu().numpy()), refs):
+        assert np.array_equal(np.isfinite(got), np.isfinite(ref))
+        assert np.array_equal(np.isnan(got), np.isnan(ref))
+
+
+def test_conv_bands_keep_infinities_to_their_images():
+    """Images that share a band do not see each other's values."""
+    rng = np.random.default_rng(6)
+    B, H, W = 2051, 4, 5
+    x, dy = rng.standard_normal((B, H, W, 32)), rng.standard_normal((B, H - 2, W - 2, 64))
+    x[700, H - 1, W - 1, 2], x[1401, 0, 0, 9] = np.inf, np.nan
+    dy[800, H - 3, W - 3, 5] = np.inf
     xd, xv = bf16(x)
     dyd, dyv = bf16(dy)
     wd, w = bf16(rng.standard_normal((64, 3, 3, 32)) * 0.1)
