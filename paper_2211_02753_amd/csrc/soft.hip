@@ -661,139 +661,125 @@ struct SqDev {
     int32_t adt;
 };
 
-// Four consecutive values of a column from row i0 (a multiple of 4; columns
-// are 16-byte aligned) as they lie in memory, rows at or past n as zeros: the
-// loads of every column are issued before the first conversion (a conversion
-// beside its load made each column wait for the one before).  WIDE: int64
-// columns too, whose upper two values are in b.
+// Four consecutive values of an int8, int32 or float32 column from row i0 (a
+// multiple of 4; columns are 16-byte aligned) as they lie in memory, rows at or
+// past n as zeros: the loads of every column are issued before the first
+// conversion (a conversion beside its load made each column wait for the one
+// before).
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-template <bool WIDE>
-struct SqRaw {
-    u32x4 a;
-};
-template <>
-struct SqRaw<true> {
-    u32x4 a, b;
-};
-
-template <bool WIDE>
-__device__ __forceinline__ SqRaw<WIDE> sq_load(const void* p, int dt, int64_t i0, int64_t n) {
-    SqRaw<WIDE> r;
-    r.a = u32x4{0, 0, 0, 0};
-    if constexpr (WIDE) {
-        r.b = u32x4{0, 0, 0, 0};
-        if (dt == TDP_I64) {
-            if (i0 + 4 <= n) {
-                r.a = *(const u32x4*)((const int64_t*)p + i0);
-                r.b = *(const u32x4*)((const int64_t*)p + i0 + 2);
-            } else {
-                const u32x2* q = (const u32x2*)p + i0;
-                if (i0 < n) r.a.lo = q[0];
-                if (i0 + 1 < n) r.a.hi = q[1];
-                if (i0 + 2 < n) r.b.lo = q[2];
-            }
-            return r;
-        }
-    }
+__device__ __forceinline__ u32x4 sq_load(const void* p, int dt, int64_t i0, int64_t n) {
+    u32x4 r = {0, 0, 0, 0};
     if (i0 + 4 <= n) {
-        if (dt == TDP_I8) r.a[0] = *(const uint32_t*)((const int8_t*)p + i0);
-        else r.a = *(const u32x4*)((const int32_t*)p + i0);
+        if (dt == TDP_I8) r[0] = *(const uint32_t*)((const int8_t*)p + i0);
+        else r = *(const u32x4*)((const int32_t*)p + i0);
     } else if (dt == TDP_I8) {
         const uint8_t* q = (const uint8_t*)p + i0;
-        if (i0 < n) r.a[0] = q[0];
-        if (i0 + 1 < n) r.a[0] |= (uint32_t)q[1] << 8;
-        if (i0 + 2 < n) r.a[0] |= (uint32_t)q[2] << 16;
+        if (i0 < n) r[0] = q[0];
+        if (i0 + 1 < n) r[0] |= (uint32_t)q[1] << 8;
+        if (i0 + 2 < n) r[0] |= (uint32_t)q[2] << 16;
     } else {
         const uint32_t* q = (const uint32_t*)p + i0;
-        if (i0 < n) r.a[0] = q[0];
-        if (i0 + 1 < n) r.a[1] = q[1];
-        if (i0 + 2 < n) r.a[2] = q[2];
+        if (i0 < n) r[0] = q[0];
+        if (i0 + 1 < n) r[1] = q[1];
+        if (i0 + 2 < n) r[2] = q[2];
     }
     return r;
 }
 
-// Value E of an int8 or int32 column, and of any integer column.
-template <int E, bool WIDE>
-__device__ __forceinline__ int32_t sq_i32(const SqRaw<WIDE>& r, int dt) {
-    return dt == TDP_I8 ? (int32_t)(int8_t)(r.a[0] >> (8 * E)) : (int32_t)r.a[E];
-}
-
-template <int E>
-__device__ __forceinline__ int64_t sq_i64(const SqRaw<true>& r, int dt) {
-    if (dt != TDP_I64) return sq_i32<E>(r, dt);
-    const uint32_t lo = E < 2 ? r.a[E % 2 * 2] : r.b[E % 2 * 2], hi = E < 2 ? r.a[E % 2 * 2 + 1] : r.b[E % 2 * 2 + 1];
-    return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-
-template <int E, bool WIDE>
-__device__ __forceinline__ float sq_float(const SqRaw<WIDE>& r, int dt) {
-    if (dt == TDP_F32) return __uint_as_float(r.a[E]);
-    if constexpr (WIDE)
-        if (dt == TDP_I64) return (float)sq_i64<E>(r, dt);
-    return (float)sq_i32<E>(r, dt);
-}
-
-template <bool WIDE>
-__device__ __forceinline__ void sq_floats(const SqRaw<WIDE>& r, int dt, float v[4]) {
-    v[0] = sq_float<0>(r, dt);
-    v[1] = sq_float<1>(r, dt);
-    v[2] = sq_float<2>(r, dt);
-    v[3] = sq_float<3>(r, dt);
+// Value e of an int8 or int32 column.
+__device__ __forceinline__ int32_t sq_i32(const u32x4& r, int dt, int e) {
+    return dt == TDP_I8 ? (int32_t)(int8_t)(r[0] >> (8 * e)) : (int32_t)r[e];
 }
 
 // Every column of four rows (NJ: the conjuncts the kernel is built for).
+// WIDE, where a column has int64 values (or a key domain needs 64 bits): the
+// columns are read and converted where they are used, since eight registers a
+// column, held for all of them, were slower than the waits (forward and backward
+// with two conjuncts, one of int64: 10M rows 95 us held, 84 so; 100K rows with
+// an int64 value column 45 and 36).
 template <int NJ, bool WIDE>
 struct SqRows {
-    SqRaw<WIDE> key[2], a, pr[NJ];
+    u32x4 key[2], av, prv[NJ];
+
+    __device__ __forceinline__ void load(const SqDev& d, int64_t i0) {
+        const u32x4 none = {0, 0, 0, 0};
+        key[0] = sq_load(d.kp[0], d.kdt[0], i0, d.n);
+        key[1] = d.n_keys > 1 ? sq_load(d.kp[1], d.kdt[1], i0, d.n) : none;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) prv[j] = j < d.J ? sq_load(d.pr[j].p, d.pr[j].dt, i0, d.n) : none;
+        av = d.a ? sq_load(d.a, d.adt, i0, d.n) : none;
+    }
+    // Key differences of row e, modulo 2^32, and whether both lie in their domains.
+    __device__ __forceinline__ void keys(const SqDev& d, int64_t, uint32_t c1, uint32_t u0[4], uint32_t u1[4], bool in[4]) const {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            u0[e] = (uint32_t)sq_i32(key[0], d.kdt[0], e) - (uint32_t)d.lo[0];
+            u1[e] = d.n_keys > 1 ? (uint32_t)sq_i32(key[1], d.kdt[1], e) - (uint32_t)d.lo[1] : 0u;
+            in[e] = u0[e] < (uint32_t)d.card[0] && u1[e] < c1;
+        }
+    }
+    static __device__ __forceinline__ void floats(const u32x4& r, int dt, float v[4]) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = dt == TDP_F32 ? __uint_as_float(r[e]) : (float)sq_i32(r, dt, e);
+    }
+    __device__ __forceinline__ void value(const SqDev& d, int64_t, float v[4]) const { floats(av, d.adt, v); }
+    __device__ __forceinline__ void pred(const SqDev& d, int64_t, int j, float v[4]) const { floats(prv[j], d.pr[j].dt, v); }
 };
 
-template <int NJ, bool WIDE>
-__device__ __forceinline__ void sq_load_rows(const SqDev& d, int64_t i0, SqRows<NJ, WIDE>& r) {
-    const SqRaw<WIDE> none = {};
-    r.key[0] = sq_load<WIDE>(d.kp[0], d.kdt[0], i0, d.n);
-    r.key[1] = d.n_keys > 1 ? sq_load<WIDE>(d.kp[1], d.kdt[1], i0, d.n) : none;
+template <int NJ>
+struct SqRows<NJ, true> {
+    __device__ __forceinline__ void load(const SqDev&, int64_t) {}
+    __device__ __forceinline__ void keys(const SqDev& d, int64_t i0, uint32_t c1, uint32_t u0[4], uint32_t u1[4], bool in[4]) const {
+        int64_t k0[4], k1[4] = {0, 0, 0, 0};
+        load4_int(d.kp[0], d.kdt[0], i0, d.n, k0);
+        if (d.n_keys > 1) load4_int(d.kp[1], d.kdt[1], i0, d.n, k1);
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) r.pr[j] = j < d.J ? sq_load<WIDE>(d.pr[j].p, d.pr[j].dt, i0, d.n) : none;
-    r.a = d.a ? sq_load<WIDE>(d.a, d.adt, i0, d.n) : none;
-}
-
-// Dense group id of a row (fewer than 2^16 groups); -1 outside its key domain
-// (which raises the flag) or past the end.  Without WIDE the keys have at most
-// 32 bits and domains that 32-bit differences decide.
-template <int E, int NJ, bool WIDE>
-__device__ __forceinline__ int32_t sq_gid(const SqDev& d, const SqRows<NJ, WIDE>& r, int64_t i0, uint32_t c1,
-                                          int32_t* flags) {
-    bool in;
-    uint32_t u0, u1 = 0;
-    if constexpr (WIDE) {
-        const int64_t w0 = sq_i64<E>(r.key[0], d.kdt[0]) - d.lo[0];
-        const int64_t w1 = d.n_keys > 1 ? sq_i64<E>(r.key[1], d.kdt[1]) - d.lo[1] : 0;
-        in = w0 >= 0 && w0 < d.card[0] && w1 >= 0 && w1 < (int64_t)c1;
-        u0 = (uint32_t)w0;
-        u1 = (uint32_t)w1;
-    } else {
-        u0 = (uint32_t)sq_i32<E>(r.key[0], d.kdt[0]) - (uint32_t)d.lo[0];
-        if (d.n_keys > 1) u1 = (uint32_t)sq_i32<E>(r.key[1], d.kdt[1]) - (uint32_t)d.lo[1];
-        in = u0 < (uint32_t)d.card[0] && u1 < c1;
+        for (int e = 0; e < 4; ++e) {
+            const int64_t w0 = k0[e] - d.lo[0], w1 = d.n_keys > 1 ? k1[e] - d.lo[1] : 0;
+            in[e] = w0 >= 0 && w0 < d.card[0] && w1 >= 0 && w1 < (int64_t)c1;
+            u0[e] = (uint32_t)w0;
+            u1[e] = (uint32_t)w1;
+        }
     }
-    if (i0 + E >= d.n) return -1;
-    if (!in) {
-        raise_flag(flags, TDP_FLAG_KEY_DOMAIN);
-        return -1;
+    static __device__ __forceinline__ void floats(const void* p, int dt, int64_t i0, int64_t n, float v[4]) {
+        if (dt == TDP_F32 && i0 + 4 <= n) {
+            const float4 q = *(const float4*)((const float*)p + i0);
+            v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+        } else if (dt == TDP_I32 && i0 + 4 <= n) {
+            const int4 q = *(const int4*)((const int32_t*)p + i0);
+            v[0] = (float)q.x; v[1] = (float)q.y; v[2] = (float)q.z; v[3] = (float)q.w;
+        } else if (dt != TDP_I64) {
+            SqRows<NJ, false>::floats(sq_load(p, dt, i0, n), dt, v);
+        } else {
+            int64_t x[4];
+            load4_int(p, dt, i0, n, x);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = (float)x[e];
+        }
     }
-    return (int32_t)(u0 * c1 + u1);
-}
+    __device__ __forceinline__ void value(const SqDev& d, int64_t i0, float v[4]) const { floats(d.a, d.adt, i0, d.n, v); }
+    __device__ __forceinline__ void pred(const SqDev& d, int64_t i0, int j, float v[4]) const {
+        floats(d.pr[j].p, d.pr[j].dt, i0, d.n, v);
+    }
+};
 
+// Dense group ids of four rows (fewer than 2^16 groups); -1 outside the key
+// domain (which raises the flag) or past the end.
 template <int NJ, bool WIDE>
 __device__ __forceinline__ void sq_gids(const SqDev& d, const SqRows<NJ, WIDE>& r, int64_t i0, int32_t gid[4],
                                         int32_t* flags) {
     const uint32_t c1 = d.n_keys > 1 ? (uint32_t)d.card[1] : 1u;
-    gid[0] = sq_gid<0>(d, r, i0, c1, flags);
-    gid[1] = sq_gid<1>(d, r, i0, c1, flags);
-    gid[2] = sq_gid<2>(d, r, i0, c1, flags);
-    gid[3] = sq_gid<3>(d, r, i0, c1, flags);
+    uint32_t u0[4], u1[4];
+    bool in[4];
+    r.keys(d, i0, c1, u0, u1, in);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        gid[e] = -1;
+        if (i0 + e >= d.n) continue;
+        if (in[e]) gid[e] = (int32_t)(u0[e] * c1 + u1[e]);
+        else raise_flag(flags, TDP_FLAG_KEY_DOMAIN);
+    }
 }
 
 // sigma(z) and 1 - sigma(z) = sigma(-z), neither from a difference.
@@ -828,14 +814,14 @@ __global__ __launch_bounds__(kFwdThreads) void soft_query_fwd_kernel(SqDev d, in
         float w[4] = {1.0f, 1.0f, 1.0f, 1.0f}, ev[4] = {1.0f, 1.0f, 1.0f, 1.0f};
         int32_t gid[4];
         SqRows<NJ, WIDE> rows;
-        sq_load_rows(d, i0, rows);
+        rows.load(d, i0);
         sq_gids(d, rows, i0, gid, ws.flags);
-        if (d.a) sq_floats(rows.a, d.adt, ev);
+        if (d.a) rows.value(d, i0, ev);
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
             if (j >= d.J) break;
             float x[4];
-            sq_floats(rows.pr[j], d.pr[j].dt, x);
+            rows.pred(d, i0, j, x);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 float wd;
@@ -882,15 +868,15 @@ __global__ __launch_bounds__(kSoftThreads) void soft_query_bwd_kernel(SqDev d, c
         float ev[4] = {1.0f, 1.0f, 1.0f, 1.0f};
         int32_t gid[4];
         SqRows<NJ, WIDE> rows;
-        sq_load_rows(d, i0, rows);
+        rows.load(d, i0);
         sq_gids(d, rows, i0, gid, nullptr);
-        if (d.a) sq_floats(rows.a, d.adt, ev);
+        if (d.a) rows.value(d, i0, ev);
         float z[TAU ? NJ : 1][4], om[NJ][4], w[4] = {1.0f, 1.0f, 1.0f, 1.0f};
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
             if (j >= d.J) break;
             float x[4];
-            sq_floats(rows.pr[j], d.pr[j].dt, x);
+            rows.pred(d, i0, j, x);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const float ze = (c[j] - x[e]) * itau[j];
@@ -1559,7 +1545,8 @@ extern "C" int tdp_soft_query(const tdp_groupby_desc* d, const float* d_c, const
         const int64_t wgs = ceil_div(std::max<int64_t>(q.n, 1), (int64_t)kFwdThreads * 16);
         const int grid = (int)std::min<int64_t>(std::min<int64_t>(wgs, 256), kRowFloats / q.G);
         const int copies = table_copies(q.G);
-        if (q.wide) sq_fwd<kSqMaxPreds, true>(q, grid, copies, s, stream);
+        if (q.wide && q.J <= 2) sq_fwd<2, true>(q, grid, copies, s, stream);
+        else if (q.wide) sq_fwd<kSqMaxPreds, true>(q, grid, copies, s, stream);
         else if (q.J <= 1) sq_fwd<1, false>(q, grid, copies, s, stream);
         else if (q.J == 2) sq_fwd<2, false>(q, grid, copies, s, stream);
         else sq_fwd<kSqMaxPreds, false>(q, grid, copies, s, stream);
@@ -1585,6 +1572,8 @@ extern "C" int tdp_soft_query_bwd(const tdp_groupby_desc* d, const float* d_c, c
     const bool tau = d_dtau != nullptr;
     if (q.G > kMaxLdsFloats)
         soft_query_bwd_kernel<false, kSqMaxPreds, true, true><<<grid, kSoftThreads, 0, stream>>>(q, dS, de, s);
+    else if (q.wide && q.J <= 2)
+        sq_bwd<2, true>(q, grid, dS, de, tau, s, stream);
     else if (q.wide)
         sq_bwd<kSqMaxPreds, true>(q, grid, dS, de, tau, s, stream);
     else if (q.J <= 1)

@@ -78,6 +78,15 @@ def test_soft_query_variants(preds, keys, value, n, card):
         assert got[2][j] == got[0][j]  # without the temperatures' gradient
 
 
+# int64 columns beside each other type, one to four conjuncts, tails of 1 to 3 rows, groups beyond the LDS tables
+@pytest.mark.parametrize("preds,keys,value,n,card", [
+    ([], [(I64, -2**62)], I64, 4099, 7), ([I64], [(I8, 0)], F32, 9_002, 5), ([I64, I8], [(I64, 2**62)], I32, 30_001, 11),
+    ([I64, F32, I32], [(I32, 3)], I8, 50_003, 25), ([I8, I64, I32, F32], [(I64, 0), (I8, -3)], None, 33_333, 6),
+    ([I32, F32], [(I32, 0), (I64, -5)], I64, 70_001, 200), ([I64, I64, F32], [(I32, 0), (I32, 7)], F32, 20_002, 200)])
+def test_soft_query_wide_columns(preds, keys, value, n, card):
+    test_soft_query_variants(preds, keys, value, n, card)
+
+
 # every class count and both feature builds, each kind of bag (one row, folds of units alone, of classes too, a whole
 # wave, several rows a lane), with last bags and last waves that are short
 @pytest.mark.parametrize("bag", [1, 2, 4, 16, 32, 64, 128, 256])
