@@ -944,21 +944,26 @@ constexpr int kPeMaxK = 16;      // values of one probability attribute
 constexpr int kPeMaxCells = 64;  // K1 * K2: at most one wave lane per cell
 constexpr int kPeWaves = kSoftThreads / kWave;
 constexpr int kPeLdsBytes = 32 * 1024;  // LDS of one workgroup, all four waves
-// Workgroups of the segmented kernels: one group per wave, so that workgroups
-// start as others end, each at another phase of its group, but about kPeWaveRows
-// rows per wave (which then loops over groups), from kPeMinGrid up to
-// kPeMaxGrid.  Both directions, 10 + 2 probabilities a row: 123,457 groups of
-// 81 rows take 231 us with 4096 workgroups and 207 with one group per wave;
-// of 4 rows 83 and 96; 400,000 groups of 9 rows 296 with 4096, 278 with
-// 16384, 330 with one group per wave; 1M groups of 16 rows 693 with 16384 or
-// 32768, 835 with one group per wave.
+// Workgroups of the segmented kernels: kPeMinGrid, whose waves loop over
+// groups; or one group per wave, so that workgroups start as others end, each at
+// another phase of its group, but about kPeWaveRows rows per wave, up to
+// kPeMaxGrid.  The latter where a wave has enough to load per group, or many
+// small groups, in the narrow kernels.  us with 4096 workgroups and so, 123,457
+// groups of 81 rows: forward, 10 + 2 probabilities 104 and 101, 6 + 2 79 and 83,
+// 2 + 1 64 and 71; backward 194 and 169, 6 + 1 119 and 111, 3 + 2 95 and 98, 2 + 1
+// 66 and 73; 400,000 groups of 9 rows, 10 + 2, 127 and 124, 258 and 246, 3 + 2 149
+// and 143, 184 and 176; the wide kernels, 16 + 2, 81 rows, 173 and 181, 707 and
+// 764.  4-row groups 83 and 96 with one group per wave, so no fewer rows each.
 constexpr int kPeWaveRows = 64;
+constexpr int kPeFewRows = 32;  // rows of a small group
 constexpr int kPeMinGrid = 4096;
 constexpr int kPeMaxGrid = 32768;
 
-int pe_grid(int64_t groups, int64_t n) {
-    const int64_t by_rows = std::min<int64_t>(std::max<int64_t>(n / (kPeWaves * kPeWaveRows), kPeMinGrid), kPeMaxGrid);
-    return (int)std::max<int64_t>(std::min<int64_t>(ceil_div(groups, (int64_t)kPeWaves), by_rows), 1);
+int pe_grid(int64_t groups, int64_t n, bool narrow, bool enough) {
+    int64_t most = kPeMinGrid;
+    if (narrow && (enough || n < groups * kPeFewRows))
+        most = std::min<int64_t>(std::max<int64_t>(n / (kPeWaves * kPeWaveRows), kPeMinGrid), kPeMaxGrid);
+    return (int)std::max<int64_t>(std::min<int64_t>(ceil_div(groups, (int64_t)kPeWaves), most), 1);
 }
 
 struct PeArgs {
@@ -1407,7 +1412,7 @@ extern "C" int tdp_soft_pe_groupby(const int64_t* seg, int32_t G, const float* p
             pe_fwd_kernel<7, 7><<<grid, kSoftThreads, lds, stream>>>(A, s, S);
     };
     if (seg) {
-        const int grid = pe_grid(G, n);
+        const int grid = pe_grid(G, n, small, K1 + K2 >= 11);
         fwd(grid);
         // no cross-workgroup sums: the finishing kernel only reports and clears the flags
         soft_groups_finish_kernel<<<1, kFinishThreads, 0, stream>>>(s, 0, nullptr, nullptr, nullptr, nullptr, d_status);
@@ -1431,8 +1436,8 @@ extern "C" int tdp_soft_pe_groupby_bwd(const int64_t* seg, int32_t G, const floa
     const int T = pe_tile_rows(K1, K2);
     const PeArgs A{seg, G, p, q, K1, K2, n, T};
     const int64_t want = std::min<int64_t>(std::max<int64_t>(ceil_div(n, (int64_t)kSoftThreads * 16), 1), 2048);
-    const int grid = seg ? pe_grid(G, n) : (int)want;
     const bool small = pe_tile_words(T, K1) <= 4 * kWave && pe_tile_words(T, K2) <= kWave && K2 <= 2;
+    const int grid = seg ? pe_grid(G, n, small, K1 + K2 >= 7) : (int)want;
     if (small)
         pe_bwd_kernel<4, 1, 2><<<grid, kSoftThreads, pe_bwd_lds(T, K1, K2), stream>>>(A, dS, dp, dq);
     else

@@ -138,3 +138,32 @@ def test_segmented_counts_over_many_groups(groups, rows):
     dr = np.repeat(d.astype(np.float64), lens, axis=0)
     assert np.all(np.abs(dp.cpu().numpy() - dr * q) <= 1e-6 * np.abs(dr * q))
     assert np.all(np.abs(dq.cpu().numpy()[:, 0] - (dr * p).sum(1)) <= 1e-6 * np.abs(dr * p).sum(1))
+
+
+# one group per wave with 64 rows a wave at least (ten and two probabilities), backward only, waves that loop over the
+# groups (the wide kernels), and many small groups
+@pytest.mark.parametrize("groups,rows,k1,k2", [(40_001, 50, 10, 2), (40_001, 50, 6, 1), (20_003, 40, 5, 4),
+                                               (70_001, 20, 3, 2)])
+def test_segmented_counts_grids(groups, rows, k1, k2):
+    from paper_2211_02753_amd import soft
+    rng = np.random.default_rng(groups + k1)
+    lens = rng.integers(rows - 3, rows + 4, groups)
+    seg = np.concatenate([[0], np.cumsum(lens)]).astype(I64)
+    n = int(seg[-1])
+    p, q = rng.random((n, k1), dtype=F32), rng.random((n, k2), dtype=F32)
+    d = rng.random((groups, k1, k2), dtype=F32)
+    print("segmented grids", groups, rows, k1, k2, flush=True)
+    st = torch.zeros(1, dtype=torch.int32, device=DEV)
+    S = soft.soft_pe_groupby(t(p), t(q), t(seg), groups, status=st).cpu().numpy()
+    assert int(st.item()) == 0
+    dp, dq = (x.cpu().numpy() for x in soft.soft_pe_groupby_bwd(t(p), t(q), t(seg), t(d)))
+    p, q, d = p.astype(np.float64), q.astype(np.float64), d.astype(np.float64)
+    for a in range(k1):
+        for b in range(k2):
+            want = np.add.reduceat(p[:, a] * q[:, b], seg[:-1])
+            assert np.all(np.abs(S[:, a, b] - want) <= 1e-6 * want)
+    dr = np.repeat(d, lens, axis=0)
+    want = np.matmul(dr, q[:, :, None])[:, :, 0]
+    assert np.all(np.abs(dp - want) <= 1e-6 * want)
+    want = np.matmul(p[:, None, :], dr)[:, 0]
+    assert np.all(np.abs(dq - want) <= 2e-6 * want)
