@@ -249,6 +249,7 @@ constexpr int kTile = 1024;
 constexpr int kSortThreads = kTile / 2;
 constexpr int kMergeWay = 16;
 constexpr int kMergeWaves = 4;  // waves that share the searches of 64 representatives
+constexpr int kMergeGrid = 1 << 15;  // most workgroups of a merge
 
 // Word pair p of a string, most significant word first.
 __device__ __forceinline__ uint64_t load_pair(const uint32_t* s, int W, int p) {
@@ -349,71 +350,74 @@ __global__ __launch_bounds__(kMergeWaves * kWave) void dict_merge_kernel(DictRun
     constexpr int kPer = kMergeWay / kMergeWaves;
     __shared__ int32_t s_part[kMergeWaves][kWave];
     const int64_t d = *d_count < cap ? *d_count : cap;
-    const int64_t i = (int64_t)blockIdx.x * kWave + lane_id();
-    if ((int64_t)blockIdx.x * kWave >= d) return;
-    const bool have = i < d;
     const int wave = threadIdx.x / kWave;
-    uint64_t key[P];
+    for (int64_t i0 = (int64_t)blockIdx.x * kWave; i0 < d; i0 += (int64_t)gridDim.x * kWave) {
+        const int64_t i = i0 + lane_id();
+        const bool have = i < d;
+        uint64_t key[P];
 #pragma unroll
-    for (int p = 0; p < P; ++p) key[p] = in.pair[p * in.n + (have ? i : d - 1)];
-    const int64_t own = (int64_t)blockIdx.x * kWave / run;  // run is a multiple of 64
-    const int64_t g0 = own / kMergeWay * kMergeWay;         // first run of the group
-    int64_t first[kPer];
-    int32_t lo[kPer], len[kPer];
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-        const int64_t r = g0 + wave * kPer + k;
-        first[k] = r * run;
-        const int64_t left = d - first[k];
-        len[k] = r == own || left <= 0 ? 0 : (int32_t)(left < run ? left : run);
-        if (len[k] == 0) first[k] = 0;
-        lo[k] = 0;
-    }
-    // lo counts strings known to be smaller; the last step can find the whole run smaller
-    for (int64_t step = run / 2; step >= 0; step = step > 1 ? step >> 1 : step - 1) {
-        const int32_t s = step > 0 ? (int32_t)step : 1;
-        uint64_t x[kPer];
-#pragma unroll
-        for (int k = 0; k < kPer; ++k) x[k] = in.pair[first[k] + (lo[k] + s <= len[k] ? lo[k] + s - 1 : 0)];
+        for (int p = 0; p < P; ++p) key[p] = in.pair[p * in.n + (have ? i : d - 1)];
+        const int64_t own = i0 / run;                           // run is a multiple of 64
+        const int64_t g0 = own / kMergeWay * kMergeWay;         // first run of the group
+        int64_t first[kPer];
+        int32_t lo[kPer], len[kPer];
 #pragma unroll
         for (int k = 0; k < kPer; ++k) {
-            if (lo[k] + s > len[k]) continue;
-            bool less = x[k] < key[0];
-            if (P > 1 && x[k] == key[0]) {
-                bool open = true;
+            const int64_t r = g0 + wave * kPer + k;
+            first[k] = r * run;
+            const int64_t left = d - first[k];
+            len[k] = r == own || left <= 0 ? 0 : (int32_t)(left < run ? left : run);
+            if (len[k] == 0) first[k] = 0;
+            lo[k] = 0;
+        }
+        // lo counts strings known to be smaller; the last step can find the whole run smaller
+        for (int64_t step = run / 2; step >= 0; step = step > 1 ? step >> 1 : step - 1) {
+            const int32_t s = step > 0 ? (int32_t)step : 1;
+            uint64_t x[kPer];
 #pragma unroll
-                for (int p = 1; p < P; ++p) {
-                    const uint64_t y = in.pair[p * in.n + first[k] + lo[k] + s - 1];
-                    if (open && y != key[p]) {
-                        less = y < key[p];
-                        open = false;
+            for (int k = 0; k < kPer; ++k) x[k] = in.pair[first[k] + (lo[k] + s <= len[k] ? lo[k] + s - 1 : 0)];
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) {
+                if (lo[k] + s > len[k]) continue;
+                bool less = x[k] < key[0];
+                if (P > 1 && x[k] == key[0]) {
+                    bool open = true;
+#pragma unroll
+                    for (int p = 1; p < P; ++p) {
+                        const uint64_t y = in.pair[p * in.n + first[k] + lo[k] + s - 1];
+                        if (open && y != key[p]) {
+                            less = y < key[p];
+                            open = false;
+                        }
                     }
                 }
+                if (less) lo[k] += s;
             }
-            if (less) lo[k] += s;
         }
-    }
-    int32_t sum = 0;
+        int32_t sum = 0;
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) sum += lo[k];
-    s_part[wave][lane_id()] = sum;
-    __syncthreads();
-    if (wave > 0 || !have) return;
-    int64_t rank = g0 * run + i - own * run;
+        for (int k = 0; k < kPer; ++k) sum += lo[k];
+        s_part[wave][lane_id()] = sum;
+        __syncthreads();
+        if (wave == 0 && have) {
+            int64_t rank = g0 * run + i - own * run;
 #pragma unroll
-    for (int w = 0; w < kMergeWaves; ++w) rank += s_part[w][lane_id()];
-    const int32_t row = in.rep[i];
-    if (LAST) {
-        slot_code[row_slot[row]] = (int32_t)rank;
+            for (int w = 0; w < kMergeWaves; ++w) rank += s_part[w][lane_id()];
+            const int32_t row = in.rep[i];
+            if (LAST) {
+                slot_code[row_slot[row]] = (int32_t)rank;
 #pragma unroll
-        for (int p = 0; p < P; ++p) {
-            dict[rank * W + 2 * p] = __builtin_bswap32((uint32_t)(key[p] >> 32));
-            if (2 * p + 1 < W) dict[rank * W + 2 * p + 1] = __builtin_bswap32((uint32_t)key[p]);
+                for (int p = 0; p < P; ++p) {
+                    dict[rank * W + 2 * p] = __builtin_bswap32((uint32_t)(key[p] >> 32));
+                    if (2 * p + 1 < W) dict[rank * W + 2 * p + 1] = __builtin_bswap32((uint32_t)key[p]);
+                }
+            } else {
+                out.rep[rank] = row;
+#pragma unroll
+                for (int p = 0; p < P; ++p) out.pair[p * out.n + rank] = key[p];
+            }
         }
-    } else {
-        out.rep[rank] = row;
-#pragma unroll
-        for (int p = 0; p < P; ++p) out.pair[p * out.n + rank] = key[p];
+        __syncthreads();  // the counts have been read
     }
 }
 
@@ -529,7 +533,8 @@ DictWs dict_layout(void* ws, int64_t n, int64_t max_distinct, int W, size_t* byt
     DictWs w;
     int64_t slots = 256;
     const bool repeats = n >= kSeenMinRows && n >= kSeenRepeat * max_distinct;
-    while (slots < (repeats ? 4 : 2) * max_distinct) slots <<= 1;
+    // slots are int32 (a bound above 2^30 fills its table beyond a half)
+    while (slots < (repeats ? 4 : 2) * max_distinct && slots < (int64_t)1 << 31) slots <<= 1;
     WsAlloc wa(ws);
     w.table = wa.take<int32_t>(slots);
     w.slot_code = wa.take<int32_t>(slots);
@@ -568,7 +573,7 @@ void dict_sort(const uint32_t* strs, int W, const DictWs& w, int64_t cap, const 
                hipStream_t stream) {
     dict_tile_sort_kernel<P><<<(unsigned)ceil_div(cap, kTile), kSortThreads, 0, stream>>>(strs, W, w.reps, d_count, cap,
                                                                                          w.run[0]);
-    const unsigned grid = (unsigned)ceil_div(cap, kWave);
+    const unsigned grid = (unsigned)std::min<int64_t>(ceil_div(cap, kWave), kMergeGrid);
     int at = 0;
     int64_t run = kTile;
     for (; run * kMergeWay < cap; run *= kMergeWay, at ^= 1)

@@ -131,3 +131,43 @@ def test_dictionary_over_its_bound_with_repeated_rows_raises_the_flag():
     rows = words[np.random.default_rng(10).integers(0, 40_000, 200_000)]
     with pytest.raises(L.TdpError, match="TABLE_FULL"):
         dictenc.encode(t(rows), max_distinct=5000)
+
+
+def _base26(v, width, prefix):
+    """Rows of `prefix` letters 'q' and then v in `width - prefix` base-26 letters: they order as v does."""
+    out = torch.full((len(v), width), ord("q"), dtype=torch.uint8, device=DEV)
+    for k in range(width - 1, prefix - 1, -1):
+        out[:, k] = (v % 26 + ord("a")).to(torch.uint8)
+        v = v // 26
+    return out
+
+
+# three levels of merges with strings at every one, and more strings than one step of the merge's workgroups takes;
+# strings that differ in their first, second and last word pair
+@pytest.mark.parametrize("n,width,prefix", [(300_001, 8, 0), (300_001, 12, 6), (2_200_003, 16, 8), (2_200_003, 32, 25)])
+def test_dictionary_of_many_strings(n, width, prefix):
+    v = torch.randperm(n, device=DEV)
+    strs = _base26(v, width, prefix)
+    print("many strings", n, width, flush=True)
+    d, codes = dictenc.encode(strs)
+    assert d.shape[0] == n and torch.equal(codes.long(), v)
+    assert torch.equal(d, _base26(torch.arange(n, device=DEV), width, prefix))
+
+
+def test_dictionary_of_a_bound_above_2_to_the_30():
+    """A column of more than 2^30 rows without a bound of its own: the table's slots stay int32, the merge's grid
+    within a launch's limit."""
+    n, nd = (1 << 30) + 1001, 250
+    if torch.cuda.mem_get_info()[0] < 170 << 30:
+        pytest.skip("needs 170 GiB of device memory")
+    words = _base26(torch.arange(nd, device=DEV), 4, 1)
+    pick = torch.randint(0, nd, (n,), dtype=torch.uint8, device=DEV)
+    strs = torch.empty((n, 4), dtype=torch.uint8, device=DEV)
+    for i in range(0, n, 1 << 27):
+        strs[i:i + (1 << 27)] = words[pick[i:i + (1 << 27)].long()]
+    print("bound above 2^30", flush=True)
+    d, codes = dictenc.encode(strs)
+    assert torch.equal(d, words)
+    assert all(torch.equal(codes[i:i + (1 << 27)], pick[i:i + (1 << 27)].int()) for i in range(0, n, 1 << 27))
+    del strs, codes, pick, d
+    torch.cuda.empty_cache()
