@@ -257,21 +257,36 @@ __device__ __forceinline__ uint64_t load_pair(const uint32_t* s, int W, int p) {
     return 2 * p + 1 < W ? hi | __builtin_bswap32(s[2 * p + 1]) : hi;
 }
 
-// Representatives in order: their rows, and their strings as word pairs (pair
-// p of representative i at pair[p * n + i]).
+// d representatives in order: their rows, and their strings as columns of word
+// pairs (pair p of representative i from words[2 * (p * d + i)] on, then a
+// column of single words where W is odd), so that they take as many bytes as d
+// rows of the dictionary, whose buffer holds one of the two runs of a merge.
 struct DictRun {
     int32_t* rep;
-    uint64_t* pair;
-    int64_t n;
+    uint32_t* words;
 };
+typedef uint64_t __attribute__((aligned(4))) u64a4;
+
+template <int W>
+__device__ __forceinline__ uint64_t run_pair(const DictRun& r, int64_t d, int p, int64_t i) {
+    if (2 * p + 1 == W) return (uint64_t)r.words[2 * p * d + i] << 32;
+    return *(const u64a4*)&r.words[2 * (p * d + i)];
+}
+
+template <int W>
+__device__ __forceinline__ void put_pair(const DictRun& r, int64_t d, int p, int64_t i, uint64_t v) {
+    if (2 * p + 1 == W) r.words[2 * p * d + i] = (uint32_t)(v >> 32);
+    else *(u64a4*)&r.words[2 * (p * d + i)] = v;
+}
 
 // A bitonic network over one tile.  Only the first pair and the tile position
 // move; a tie reads the other pairs where they were loaded.  Strides of at
 // most a wave's 128 elements need no workgroup barrier.
-template <int P>
-__global__ __launch_bounds__(kSortThreads) void dict_tile_sort_kernel(const uint32_t* __restrict__ strs, int W,
+template <int W>
+__global__ __launch_bounds__(kSortThreads) void dict_tile_sort_kernel(const uint32_t* __restrict__ strs,
                                                                       const int32_t* reps, const int64_t* d_count,
                                                                       int64_t cap, DictRun out) {
+    constexpr int P = (W + 1) / 2;      // word pairs
     constexpr uint16_t kNone = 0xFFFF;  // no string: sorts last
     __shared__ uint64_t s_key[kTile];
     __shared__ uint64_t s_rest[P > 1 ? P - 1 : 1][kTile];
@@ -330,9 +345,9 @@ __global__ __launch_bounds__(kSortThreads) void dict_tile_sort_kernel(const uint
     for (int e = threadIdx.x; e < m; e += kSortThreads) {
         const int at = s_at[e];
         out.rep[base + e] = reps[base + at];
-        out.pair[base + e] = s_key[e];
+        put_pair<W>(out, d, 0, base + e, s_key[e]);
 #pragma unroll
-        for (int p = 1; p < P; ++p) out.pair[p * out.n + base + e] = s_rest[p - 1][at];
+        for (int p = 1; p < P; ++p) put_pair<W>(out, d, p, base + e, s_rest[p - 1][at]);
     }
 }
 
@@ -342,11 +357,12 @@ __global__ __launch_bounds__(kSortThreads) void dict_tile_sort_kernel(const uint
 // neighbours of one run, whose searches touch the same few lines, and its
 // waves share the runs, four searches in flight per lane.  LAST (one group in
 // all): the place is the string's code and its row of the dictionary.
-template <int P, bool LAST>
+template <int W, bool LAST>
 __global__ __launch_bounds__(kMergeWaves * kWave) void dict_merge_kernel(DictRun in, DictRun out, int64_t run,
-                                                                         const int64_t* d_count, int64_t cap, int W,
+                                                                         const int64_t* d_count, int64_t cap,
                                                                          const int32_t* row_slot, int32_t* slot_code,
                                                                          uint32_t* dict) {
+    constexpr int P = (W + 1) / 2;
     constexpr int kPer = kMergeWay / kMergeWaves;
     __shared__ int32_t s_part[kMergeWaves][kWave];
     const int64_t d = *d_count < cap ? *d_count : cap;
@@ -356,7 +372,7 @@ __global__ __launch_bounds__(kMergeWaves * kWave) void dict_merge_kernel(DictRun
         const bool have = i < d;
         uint64_t key[P];
 #pragma unroll
-        for (int p = 0; p < P; ++p) key[p] = in.pair[p * in.n + (have ? i : d - 1)];
+        for (int p = 0; p < P; ++p) key[p] = run_pair<W>(in, d, p, have ? i : d - 1);
         const int64_t own = i0 / run;                           // run is a multiple of 64
         const int64_t g0 = own / kMergeWay * kMergeWay;         // first run of the group
         int64_t first[kPer];
@@ -375,7 +391,7 @@ __global__ __launch_bounds__(kMergeWaves * kWave) void dict_merge_kernel(DictRun
             const int32_t s = step > 0 ? (int32_t)step : 1;
             uint64_t x[kPer];
 #pragma unroll
-            for (int k = 0; k < kPer; ++k) x[k] = in.pair[first[k] + (lo[k] + s <= len[k] ? lo[k] + s - 1 : 0)];
+            for (int k = 0; k < kPer; ++k) x[k] = run_pair<W>(in, d, 0, first[k] + (lo[k] + s <= len[k] ? lo[k] + s - 1 : 0));
 #pragma unroll
             for (int k = 0; k < kPer; ++k) {
                 if (lo[k] + s > len[k]) continue;
@@ -384,7 +400,7 @@ __global__ __launch_bounds__(kMergeWaves * kWave) void dict_merge_kernel(DictRun
                     bool open = true;
 #pragma unroll
                     for (int p = 1; p < P; ++p) {
-                        const uint64_t y = in.pair[p * in.n + first[k] + lo[k] + s - 1];
+                        const uint64_t y = run_pair<W>(in, d, p, first[k] + lo[k] + s - 1);
                         if (open && y != key[p]) {
                             less = y < key[p];
                             open = false;
@@ -414,7 +430,7 @@ __global__ __launch_bounds__(kMergeWaves * kWave) void dict_merge_kernel(DictRun
             } else {
                 out.rep[rank] = row;
 #pragma unroll
-                for (int p = 0; p < P; ++p) out.pair[p * out.n + rank] = key[p];
+                for (int p = 0; p < P; ++p) put_pair<W>(out, d, p, rank, key[p]);
             }
         }
         __syncthreads();  // the counts have been read
@@ -525,7 +541,7 @@ struct DictWs {
     int32_t* row_slot;
     int32_t* reps;
     uint32_t* seen;  // string copies by slot, for builds whose rows repeat their strings (null otherwise)
-    DictRun run[2];  // the sorted runs before and after a merge
+    uint32_t* words; // strings of the sorted run that is not in the dictionary's buffer
     int64_t n_slots;
 };
 
@@ -540,11 +556,7 @@ DictWs dict_layout(void* ws, int64_t n, int64_t max_distinct, int W, size_t* byt
     w.slot_code = wa.take<int32_t>(slots);
     w.row_slot = wa.take<int32_t>(std::max<int64_t>(n, 1));
     w.reps = wa.take<int32_t>(max_distinct);
-    for (DictRun& r : w.run) {
-        r.n = max_distinct;
-        r.rep = wa.take<int32_t>(max_distinct);
-        r.pair = wa.take<uint64_t>(max_distinct * ((W + 1) / 2));
-    }
+    w.words = wa.take<uint32_t>(max_distinct * W);
     w.seen = repeats ? wa.take<uint32_t>(slots * W) : nullptr;
     w.n_slots = slots;
     if (bytes) *bytes = wa.bytes();
@@ -568,18 +580,26 @@ void dict_insert(const uint32_t* strs, int64_t n, const DictWs& w, int32_t* stat
                                                                           w.row_slot, status);
 }
 
-template <int P>
-void dict_sort(const uint32_t* strs, int W, const DictWs& w, int64_t cap, const int64_t* d_count, uint32_t* dict,
+template <int W>
+void dict_sort(const uint32_t* strs, const DictWs& w, int64_t cap, const int64_t* d_count, uint32_t* dict,
                hipStream_t stream) {
-    dict_tile_sort_kernel<P><<<(unsigned)ceil_div(cap, kTile), kSortThreads, 0, stream>>>(strs, W, w.reps, d_count, cap,
-                                                                                         w.run[0]);
+    // The last merge writes the dictionary, so it reads the run in the workspace;
+    // the tile sort starts in the one from which the merges before it end there.
+    // The table is read no more, and holds the rows of the run that the tile
+    // sort, which still reads reps, writes.
+    int merges = 0;
+    for (int64_t run = kTile; run * kMergeWay < cap; run *= kMergeWay) ++merges;
+    int at = merges & 1;
+    DictRun runs[2] = {{w.reps, w.words}, {w.reps, dict}};
+    runs[at].rep = w.table;
+    dict_tile_sort_kernel<W><<<(unsigned)ceil_div(cap, kTile), kSortThreads, 0, stream>>>(strs, w.reps, d_count, cap,
+                                                                                         runs[at]);
     const unsigned grid = (unsigned)std::min<int64_t>(ceil_div(cap, kWave), kMergeGrid);
-    int at = 0;
     int64_t run = kTile;
-    for (; run * kMergeWay < cap; run *= kMergeWay, at ^= 1)
-        dict_merge_kernel<P, false><<<grid, kMergeWaves * kWave, 0, stream>>>(w.run[at], w.run[at ^ 1], run, d_count, cap,
-                                                                              W, nullptr, nullptr, nullptr);
-    dict_merge_kernel<P, true><<<grid, kMergeWaves * kWave, 0, stream>>>(w.run[at], w.run[at ^ 1], run, d_count, cap, W,
+    for (; merges > 0; --merges, run *= kMergeWay, at ^= 1)
+        dict_merge_kernel<W, false><<<grid, kMergeWaves * kWave, 0, stream>>>(runs[at], runs[at ^ 1], run, d_count, cap,
+                                                                              nullptr, nullptr, nullptr);
+    dict_merge_kernel<W, true><<<grid, kMergeWaves * kWave, 0, stream>>>(runs[at], runs[at ^ 1], run, d_count, cap,
                                                                          w.row_slot, w.slot_code, dict);
 }
 
@@ -638,11 +658,16 @@ extern "C" int tdp_dict_build(const uint8_t* strs, int64_t n, int32_t L, int64_t
         }
         dict_compact_kernel<<<(unsigned)std::min<int64_t>(ceil_div(w.n_slots, 4 * kCompactThreads), kCUs), kCompactThreads, 0, stream>>>(
             w.table, w.n_slots, w.reps, md, d_n_dict, d_status);
-        switch ((W + 1) / 2) {
-            case 1: dict_sort<1>(s32, W, w, md, d_n_dict, (uint32_t*)dict, stream); break;
-            case 2: dict_sort<2>(s32, W, w, md, d_n_dict, (uint32_t*)dict, stream); break;
-            case 3: dict_sort<3>(s32, W, w, md, d_n_dict, (uint32_t*)dict, stream); break;
-            default: dict_sort<4>(s32, W, w, md, d_n_dict, (uint32_t*)dict, stream); break;
+        uint32_t* out = (uint32_t*)dict;
+        switch (W) {
+            case 1: dict_sort<1>(s32, w, md, d_n_dict, out, stream); break;
+            case 2: dict_sort<2>(s32, w, md, d_n_dict, out, stream); break;
+            case 3: dict_sort<3>(s32, w, md, d_n_dict, out, stream); break;
+            case 4: dict_sort<4>(s32, w, md, d_n_dict, out, stream); break;
+            case 5: dict_sort<5>(s32, w, md, d_n_dict, out, stream); break;
+            case 6: dict_sort<6>(s32, w, md, d_n_dict, out, stream); break;
+            case 7: dict_sort<7>(s32, w, md, d_n_dict, out, stream); break;
+            default: dict_sort<8>(s32, w, md, d_n_dict, out, stream); break;
         }
         dict_codes_kernel<<<dict_grid(ceil_div(n, 4)), 256, 0, stream>>>(w.row_slot, n, w.slot_code, codes);
     }

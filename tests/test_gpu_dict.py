@@ -171,3 +171,27 @@ def test_dictionary_of_a_bound_above_2_to_the_30():
     assert all(torch.equal(codes[i:i + (1 << 27)], pick[i:i + (1 << 27)].int()) for i in range(0, n, 1 << 27))
     del strs, codes, pick, d
     torch.cuda.empty_cache()
+
+
+# no merge before the last, one and two of them; buffers that start 4 bytes off a 16-byte unit, odd word counts
+@pytest.mark.parametrize("n,bound", [(900, 0), (20_000, 0), (20_000, 16_385), (300_007, 290_000)])
+@pytest.mark.parametrize("width", [4, 12, 20, 28, 32])
+def test_dictionary_buffer_beyond_the_strings(n, bound, width):
+    """The rows of the dictionary's buffer behind the last string stay as they were."""
+    nd = min(n // 2, 14_000, 26 ** 3 - 1) if width == 4 else n // 2 if bound != 16_385 else 16_000
+    v = torch.randint(0, nd, (n,), device=DEV)
+    v[:nd] = torch.randperm(nd, device=DEV)
+    strs = _base26(v, width, 1)
+    md = bound or n
+    lib, s = L.load(), L.stream_handle(torch.device("cuda:0"))
+    buf = torch.full((4 + md * width + 4,), 0xEE, dtype=torch.uint8, device=DEV)
+    dic, codes = buf[4:], torch.empty(n, dtype=torch.int32, device=DEV)
+    cnt, st = torch.zeros(1, dtype=torch.int64, device=DEV), torch.zeros(1, dtype=torch.int32, device=DEV)
+    ws = L.workspace(lib.tdp_dict_build_workspace_size(n, bound), DEV)
+    print("dictionary buffer", n, bound, width, flush=True)
+    L.check("dict", lib.tdp_dict_build(L.ptr(strs), n, width, bound, L.ptr(dic), L.ptr(cnt), L.ptr(codes), L.ptr(st),
+                                       L.ptr(ws), ws.numel(), s))
+    assert int(cnt) == nd and int(st) == 0
+    assert torch.equal(codes.long(), v)
+    assert torch.equal(dic[:nd * width].view(nd, width), _base26(torch.arange(nd, device=DEV), width, 1))
+    assert bool((buf[:4] == 0xEE).all()) and bool((dic[nd * width:] == 0xEE).all())
