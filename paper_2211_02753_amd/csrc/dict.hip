@@ -105,9 +105,55 @@ __global__ void dict_fill_kernel(int32_t* p, int64_t n, int32_t v, int64_t* d_co
     }
 }
 
-// Each row of [first, n) finds or claims the slot of its string;
-// row_slot[i] = the slot.  SEEN: `seen` holds copies of the strings whose
-// slots were claimed by an earlier launch, [slot][W], so a row whose string
+// The rows of a pass over a column whose rows repeat their strings: of every
+// group of 16 units of kUnitRows rows one unit is the sample, at a place that
+// varies from group to group, so that the sample shows the strings of a sorted
+// or clustered column too, and of one that repeats every so many rows.
+// PASS_FIRST takes the sample of one of every four groups (again at varying
+// places), PASS_SAMPLE that of the others, PASS_REST the units outside it.
+enum DictPass { PASS_ALL, PASS_FIRST, PASS_SAMPLE, PASS_REST };
+constexpr int kUnitRows = 8;
+constexpr int kGroupUnits = 16;
+
+// The j-th number from 0 on whose place among every N, in quotient q = j / (N - 1)
+// of them, is not `taken`.
+template <int N>
+__device__ __forceinline__ uint32_t skip_one(uint32_t j, uint32_t q, uint32_t taken) {
+    const uint32_t o = j - q * (N - 1);
+    return q * N + o + (o >= taken);
+}
+
+// k-th row of a pass (some lie past the column's end), and their number.
+template <int PASS>
+__device__ __forceinline__ int64_t pass_row(int64_t k) {
+    if (PASS == PASS_ALL) return k;
+    const uint32_t j = (uint32_t)(k / kUnitRows);
+    auto unit_of = [](uint32_t g) { return hash32(g) % kGroupUnits; };
+    auto quarter_of = [](uint32_t q) { return hash32(~q) % 4; };
+    uint32_t unit;
+    if (PASS == PASS_REST) {
+        const uint32_t g = j / (kGroupUnits - 1);
+        unit = skip_one<kGroupUnits>(j, g, unit_of(g));
+    } else {
+        const uint32_t g = PASS == PASS_FIRST ? 4 * j + quarter_of(j) : skip_one<4>(j, j / 3, quarter_of(j / 3));
+        unit = g * kGroupUnits + unit_of(g);
+    }
+    return (int64_t)unit * kUnitRows + k % kUnitRows;
+}
+
+int64_t pass_rows(int pass, int64_t n) {
+    const int64_t groups = ceil_div(n, (int64_t)kGroupUnits * kUnitRows), quarters = ceil_div(groups, (int64_t)4);
+    switch (pass) {
+        case PASS_FIRST: return quarters * kUnitRows;
+        case PASS_SAMPLE: return quarters * 3 * kUnitRows;
+        case PASS_REST: return groups * (kGroupUnits - 1) * kUnitRows;
+        default: return n;
+    }
+}
+
+// Each of the pass's `rows` rows finds or claims the slot of its string;
+// row_slot[i] = the slot.  PASS_REST: `seen` holds copies of the strings whose
+// slots the sample claimed, [slot][W], so a row whose string
 // is among them reads one line of a small array instead of a slot and then a
 // row of the column at a random place (the column's lines, 128 bytes for each
 // row's 16, were the bound of the one-launch form: 235 us for 10M rows of
@@ -116,21 +162,27 @@ __global__ void dict_fill_kernel(int32_t* p, int64_t n, int32_t v, int64_t* d_co
 // A thread takes kRows rows at a time, 256 apart, and walks their probe
 // sequences together: a wave lasts as long as its longest sequence, so one
 // row after the other would add up the longest of each.
-template <int W, bool SEEN>
-__global__ __launch_bounds__(256) void dict_insert_kernel(const uint32_t* __restrict__ strs, int64_t first, int64_t n,
+template <int W, int PASS>
+__global__ __launch_bounds__(256) void dict_insert_kernel(const uint32_t* __restrict__ strs, int64_t rows, int64_t n,
                                                           int32_t* table, uint32_t mask,
                                                           const uint32_t* __restrict__ seen, int32_t* row_slot,
                                                           int32_t* status) {
+    constexpr bool SEEN = PASS == PASS_REST;
     constexpr int kRows = SEEN ? (W <= 4 ? 4 : 2) : 1;
     const int64_t step = 256 * kRows;
     const bool aligned = ((uintptr_t)strs & 15) == 0;
-    for (int64_t i0 = first + (int64_t)blockIdx.x * step; i0 < n; i0 += (int64_t)gridDim.x * step) {
+    for (int64_t k0 = (int64_t)blockIdx.x * step; k0 < rows; k0 += (int64_t)gridDim.x * step) {
+        int64_t row[kRows];
+#pragma unroll
+        for (int e = 0; e < kRows; ++e) {
+            const int64_t k = k0 + e * 256 + threadIdx.x;
+            row[e] = k < rows ? pass_row<PASS>(k) : n;
+        }
         uint32_t w[kRows][W], s[kRows];
         bool found[kRows];
 #pragma unroll
         for (int e = 0; e < kRows; ++e) {
-            const int64_t i = i0 + e * 256 + threadIdx.x;
-            load_raw<W>(strs + (i < n ? i : n - 1) * W, aligned, w[e]);
+            load_raw<W>(strs + (row[e] < n ? row[e] : n - 1) * W, aligned, w[e]);
         }
 #pragma unroll
         for (int e = 0; e < kRows; ++e) {
@@ -160,7 +212,7 @@ __global__ __launch_bounds__(256) void dict_insert_kernel(const uint32_t* __rest
         }
 #pragma unroll
         for (int e = 0; e < kRows; ++e) {
-            const int64_t i = i0 + e * 256 + threadIdx.x;
+            const int64_t i = row[e];
             if (i >= n) continue;
             int32_t slot = found[e] ? (int32_t)s[e] : -1;
             for (uint32_t p = 0; slot < 0 && p <= mask; ++p) {
@@ -524,9 +576,9 @@ __global__ void dict_decode_kernel(const int32_t* codes, int64_t n, const uint32
     }
 }
 
-// When the bound promises at least kSeenRepeat rows per string, the first
-// sixteenth of the rows claims most slots and the rest read the copies of
-// their strings; the first 64th goes alone, so that few rows at a time find a
+// When the bound promises at least kSeenRepeat rows per string, a sixteenth of
+// the rows claims most slots and the rest read the copies of their strings; a
+// quarter of that sample goes alone, so that few rows at a time find a
 // slot empty (each such row is a device-scope compare-and-swap, about 11 G/s:
 // 46 us for a sixteenth of 10M rows in one launch, 2 x 20 us in two).  These
 // builds get four slots per string: a wave waits for its longest probe
@@ -568,16 +620,17 @@ int dict_grid(int64_t n) { return (int)std::min<int64_t>(std::max<int64_t>(ceil_
 template <int W>
 void dict_insert(const uint32_t* strs, int64_t n, const DictWs& w, int32_t* status, hipStream_t stream) {
     const uint32_t mask = (uint32_t)(w.n_slots - 1);
-    const int64_t first = w.seen ? n / 16 : n, few = w.seen ? n / 64 : 0;
-    if (few)
-        dict_insert_kernel<W, false><<<dict_grid(few), 256, 0, stream>>>(strs, 0, few, w.table, mask, nullptr,
-                                                                         w.row_slot, status);
-    dict_insert_kernel<W, false><<<dict_grid(first - few), 256, 0, stream>>>(strs, few, first, w.table, mask, nullptr,
-                                                                             w.row_slot, status);
-    if (!w.seen) return;
+    auto run = [&](auto kernel, int pass, int rows_per_thread) {
+        const int64_t rows = pass_rows(pass, n);
+        if (rows > 0)
+            kernel<<<dict_grid(ceil_div(rows, (int64_t)rows_per_thread)), 256, 0, stream>>>(strs, rows, n, w.table, mask,
+                                                                                          w.seen, w.row_slot, status);
+    };
+    if (!w.seen) return run(dict_insert_kernel<W, PASS_ALL>, PASS_ALL, 1);
+    run(dict_insert_kernel<W, PASS_FIRST>, PASS_FIRST, 1);
+    run(dict_insert_kernel<W, PASS_SAMPLE>, PASS_SAMPLE, 1);
     dict_seen_kernel<<<dict_grid(w.n_slots * W), 256, 0, stream>>>(strs, W, w.table, w.n_slots, w.seen);
-    dict_insert_kernel<W, true><<<dict_grid(ceil_div(n - first, 4)), 256, 0, stream>>>(strs, first, n, w.table, mask, w.seen,
-                                                                          w.row_slot, status);
+    run(dict_insert_kernel<W, PASS_REST>, PASS_REST, 4);
 }
 
 template <int W>

@@ -195,3 +195,21 @@ def test_dictionary_buffer_beyond_the_strings(n, bound, width):
     assert torch.equal(codes.long(), v)
     assert torch.equal(dic[:nd * width].view(nd, width), _base26(torch.arange(nd, device=DEV), width, 1))
     assert bool((buf[:4] == 0xEE).all()) and bool((dic[nd * width:] == 0xEE).all())
+
+
+# columns whose rows are copied from a sample: sizes at the ends of its units and groups, strings that only one row
+# holds, orders that show the sample one string, half of them, all of them, runs of them, or the same rows again
+@pytest.mark.parametrize("n", [1 << 17, (1 << 17) + 1, (1 << 17) + 127, (1 << 17) + 129, 200_003])
+@pytest.mark.parametrize("order", ["sorted", "one", "halves", "cycle", "random"])
+def test_dictionary_of_repeating_rows(n, order):
+    nd, width = 4096, 12
+    at = torch.arange(n, device=DEV)
+    rnd = torch.randint(0, nd - 2, (n,), device=DEV)
+    v = {"sorted": at * (nd - 2) // n, "one": torch.where(at < n // 2, 0, rnd), "cycle": at % 2048, "random": rnd,
+         "halves": torch.where(at < n // 2, rnd // 2, rnd // 2 + nd // 2 - 2)}[order]
+    v[-1], v[n // 3] = nd - 1, nd - 2  # one row each, the last one among them
+    want, codes_want = torch.unique(v, return_inverse=True)
+    print("repeating rows", n, order, flush=True)
+    d, codes = dictenc.encode(_base26(v, width, 5), max_distinct=nd)
+    assert torch.equal(d, _base26(want, width, 5))
+    assert torch.equal(codes.long(), codes_want)
