@@ -131,6 +131,26 @@ def test_small_build_forms(nb, load, mode):
     _same(q(), want, 1)
 
 
+# the largest table that keeps a column's values and the next one, which keeps row ids
+@pytest.mark.parametrize("nb", [(1 << 23) - 1, (1 << 23) + 1])
+@pytest.mark.parametrize("dtype", [torch.int8, torch.int32])
+def test_values_in_large_tables(nb, dtype):
+    n = 300_001
+    pk = torch.randperm(nb, device=DEV)
+    value = torch.randint(0, 100, (nb,), device=DEV).to(dtype)
+    key, amount = torch.randint(0, nb + 1000, (n,), device=DEV), torch.randint(-2**40, 2**40, (n,), device=DEV)
+    print("values in large tables", nb, dtype, flush=True)
+    got = Q.GroupbyQuery(n, [Q.Key(value, 0, 100, L.BUILD)], expr=L.EXPR_COL, a=Q.Operand(amount),
+                         join=(pk.to(torch.int32), key.to(torch.int32), True))()
+    row = torch.empty_like(pk)
+    row[pk] = torch.arange(nb, device=DEV)
+    on = key < nb
+    g = value[row[key[on]]].long()
+    count = torch.zeros(100, dtype=torch.int64, device=DEV).index_add_(0, g, torch.ones_like(g))
+    total = torch.zeros(100, dtype=torch.int64, device=DEV).index_add_(0, g, amount[on])
+    assert torch.equal(got["count"], count) and torch.equal(got["sum"], total)
+
+
 def test_small_build_flags():
     n = 1000
     pk = dev(np.arange(n, dtype=np.int32))
