@@ -314,23 +314,24 @@ __device__ __forceinline__ uint32_t block_of(int32_t key, uint32_t mask, int gsh
     return (hash32((uint32_t)key) & mask) >> gshift;
 }
 
-// Calls f(i, key) for the build rows [lo, hi) a workgroup of T threads
-// owns, four keys per thread and step when the column is 16-byte aligned (lo
-// is a multiple of 4 then), so each thread keeps four loads in flight.
+// Calls f(i, key, m) for the build rows [lo, hi) a workgroup of T threads
+// owns, m = 4 consecutive rows with their keys at a time (m a compile-time
+// constant) when the column is 16-byte aligned (lo is a multiple of 4 then), so
+// that each thread keeps several loads in flight, else m = 1.
 template <int T, class F>
 __device__ __forceinline__ void for_chunk_keys(const int32_t* __restrict__ bkey, int64_t lo, int64_t hi, F f) {
+    constexpr std::integral_constant<int, 1> one{};
+    constexpr std::integral_constant<int, 4> four{};
     if (((uintptr_t)bkey & 15) == 0) {
         int64_t i = lo + (int64_t)threadIdx.x * 4;
         for (; i + 4 <= hi; i += T * 4) {
             const int4 q = *(const int4*)(bkey + i);
-            f(i, q.x);
-            f(i + 1, q.y);
-            f(i + 2, q.z);
-            f(i + 3, q.w);
+            const int32_t key[4] = {q.x, q.y, q.z, q.w};
+            f(i, key, four);
         }
-        for (; i < hi; ++i) f(i, bkey[i]);
+        for (; i < hi; ++i) f(i, bkey + i, one);
     } else {
-        for (int64_t i = lo + threadIdx.x; i < hi; i += T) f(i, bkey[i]);
+        for (int64_t i = lo + threadIdx.x; i < hi; i += T) f(i, bkey + i, one);
     }
 }
 
@@ -342,7 +343,10 @@ __global__ __launch_bounds__(T) void lb_hist_kernel(const int32_t* __restrict__ 
     for (uint32_t b = threadIdx.x; b < nblk; b += T) h[b] = 0;
     __syncthreads();
     const int64_t lo = (int64_t)blockIdx.x * chunk, hi = lo + chunk < n ? lo + chunk : n;
-    for_chunk_keys<T>(bkey, lo, hi, [&](int64_t, int32_t key) { atomicAdd(&h[block_of(key, mask, gshift)], 1u); });
+    for_chunk_keys<T>(bkey, lo, hi, [&](int64_t, const int32_t* key, auto m) {
+#pragma unroll
+        for (int e = 0; e < m; ++e) atomicAdd(&h[block_of(key[e], mask, gshift)], 1u);
+    });
     __syncthreads();
     for (uint32_t b = threadIdx.x; b < nblk; b += T) mat[(int64_t)blockIdx.x * nblk + b] = (h[b] + unit - 1) / unit * unit;
 }
@@ -410,17 +414,26 @@ __global__ __launch_bounds__(T) void lb_scatter_kernel(const int32_t* __restrict
     for (uint32_t b = threadIdx.x; b < nblk; b += T) cur[b] = base[b] + mat[(int64_t)blockIdx.x * nblk + b];
     __syncthreads();
     const int64_t lo = (int64_t)blockIdx.x * chunk, hi = lo + chunk < n ? lo + chunk : n;
-    for_chunk_keys<T>(bkey, lo, hi, [&](int64_t i, int32_t key) {
-        const uint32_t pos = atomicAdd(&cur[block_of(key, mask, gshift)], 1u);
-        if (srec) {
-            AggIn r;
-            r.key = key;
-            r.pad = 0;
-            r.val = (unsigned long long)load_int(bvals, bdt, i);
-            srec[pos] = r;
-        } else {
-            skeys[pos] = key;
-            if (srows) srows[pos] = row_value(t, i);
+    for_chunk_keys<T>(bkey, lo, hi, [&](int64_t i, const int32_t* key, auto m) {
+        // the rows' values are on their way together, before the rows take their places
+        int64_t val[4] = {i, i + 1, i + 2, i + 3};
+        const void* p = srec ? bvals : srows ? t.pay : nullptr;
+        if (p) load4_int(p, srec ? bdt : t.pay_dt, i, i + m, val);
+        uint32_t pos[m];
+#pragma unroll
+        for (int e = 0; e < m; ++e) pos[e] = atomicAdd(&cur[block_of(key[e], mask, gshift)], 1u);
+#pragma unroll
+        for (int e = 0; e < m; ++e) {
+            if (srec) {
+                AggIn r;
+                r.key = key[e];
+                r.pad = 0;
+                r.val = (unsigned long long)val[e];
+                srec[pos[e]] = r;
+            } else {
+                skeys[pos[e]] = key[e];
+                if (srows) srows[pos[e]] = (int32_t)val[e];
+            }
         }
     });
 }
