@@ -157,6 +157,7 @@ constexpr int kDgMaxPx = 290;  // three workgroups per CU
 constexpr int kDgPerCU = 3;
 constexpr int kDgLoads = (kDgMaxPx * 8 + kDgThreads - 1) / kDgThreads;
 
+template <bool MANY>
 __global__ __launch_bounds__(kDgThreads, kDgPerCU) void conv_dgrad_kernel(const uint16_t* __restrict__ dy,
                                                                    const uint16_t* __restrict__ w,
                                                                    const uint16_t* __restrict__ mask, int B, int H, int W,
@@ -192,14 +193,14 @@ __global__ __launch_bounds__(kDgThreads, kDgPerCU) void conv_dgrad_kernel(const 
     for (int i = t; i < kDgMaxPx * kYStride / 16; i += kDgThreads) ((uint4*)s_y)[i] = make_uint4(0, 0, 0, 0);
     const int row_pieces = Wo * 8;  // 16-byte pieces of a dy row
     for (int it = blockIdx.x; it < items; it += gridDim.x) {
-        const int q2 = it / bands, b = q2 * imgs, iy0 = (it - q2 * bands) * rows;
-        const int ni = B - b < imgs ? B - b : imgs;
+        const int q2 = it / bands, b = MANY ? q2 * imgs : q2, iy0 = (it - q2 * bands) * rows;
+        const int ni = !MANY ? 1 : B - b < imgs ? B - b : imgs;
         {
             // the dy rows of a band of one image, from two above it, those outside the image as zeros; or all of
             // several images, each behind two rows that stay zero
             const u32x4* src = (const u32x4*)(dy + (int64_t)b * Ho * Wo * kCo);
-            const int first = imgs > 1 ? 0 : (iy0 - 2) * row_pieces, total = ni * Ho * row_pieces;
-            const int pieces = imgs > 1 ? total : (rows + 2) * row_pieces;
+            const int first = MANY ? 0 : (iy0 - 2) * row_pieces, total = ni * Ho * row_pieces;
+            const int pieces = MANY ? total : (rows + 2) * row_pieces;
             u32x4 pre[kDgLoads];
 #pragma unroll
             for (int k = 0; k < kDgLoads; ++k) {
@@ -212,7 +213,7 @@ __global__ __launch_bounds__(kDgThreads, kDgPerCU) void conv_dgrad_kernel(const 
 #pragma unroll
             for (int k = 0; k < kDgLoads; ++k) {
                 const int i = k * kDgThreads + t, row = div_small(i >> 3, inv_wo);
-                const int at = row * W + (i >> 3) - row * Wo + (imgs > 1 ? 2 + 2 * div_small(row, inv_ho) : 0) * W;
+                const int at = row * W + (i >> 3) - row * Wo + (MANY ? 2 + 2 * div_small(row, inv_ho) : 0) * W;
                 if (i < pieces) *(u32x4*)&s_y[(at + 2) * kYStride + (i & 7) * 16] = pre[k];
             }
             lds_barrier();
@@ -274,6 +275,7 @@ __device__ __forceinline__ bf16x8 join_tr(s16x4 lo, s16x4 hi) {
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
+template <bool MANY>
 __global__ __launch_bounds__(kWgThreads) void conv_wgrad_kernel(const uint16_t* __restrict__ x,
                                                                 const uint16_t* __restrict__ dy, int B, int H, int W,
                                                                 int rows, int bands, int imgs, int items, int shares,
@@ -295,9 +297,9 @@ __global__ __launch_bounds__(kWgThreads) void conv_wgrad_kernel(const uint16_t* 
     // output rows of the band of item it, over its images (several only where each is one band)
     auto band_rows = [&](int it, int& b, int& oy0) {
         const int q = it / bands;
-        b = q * imgs;
+        b = MANY ? q * imgs : q;
         oy0 = (it - q * bands) * rows;
-        return (B - b < imgs ? B - b : imgs) * (Ho - oy0 < rows ? Ho - oy0 : rows);
+        return (!MANY ? 1 : B - b < imgs ? B - b : imgs) * (Ho - oy0 < rows ? Ho - oy0 : rows);
     };
     auto fetch = [&](int it) {
         int b, oy0;
@@ -313,7 +315,8 @@ __global__ __launch_bounds__(kWgThreads) void conv_wgrad_kernel(const uint16_t* 
 #pragma unroll
         for (int k = 0; k < kXLoads; ++k) {
             const int i = k * kWgThreads + t < nx ? k * kWgThreads + t : nx - 1;
-            px[k] = xs[i + div_small(i >> 2, inv_in) * 2 * W * 4];  // two rows between the images' rows under the tap
+            // two rows lie between the images' rows under the tap
+            px[k] = xs[MANY ? i + div_small(i >> 2, inv_in) * 2 * W * 4 : i];
         }
     };
     float bsum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // this thread's eight channels of dy
@@ -459,8 +462,9 @@ bool conv_dgrad_64_32(const uint16_t* dy, const uint16_t* w, const uint16_t* mas
     const int imgs = band_images(bands, ((kDgMaxPx - 2) / W - 2) / H, B + kCUs - 1, kCUs);
     const int64_t items = ceil_div(B, imgs) * bands;
     if (items >= (1ll << 30)) return false;
-    conv_dgrad_kernel<<<(unsigned)std::min<int64_t>(items, kDgPerCU * kCUs), kDgThreads, 0, s>>>(
-        dy, w, mask, B, H, W, rows, bands, imgs, (int)items, inv_small(W - 2), imgs > 1 ? inv_small(H - 2) : 0, dx);
+    const auto kernel = imgs > 1 ? conv_dgrad_kernel<true> : conv_dgrad_kernel<false>;
+    kernel<<<(unsigned)std::min<int64_t>(items, kDgPerCU * kCUs), kDgThreads, 0, s>>>(
+        dy, w, mask, B, H, W, rows, bands, imgs, (int)items, inv_small(W - 2), inv_small(H - 2), dx);
     return true;
 }
 
@@ -476,8 +480,9 @@ bool conv_wgrad_32_64(const uint16_t* x, const uint16_t* dy, int B, int H, int W
     // every share the same number of bands, but for the last ones
     const int shares = (int)ceil_div(items, ceil_div(items, (int64_t)kWgShares));
     const int step = (int)ceil_div(shares, 8) * 8;
-    conv_wgrad_kernel<<<3 * step, kWgThreads, 0, s>>>(x, dy, B, H, W, rows, bands, imgs, (int)items, shares, step,
-                                                      inv_small(W - 2), imgs > 1 ? inv_small((H - 2) * W) : 0, dw, db);
+    const auto kernel = imgs > 1 ? conv_wgrad_kernel<true> : conv_wgrad_kernel<false>;
+    kernel<<<3 * step, kWgThreads, 0, s>>>(x, dy, B, H, W, rows, bands, imgs, (int)items, shares, step, inv_small(W - 2),
+                                           inv_small((H - 2) * W), dw, db);
     return true;
 }
 
